@@ -65,6 +65,9 @@ typedef enum {
  *   precision  a qaoa_precision value
  *   stream  hipStream_t to order all work on; NULL creates a private stream
  *   out     receives the handle
+ * C(z) = C(~z), so above one tile (n > 12 complex128, n > 13 complex64) the
+ * handle works on the half of the state with bit n-1 clear; every output is
+ * that of the whole state.
  * The handle allocates the state and cost diagonal on the current HIP device
  * (Sec. IV-B: state and cost arrays at initialisation, other buffers lazily when
  * first needed).  The cost diagonal is built here.
@@ -289,6 +292,7 @@ qaoa_status qaoa_profile_read(qaoa_handle h, int32_t kind, int64_t *launches, do
  * tile_bits[i] (TB = 12 for QAOA_C128, 13 for QAOA_C64: 64 KiB of state) and
  * rotates the qubits in target_bits[i]; the remaining tile bits are low
  * spectator bits kept for contiguous memory access (runs of >= 64 bytes).
+ * (MaxCut handles run half of the tiles, see qaoa_create_maxcut.)
  *   cap       capacity of the two output arrays
  *   npasses   receives the number of sweeps per layer
  * Errors: INVALID_ARGUMENT for n outside [1, QAOA_MAX_QUBITS], an unknown

@@ -43,6 +43,11 @@ struct qaoa_handle_s {
     int prec = QAOA_C128;
     int device = 0;
     uint64_t N = 0;
+    // MaxCut states of more than one tile are kept folded (qk::fold_state): the
+    // M = N / 2 amplitudes and cost entries with bit n-1 clear, at the start of
+    // buffers that are sized for all N.
+    bool fold = false;
+    uint64_t M = 0;  // amplitudes stored: N, or N / 2 when folded
     qaoa_allocator alloc{};  // device-memory provider (alloc == NULL: hipMalloc / hipFree)
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -144,7 +149,11 @@ inline uint64_t nblocks(int n, bool c64)
     const int tb = qk::tile_bits(c64);
     return n <= tb ? 1ull : (1ull << (n - tb));
 }
-inline uint64_t nblocks(const qaoa_handle h) { return nblocks(h->n, c64(h)); }
+inline uint64_t nblocks(const qaoa_handle h) { return nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0); }
+// Factor of the sums over the stored amplitudes.
+inline double sum_scale(const qaoa_handle h) { return h->fold ? 2.0 : 1.0; }
+// Qubits of a plain streaming kernel over the stored entries.
+inline int stored_bits(const qaoa_handle h) { return h->fold ? h->n - 1 : h->n; }
 
 qaoa_status check_handle(qaoa_handle h)
 {
@@ -214,6 +223,7 @@ qk::PassArgs pass_args(qaoa_handle h, const qk::PassPlan &pp, double beta)
     a.lam = h->lam;
     a.cost = h->cost;
     qk::make_geometry(h->n, pp, &a.geo);  // plans are validated when made
+    if (h->fold) qk::fold_geometry(h->n, pp, &a.geo);
     // Nontemporal accesses pay off for runs of >= 64 consecutive amplitudes; for
     // short runs the L2 must keep each line for the neighbouring tile.
     if (a.geo.t_dst[0] == 0 && a.geo.t_len[0] >= 6) a.flags |= qk::kStream;
@@ -278,7 +288,7 @@ int group_at(int l, int idx, int P) { return (l % 2 == 0) ? idx : P - 1 - idx; }
 // writes once, plus one read of the cost diagonal when it applies or measures C.
 double pass_bytes(qaoa_handle h, int mode, const qk::PassArgs &a)
 {
-    const double N = (double)h->N, s = (double)amp_bytes(h->prec), c = (double)cost_bytes(h->prec);
+    const double N = (double)h->M, s = (double)amp_bytes(h->prec), c = (double)cost_bytes(h->prec);
     const bool store = !(a.flags & qk::kNoStore);
     const bool initd = (a.flags & qk::kInit) != 0;
     if (mode == qk::kFwd)
@@ -529,14 +539,14 @@ qaoa_status ensure_lam(qaoa_handle h)
 
 qaoa_status fetch_results(qaoa_handle h, int nslots, uint64_t count, double *host)
 {
-    HIPCHECK(h, qk::launch_sum_slots(h->parts, count, count, nslots, h->res, h->stream));
+    HIPCHECK(h, qk::launch_sum_slots(h->parts, count, count, nslots, sum_scale(h), h->res, h->stream));
     HIPCHECK(h, hipMemcpyAsync(host, h->res, (size_t)nslots * sizeof(double), hipMemcpyDeviceToHost,
                                h->stream));
     HIPCHECK(h, hipStreamSynchronize(h->stream));
     return QAOA_OK;
 }
 
-qaoa_status create_common(int32_t n, int32_t precision, void *stream, qaoa_handle *out,
+qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *stream, qaoa_handle *out,
                           qaoa_handle *hh)
 {
     if (!out) return fail(QAOA_ERR_INVALID_ARGUMENT, "out is NULL");
@@ -547,6 +557,8 @@ qaoa_status create_common(int32_t n, int32_t precision, void *stream, qaoa_handl
     h->n = n;
     h->prec = precision;
     h->N = 1ull << n;
+    h->fold = qk::fold_state(n, precision == QAOA_C64, maxcut);
+    h->M = h->fold ? h->N / 2 : h->N;
     h->alloc = g_alloc;
     try {
         h->plan = qk::plan_passes(n, precision == QAOA_C64);
@@ -619,7 +631,7 @@ qaoa_status build_cost(qaoa_handle h, const std::vector<qk::CostPiece> &pieces, 
     hipError_t e = hipSuccess;
     if (bytes) e = hipMemcpyAsync(dev, pieces.data(), bytes, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess)
-        e = qk::launch_cost_pieces(c64(h), h->cost, h->n, (const qk::CostPiece *)dev,
+        e = qk::launch_cost_pieces(c64(h), h->cost, stored_bits(h), (const qk::CostPiece *)dev,
                                    (int64_t)pieces.size(), offset, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
@@ -643,11 +655,11 @@ qaoa_status make_pieces(std::vector<qk::CostPiece> *out, Make make)
 }
 
 // Creates the handle and its cost diagonal from pieces; on error nothing is left.
-qaoa_status create_with_pieces(int32_t n, int32_t precision, void *stream, qaoa_handle *out,
+qaoa_status create_with_pieces(int32_t n, int32_t precision, bool maxcut, void *stream, qaoa_handle *out,
                                const std::vector<qk::CostPiece> &pieces, double offset)
 {
     qaoa_handle h = nullptr;
-    qaoa_status st = create_common(n, precision, stream, out, &h);
+    qaoa_status st = create_common(n, precision, maxcut, stream, out, &h);
     if (st != QAOA_OK) return st;
     st = build_cost(h, pieces, offset);
     if (st != QAOA_OK) {
@@ -669,7 +681,7 @@ int handle_device(qaoa_handle h) { return h->device; }
 size_t noalloc_need(qaoa_handle h, int p)
 {
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    if (p == 0) return al((size_t)((h->N + kTile - 1) / kTile) * sizeof(double)) + sizeof(double);
+    if (p == 0) return al((size_t)((h->N + kTile - 1) / kTile) * sizeof(double)) + sizeof(double);  // (an upper bound when folded)
     const size_t nslots = 2 * (size_t)p + 1;
     return al(h->N * amp_bytes(h->prec)) + al(nslots * nblocks(h) * sizeof(double)) + nslots * sizeof(double);
 }
@@ -712,13 +724,13 @@ qaoa_status gradient_on_scratch(qaoa_handle h, int32_t p, const double *gamma, c
     double *res;
     int nslots;
     if (p == 0) {
-        const uint64_t T0 = (h->N + kTile - 1) / kTile;
+        const uint64_t T0 = (h->M + kTile - 1) / kTile;
         double *parts = (double *)base;
         res = (double *)(base + al(T0 * sizeof(double)));
         nslots = 1;
-        HIPCHECK(h, launch_fill_plus(c64(h), h->psi, h->n, h->stream));
-        HIPCHECK(h, launch_expect(c64(h), h->psi, h->cost, h->n, parts, h->stream));
-        HIPCHECK(h, launch_sum_slots(parts, T0, T0, 1, res, h->stream));
+        HIPCHECK(h, launch_fill_plus(c64(h), h->psi, h->n, h->M, h->stream));
+        HIPCHECK(h, launch_expect(c64(h), h->psi, h->cost, stored_bits(h), parts, h->stream));
+        HIPCHECK(h, launch_sum_slots(parts, T0, T0, 1, sum_scale(h), res, h->stream));
     } else {
         const uint64_t T = nblocks(h);
         nslots = 2 * p + 1;
@@ -727,7 +739,7 @@ qaoa_status gradient_on_scratch(qaoa_handle h, int32_t p, const double *gamma, c
         res = (double *)((char *)parts + al((size_t)nslots * T * sizeof(double)));
         qaoa_status st = enqueue_gradient(h, p, gamma, beta, lam, parts);
         if (st != QAOA_OK) return st;
-        HIPCHECK(h, launch_sum_slots(parts, T, T, nslots, res, h->stream));
+        HIPCHECK(h, launch_sum_slots(parts, T, T, nslots, sum_scale(h), res, h->stream));
     }
     if (out_is_device) {
         HIPCHECK(h, launch_gradient_out(res, p, E, dgamma, dbeta, h->stream));
@@ -757,7 +769,7 @@ qaoa_status qaoa_create_maxcut(int32_t n, int64_t m, const int32_t *edges, const
     std::vector<qk::CostPiece> pieces;
     if ((st = make_pieces(&pieces, [&] { return qk::cost_pieces_maxcut(m, edges, w); })) != QAOA_OK)
         return st;
-    return create_with_pieces(n, precision, stream, out, pieces, 0.0);
+    return create_with_pieces(n, precision, true, stream, out, pieces, 0.0);
 }
 
 qaoa_status qaoa_create_qubo(int32_t n, int64_t m, const int32_t *pairs, const double *J,
@@ -774,7 +786,7 @@ qaoa_status qaoa_create_qubo(int32_t n, int64_t m, const int32_t *pairs, const d
     std::vector<qk::CostPiece> pieces;
     if ((st = make_pieces(&pieces, [&] { return qk::cost_pieces_qubo(n, m, pairs, J, hl); })) != QAOA_OK)
         return st;
-    return create_with_pieces(n, precision, stream, out, pieces, offset);
+    return create_with_pieces(n, precision, false, stream, out, pieces, offset);
 }
 
 qaoa_status qaoa_create_poly(int32_t n, int64_t L, const uint64_t *masks, const double *w,
@@ -797,7 +809,7 @@ qaoa_status qaoa_create_poly(int32_t n, int64_t L, const uint64_t *masks, const 
     std::vector<qk::CostPiece> pieces;
     qaoa_status st = make_pieces(&pieces, [&] { return qk::cost_pieces_poly(L, masks, w); });
     if (st != QAOA_OK) return st;
-    return create_with_pieces(n, precision, stream, out, pieces, offset);
+    return create_with_pieces(n, precision, false, stream, out, pieces, offset);
 }
 
 qaoa_status qaoa_destroy(qaoa_handle h)
@@ -834,6 +846,15 @@ qaoa_status qaoa_cost_diagonal(qaoa_handle h, double *out, int32_t out_is_device
     if (st != QAOA_OK) return st;
     if (!out) return fail(QAOA_ERR_INVALID_ARGUMENT, "out is NULL");
     DeviceGuard dg(h->device);
+    if (h->fold) {
+        if (out_is_device && (uintptr_t)out % sizeof(double) == 0) {
+            HIPCHECK(h, qk::launch_unfold_cost(c64(h), h->cost, h->M, out, h->stream));
+            return QAOA_OK;
+        }
+        // the other half of the buffer takes the other half of the diagonal
+        HIPCHECK(h, c64(h) ? qk::launch_unfold_f32((const float *)h->cost, h->M, (float *)h->cost, h->stream)
+                           : qk::launch_unfold_cost(false, h->cost, h->M, (double *)h->cost, h->stream));
+    }
     if (!c64(h)) {
         HIPCHECK(h, hipMemcpyAsync(out, h->cost, h->N * 8,
                                    out_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
@@ -864,9 +885,9 @@ qaoa_status qaoa_cost_extrema(qaoa_handle h, double *cmin, double *cmax)
     if (!cmin || !cmax) return fail(QAOA_ERR_INVALID_ARGUMENT, "output is NULL");
     if (!h->extrema_valid) {
         DeviceGuard dg(h->device);
-        const uint64_t T = (h->N + qk::kTile - 1) / qk::kTile;
+        const uint64_t T = (h->M + qk::kTile - 1) / qk::kTile;
         if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * T)) != QAOA_OK) return st;
-        HIPCHECK(h, qk::launch_minmax(c64(h), h->cost, h->n, h->parts, h->parts + T, h->stream));
+        HIPCHECK(h, qk::launch_minmax(c64(h), h->cost, stored_bits(h), h->parts, h->parts + T, h->stream));
         HIPCHECK(h, qk::launch_minmax_final(h->parts, h->parts + T, T, h->res, h->stream));
         double r[2];
         HIPCHECK(h, hipMemcpyAsync(r, h->res, sizeof r, hipMemcpyDeviceToHost, h->stream));
@@ -889,13 +910,19 @@ qaoa_status qaoa_statevector(qaoa_handle h, int32_t p, const double *gamma, cons
     DeviceGuard dg(h->device);
     h->state_valid = false;
     if (p == 0) {
-        HIPCHECK(h, qk::launch_fill_plus(c64(h), h->psi, h->n, h->stream));
+        HIPCHECK(h, qk::launch_fill_plus(c64(h), h->psi, h->n, h->M, h->stream));
     } else if ((st = run_forward(h, p, gamma, beta, false, false)) != QAOA_OK) {
         return st;
     }
     if ((st = keep_angles(h, p, gamma, beta)) != QAOA_OK) return st;
     h->state_valid = true;
     if (out) {
+        if (h->fold) {
+            const bool direct = out_is_device && (uintptr_t)out % amp_bytes(h->prec) == 0;
+            // not direct: the other half of the buffer takes the other half of the state
+            HIPCHECK(h, qk::launch_unfold_state(c64(h), h->psi, h->M, direct ? out : h->psi, h->stream));
+            if (direct) return QAOA_OK;
+        }
         HIPCHECK(h, hipMemcpyAsync(out, h->psi, h->N * amp_bytes(h->prec),
                                    out_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                                    h->stream));
@@ -911,9 +938,9 @@ qaoa_status qaoa_expectation(qaoa_handle h, double *E)
     if (!E) return fail(QAOA_ERR_INVALID_ARGUMENT, "E is NULL");
     if (!h->state_valid) return fail(QAOA_ERR_NO_STATE, "no current state");
     DeviceGuard dg(h->device);
-    const uint64_t T = (h->N + qk::kTile - 1) / qk::kTile;
+    const uint64_t T = (h->M + qk::kTile - 1) / qk::kTile;
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, T)) != QAOA_OK) return st;
-    HIPCHECK(h, qk::launch_expect(c64(h), h->psi, h->cost, h->n, h->parts, h->stream));
+    HIPCHECK(h, qk::launch_expect(c64(h), h->psi, h->cost, stored_bits(h), h->parts, h->stream));
     return fetch_results(h, 1, T, E);
 }
 
@@ -993,7 +1020,7 @@ qaoa_status qaoa_gradient_from_state(qaoa_handle h, int32_t p, const double *gam
     h->state_valid = false;
     if ((st = enqueue_reverse(h, p, gamma, beta, h->lam, h->parts)) != QAOA_OK) return st;
     // slots 1 .. 2p (slot 0, E, is not written by the reverse sweep)
-    HIPCHECK(h, qk::launch_sum_slots(h->parts + T, T, T, 2 * p, h->res, h->stream));
+    HIPCHECK(h, qk::launch_sum_slots(h->parts + T, T, T, 2 * p, sum_scale(h), h->res, h->stream));
     std::vector<double> r((size_t)(2 * p));
     HIPCHECK(h, hipMemcpyAsync(r.data(), h->res, (size_t)(2 * p) * sizeof(double), hipMemcpyDeviceToHost,
                                h->stream));
@@ -1025,7 +1052,7 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     const size_t stage = out_is_device ? 0 : (size_t)shots * 2;
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, base + stage)) != QAOA_OK) return st;
     double *sub = h->parts, *pre = sub + nsub, *scr = pre + nsub + 1;
-    HIPCHECK(h, qk::launch_submass(c64(h), h->psi, h->n, sbits, sub, h->stream));
+    HIPCHECK(h, qk::launch_submass(c64(h), h->psi, h->n, h->fold, sbits, sub, h->stream));
     HIPCHECK(h, qk::launch_exclusive_scan(sub, nsub, pre, scr, h->stream));
     double T = 0;
     HIPCHECK(h, hipMemcpyAsync(&T, pre + nsub, sizeof T, hipMemcpyDeviceToHost, h->stream));
@@ -1037,7 +1064,7 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
         dz = (uint64_t *)(h->parts + base);
         dc = cost ? h->parts + base + shots : nullptr;
     }
-    HIPCHECK(h, qk::launch_shots(c64(h), h->psi, h->cost, h->n, sbits, pre, nsub, shots, seed, dz,
+    HIPCHECK(h, qk::launch_shots(c64(h), h->psi, h->cost, h->n, h->fold, sbits, pre, nsub, shots, seed, dz,
                                  dc, h->stream));
     if (!out_is_device) {
         HIPCHECK(h, hipMemcpyAsync(z, dz, (size_t)shots * 8, hipMemcpyDeviceToHost, h->stream));

@@ -46,16 +46,16 @@ namespace {
 
 // ------------------------------------------------------------ reductions
 
-// out[k] = sum_{i < count} parts[k * stride + i], one workgroup per slot, fixed order.
+// out[k] = scale * sum_{i < count} parts[k * stride + i], one workgroup per slot, fixed order.
 __global__ __launch_bounds__(kThreads) void k_sum_slots(const double *parts, uint64_t count,
-                                                        uint64_t stride, double *out)
+                                                        uint64_t stride, double scale, double *out)
 {
     __shared__ double red[4];
     const double *p = parts + (uint64_t)blockIdx.x * stride;
     double acc = 0.0;
     for (uint64_t i = threadIdx.x; i < count; i += kThreads) acc += p[i];
     const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) out[blockIdx.x] = s;
+    if (threadIdx.x == 0) out[blockIdx.x] = scale * s;
 }
 
 // Gradient outputs in device memory from the summed slots (p <= 64 threads).
@@ -217,7 +217,35 @@ __global__ __launch_bounds__(kThreads) void k_widen(const float *C32, double *ou
         out[z] = (double)C32[z];
 }
 
+// out[z] = out[2 half - 1 - z] = in[z]: a whole array from the half of a folded
+// one (z and ~z hold the same value).  Bound by memory: the half is read once,
+// where copying an unfolded array would read it all.  in == out leaves the
+// first half as it is.
+template <typename A, typename B>
+__device__ __forceinline__ B widen_to(A v)
+{
+    if constexpr (std::is_same<A, B>::value) return v;
+    else return (B)v;
+}
+template <typename A, typename B>
+__global__ __launch_bounds__(kThreads) void k_unfold(const A *in, uint64_t half, B *out)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
+    const bool self = (const void *)in == (const void *)out;
+    for (uint64_t z = (uint64_t)blockIdx.x * kThreads + threadIdx.x; z < half; z += stride) {
+        const B v = widen_to<A, B>(in[z]);
+        if (!self) out[z] = v;
+        out[2 * half - 1 - z] = v;
+    }
+}
+
 // ------------------------------------------------------------ sampling
+
+// Stored index of z: a folded state keeps z >= N/2 at its complement.
+__device__ __forceinline__ uint64_t stored(uint64_t z, uint64_t N, bool folded)
+{
+    return folded && z >= (N >> 1) ? N - 1 - z : z;
+}
 
 // Philox-4x32-10 (Salmon et al., SC'11): ten rounds of the two 32x32->64
 // multiplies with M0 = 0xD2511F53 and M1 = 0xCD9E8D57, key bumped by the Weyl
@@ -246,7 +274,7 @@ __device__ __forceinline__ double philox_uniform53(uint64_t seed, uint64_t s)
 // lane sums a fixed set of elements in order, then a shuffle tree.
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_submass(const typename Tr<R>::V *psi, uint64_t N,
-                                                      int sbits, uint64_t nsub, double *sub)
+                                                      bool folded, int sbits, uint64_t nsub, double *sub)
 {
     const uint64_t j = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
@@ -255,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void k_submass(const typename Tr<R>::V *p
     double acc = 0.0;
     for (uint64_t i = lane; i < sb; i += 64) {
         const uint64_t z = z0 + i;
-        if (z < N) acc += norm2(psi[z]);
+        if (z < N) acc += norm2(psi[stored(z, N, folded)]);
     }
     acc = wave_sum(acc);
     if (lane == 0) sub[j] = acc;
@@ -353,7 +381,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_final(const double *in, uint6
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi,
                                                     const typename Tr<R>::CT *C, uint64_t N,
-                                                    int sbits, const double *pre, uint64_t nsub,
+                                                    bool folded, int sbits, const double *pre, uint64_t nsub,
                                                     int64_t shots, uint64_t seed, uint64_t *zout,
                                                     double *cout)
 {
@@ -372,7 +400,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
         double acc = pre[lo];
         uint64_t zsel = ~0ull, zlast = z0;
         for (uint64_t z = z0; z < zend; ++z) {
-            const double pz = norm2(psi[z]);
+            const double pz = norm2(psi[stored(z, N, folded)]);
             if (pz > 0.0) zlast = z;
             acc += pz;
             if (acc > t) {
@@ -382,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
         }
         if (zsel == ~0ull) zsel = zlast;  // rounding left t at the sub-block's end
         zout[s] = zsel;
-        if (cout) cout[s] = (double)C[zsel];
+        if (cout) cout[s] = (double)C[stored(zsel, N, folded)];
     }
 }
 
@@ -450,10 +478,10 @@ hipError_t launch_pass(int mode, bool c64, const PassArgs &a, uint64_t nblocks, 
     }
 }
 
-hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots,
+hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots, double scale,
                             double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sum_slots, dim3(nslots), dim3(kThreads), 0, s, parts, count, stride, out);
+    hipLaunchKernelGGL(k_sum_slots, dim3(nslots), dim3(kThreads), 0, s, parts, count, stride, scale, out);
     return hipGetLastError();
 }
 
@@ -478,16 +506,43 @@ hipError_t launch_cost_pieces(bool c64, void *C, int n, const CostPiece *pieces,
     return hipGetLastError();
 }
 
-hipError_t launch_fill_plus(bool c64, void *psi, int n, hipStream_t s)
+hipError_t launch_fill_plus(bool c64, void *psi, int n, uint64_t count, hipStream_t s)
 {
-    const uint64_t N = 1ull << n;
-    const double amp = 1.0 / sqrt((double)N);
+    const double amp = 1.0 / sqrt((double)(1ull << n));
     if (c64)
-        hipLaunchKernelGGL(k_fill_plus<float>, dim3(grid_for(N)), dim3(kThreads), 0, s,
-                           (Tr<float>::V *)psi, N, (float)amp);
+        hipLaunchKernelGGL(k_fill_plus<float>, dim3(grid_for(count)), dim3(kThreads), 0, s,
+                           (Tr<float>::V *)psi, count, (float)amp);
     else
-        hipLaunchKernelGGL(k_fill_plus<double>, dim3(grid_for(N)), dim3(kThreads), 0, s,
-                           (Tr<double>::V *)psi, N, amp);
+        hipLaunchKernelGGL(k_fill_plus<double>, dim3(grid_for(count)), dim3(kThreads), 0, s,
+                           (Tr<double>::V *)psi, count, amp);
+    return hipGetLastError();
+}
+
+hipError_t launch_unfold_state(bool c64, const void *in, uint64_t half, void *out, hipStream_t s)
+{
+    if (c64)
+        hipLaunchKernelGGL((k_unfold<float2, float2>), dim3(grid_for(half)), dim3(kThreads), 0, s,
+                           (const float2 *)in, half, (float2 *)out);
+    else
+        hipLaunchKernelGGL((k_unfold<double2, double2>), dim3(grid_for(half)), dim3(kThreads), 0, s,
+                           (const double2 *)in, half, (double2 *)out);
+    return hipGetLastError();
+}
+
+hipError_t launch_unfold_f32(const float *in, uint64_t half, float *out, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_unfold<float, float>), dim3(grid_for(half)), dim3(kThreads), 0, s, in, half, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_unfold_cost(bool c64, const void *in, uint64_t half, double *out, hipStream_t s)
+{
+    if (c64)
+        hipLaunchKernelGGL((k_unfold<float, double>), dim3(grid_for(half)), dim3(kThreads), 0, s,
+                           (const float *)in, half, out);
+    else
+        hipLaunchKernelGGL((k_unfold<double, double>), dim3(grid_for(half)), dim3(kThreads), 0, s,
+                           (const double *)in, half, out);
     return hipGetLastError();
 }
 
@@ -543,17 +598,17 @@ uint64_t scan_scratch_doubles(uint64_t count)
     return (count + kScanChunk - 1) / kScanChunk + 1;
 }
 
-hipError_t launch_submass(bool c64, const void *psi, int n, int sbits, double *sub,
+hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub,
                           hipStream_t s)
 {
     const uint64_t N = 1ull << n, nsub = 1ull << (n - sbits);
     const unsigned nb = (unsigned)((nsub + 3) / 4);
     if (c64)
         hipLaunchKernelGGL(k_submass<float>, dim3(nb), dim3(kThreads), 0, s, (const Tr<float>::V *)psi,
-                           N, sbits, nsub, sub);
+                           N, folded, sbits, nsub, sub);
     else
         hipLaunchKernelGGL(k_submass<double>, dim3(nb), dim3(kThreads), 0, s,
-                           (const Tr<double>::V *)psi, N, sbits, nsub, sub);
+                           (const Tr<double>::V *)psi, N, folded, sbits, nsub, sub);
     return hipGetLastError();
 }
 
@@ -570,7 +625,7 @@ hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, 
     return hipGetLastError();
 }
 
-hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, int sbits,
+hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool folded, int sbits,
                         const double *pre, uint64_t nsub, int64_t shots, uint64_t seed,
                         uint64_t *z, double *cost, hipStream_t s)
 {
@@ -579,10 +634,10 @@ hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, int sbi
     const unsigned nb = grid_for((uint64_t)shots);
     if (c64)
         hipLaunchKernelGGL(k_shots<float>, dim3(nb), dim3(kThreads), 0, s, (const Tr<float>::V *)psi,
-                           (const float *)C, N, sbits, pre, nsub, shots, seed, z, cost);
+                           (const float *)C, N, folded, sbits, pre, nsub, shots, seed, z, cost);
     else
         hipLaunchKernelGGL(k_shots<double>, dim3(nb), dim3(kThreads), 0, s,
-                           (const Tr<double>::V *)psi, (const double *)C, N, sbits, pre, nsub, shots,
+                           (const Tr<double>::V *)psi, (const double *)C, N, folded, sbits, pre, nsub, shots,
                            seed, z, cost);
     return hipGetLastError();
 }

@@ -74,8 +74,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         const RegOffsets<0, WB> off(g);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            u[r] = ld(&psi[b0 | pA | off(r)], strm);
-            w[r] = ld(&psi[b1 | pA | off(r)], strm);
+            u[r] = ld(&psi[b0 ^ pA ^ off(r)], strm);
+            w[r] = ld(&psi[b1 ^ pA ^ off(r)], strm);
         }
     }
     // (measured: with this priority instruction after the loads the complex128
@@ -105,8 +105,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
     const RegOffsets<2, WB> off(g);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        st(vscale(u[r], sf), &psi[b0 | pC | off(r)], strm);
-        st(vscale(w[r], sf), &psi[b1 | pC | off(r)], strm);
+        st(vscale(u[r], sf), &psi[b0 ^ pC ^ off(r)], strm);
+        st(vscale(w[r], sf), &psi[b1 ^ pC ^ off(r)], strm);
     }
 }
 
@@ -139,8 +139,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         const RegOffsets<0, WB> off(g);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            cu[r] = ldnt(&cost[b0 | pA | off(r)]);
-            cw[r] = ldnt(&cost[b1 | pA | off(r)]);
+            cu[r] = ldnt(&cost[b0 ^ pA ^ off(r)]);
+            cw[r] = ldnt(&cost[b1 ^ pA ^ off(r)]);
         }
     }
     __builtin_amdgcn_s_setprio(0);
@@ -182,8 +182,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
     const RegOffsets<2, WB> off(g);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        stnt(vscale(u[r], sf), &psi[b0 | pC | off(r)]);
-        stnt(vscale(w[r], sf), &psi[b1 | pC | off(r)]);
+        stnt(vscale(u[r], sf), &psi[b0 ^ pC ^ off(r)]);
+        stnt(vscale(w[r], sf), &psi[b1 ^ pC ^ off(r)]);
     }
 }
 
@@ -214,8 +214,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         const RegOffsets<2, WB> off(g);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            cu[r] = ld(&cost[b0 | pC | off(r)], strm);
-            cw[r] = ld(&cost[b1 | pC | off(r)], strm);
+            cu[r] = ld(&cost[b0 ^ pC ^ off(r)], strm);
+            cw[r] = ld(&cost[b1 ^ pC ^ off(r)], strm);
         }
     }
     {
@@ -223,8 +223,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         const RegOffsets<0, WB> off(g);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            u[r] = ld(&psi[b0 | pA | off(r)], strm);
-            w[r] = ld(&psi[b1 | pA | off(r)], strm);
+            u[r] = ld(&psi[b0 ^ pA ^ off(r)], strm);
+            w[r] = ld(&psi[b1 ^ pA ^ off(r)], strm);
         }
     }
     __builtin_amdgcn_s_setprio(0);
@@ -279,8 +279,8 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
     const RegOffsets<0, WB> off(g);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        st(vscale(u[r], s2), &psi[b0 | pA | off(r)], strm);
-        st(vscale(w[r], s2), &psi[b1 | pA | off(r)], strm);
+        st(vscale(u[r], s2), &psi[b0 ^ pA ^ off(r)], strm);
+        st(vscale(w[r], s2), &psi[b1 ^ pA ^ off(r)], strm);
     }
 }
 

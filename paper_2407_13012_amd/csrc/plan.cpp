@@ -151,4 +151,10 @@ bool make_geometry(int n, const PassPlan &pp, Geometry *g)
     return tr.empty() ? false : tr[0].first == 0;
 }
 
+void fold_geometry(int n, const PassPlan &pp, Geometry *g)
+{
+    g->fold_bit = (uint32_t)(n - 1);
+    g->fold = ((pp.tile_bits >> (n - 1)) & 1ull) ? low_mask(n) : 0ull;
+}
+
 }  // namespace qk

@@ -71,6 +71,11 @@ struct Geometry {
     uint32_t f_src[kFreeRuns], f_dst[kFreeRuns], f_len[kFreeRuns];
     uint32_t tmask;  // tile-local bits that are rotated
     uint32_t tbits;  // number of valid tile-local bits (TB, or n when n < TB)
+    // Folded state (fold_state): index z with bit n-1 set is stored at its
+    // complement, so an offset with bit `fold_bit` set is XORed with `fold`
+    // (2^n - 1; 0: the tile does not hold bit n-1, or the state is not folded).
+    uint32_t fold_bit;
+    uint64_t fold;
 };
 
 // Pass plan of one mixer layer on n qubits (host).  Every qubit is a target of
@@ -82,6 +87,38 @@ struct Geometry {
 std::vector<PassPlan> plan_passes(int n, bool c64, int kmax = 10);
 // Kernel geometry of a plan entry; returns false if it needs more runs than supported.
 bool make_geometry(int n, const PassPlan &pp, Geometry *g);
+// Whether a state on n qubits is kept folded.  A cut does not change when every
+// vertex changes sides, C(z) = C(~z), and |+> and the X mixer have the same
+// symmetry, so psi(z) = psi(~z) for every MaxCut state: the half with bit n-1
+// clear is the whole state.  A pass that rotates bit n-1 finds the partners z
+// with that bit set at ~z, the others never leave the half, so every pass runs
+// half of its tiles on the same plan, with the same arithmetic per amplitude:
+// the sweeps are bound by memory, so their time halves with the tiles (E + G,
+// complex128: n = 26, p = 6 15.67 -> 7.64 ms; n = 24, p = 8 5.13 -> 2.69 ms).
+// One-tile states (n <= TB) have no tile to leave out and are kept whole.
+constexpr bool fold_state(int n, bool c64, bool maxcut) { return maxcut && n > tile_bits(c64); }
+// Geometry of the same pass over a folded state.
+void fold_geometry(int n, const PassPlan &pp, Geometry *g);
+
+// Tile-local index -> offset of the amplitude from the tile base: a linear map
+// over XOR (each tile bit goes to one global bit, bit n-1 of a folded state to
+// the complement of the others).
+__host__ __device__ __attribute__((always_inline)) inline uint64_t dep(uint32_t e, const Geometry &g)
+{
+    uint64_t o = 0;
+    for (int r = 0; r < kTileRuns; ++r)
+        o |= (uint64_t)((e >> g.t_src[r]) & ((1u << g.t_len[r]) - 1u)) << g.t_dst[r];
+    return o ^ (g.fold & (0ull - ((o >> g.fold_bit) & 1ull)));
+}
+
+// Tile index -> base index of the tile (the tile bits set to zero).
+__host__ __device__ __attribute__((always_inline)) inline uint64_t tile_base(uint64_t t, const Geometry &g)
+{
+    uint64_t o = 0;
+    for (int r = 0; r < kFreeRuns; ++r)
+        o |= ((t >> g.f_src[r]) & ((1ull << g.f_len[r]) - 1ull)) << g.f_dst[r];
+    return o;
+}
 
 struct PassArgs {
     void *psi;          // state / phi (in-out)
@@ -137,7 +174,8 @@ template <typename R, int SP>
 hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s);
 // Spectator class of a pass with kernels of its own (0 or 2..7), else -1.
 int static_spectators(const Geometry &g, bool c64, int mode);
-hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots,
+// out[k] = scale * (sum of slot k); scale 2 for the half sums of a folded state.
+hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots, double scale,
                             double *out, hipStream_t s);
 
 // Cost diagonal (Sec. IV-A, Eq. (2)).  The kernel gives each thread 16
@@ -165,7 +203,13 @@ std::vector<CostPiece> cost_pieces_poly(int64_t L, const uint64_t *masks, const 
 // `pieces` is device memory.
 hipError_t launch_cost_pieces(bool c64, void *C, int n, const CostPiece *pieces, int64_t count,
                               double offset, hipStream_t s);
-hipError_t launch_fill_plus(bool c64, void *psi, int n, hipStream_t s);
+// psi[0 .. count) = 2^{-n/2}
+hipError_t launch_fill_plus(bool c64, void *psi, int n, uint64_t count, hipStream_t s);
+// Whole arrays from folded ones: out[z] = out[2 half - 1 - z] = in[z], z < half
+// (amplitudes; cost entries widened to fp64).  out may be `in` itself (same type).
+hipError_t launch_unfold_state(bool c64, const void *in, uint64_t half, void *out, hipStream_t s);
+hipError_t launch_unfold_cost(bool c64, const void *in, uint64_t half, double *out, hipStream_t s);
+hipError_t launch_unfold_f32(const float *in, uint64_t half, float *out, hipStream_t s);
 hipError_t launch_expect(bool c64, const void *psi, const void *C, int n, double *parts,
                          hipStream_t s);
 hipError_t launch_minmax(bool c64, const void *C, int n, double *pmin, double *pmax,
@@ -175,13 +219,15 @@ hipError_t launch_minmax_final(const double *pmin, const double *pmax, uint64_t 
 hipError_t launch_widen_cost(const float *C32, double *out, uint64_t N, hipStream_t s);
 
 // Sampling: sub-block masses, their exclusive scan, then one thread per shot.
+// `folded`: psi (and C) hold the half of a folded state; masses and shots are
+// those of the whole one, summed in its order.
 int sample_subblock_bits(int n);
 uint64_t scan_scratch_doubles(uint64_t count);
-hipError_t launch_submass(bool c64, const void *psi, int n, int sbits, double *sub,
+hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub,
                           hipStream_t s);
 hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, double *scratch,
                                  hipStream_t s);
-hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, int sbits,
+hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool folded, int sbits,
                         const double *pre, uint64_t nsub, int64_t shots, uint64_t seed,
                         uint64_t *z, double *cost, hipStream_t s);
 

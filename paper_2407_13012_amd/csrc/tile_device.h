@@ -128,21 +128,11 @@ __host__ __device__ constexpr uint32_t owned()
     return ARR == 0 ? (15u << 6) : ARR == 1 ? (15u | (WB == 3 ? 1u << 12 : 0u)) : ((3u << 4) | (3u << 10));
 }
 
-// Tile-local index -> offset of the amplitude from the tile base.
-__device__ __forceinline__ uint64_t dep(uint32_t e, const Geometry &g)
-{
-    uint64_t o = 0;
-#pragma unroll
-    for (int r = 0; r < kTileRuns; ++r)
-        o |= (uint64_t)((e >> g.t_src[r]) & ((1u << g.t_len[r]) - 1u)) << g.t_dst[r];
-    return o;
-}
-
 // Offset of register r in arrangement ARR (the part of an amplitude's global
 // index that depends on r only).  dep() sends each tile bit to one global
-// bit, and the register index occupies its own tile bits, so the offset of r
-// is the OR of the offsets of its set bits: four dep() evaluations per
-// arrangement instead of one per register.
+// bit (or, for bit n-1 of a folded state, to the complement), and the register
+// index occupies its own tile bits, so offsets combine by XOR: four dep()
+// evaluations per arrangement instead of one per register.
 template <int ARR, int WB>
 struct RegOffsets {
     uint64_t b[4];
@@ -153,20 +143,10 @@ struct RegOffsets {
     }
     __device__ __forceinline__ uint64_t operator()(int r) const
     {
-        return ((r & 1) ? b[0] : 0ull) | ((r & 2) ? b[1] : 0ull) | ((r & 4) ? b[2] : 0ull) |
+        return ((r & 1) ? b[0] : 0ull) ^ ((r & 2) ? b[1] : 0ull) ^ ((r & 4) ? b[2] : 0ull) ^
                ((r & 8) ? b[3] : 0ull);
     }
 };
-
-// Tile index -> base index of the tile (the tile bits set to zero).
-__device__ __forceinline__ uint64_t tile_base(uint64_t t, const Geometry &g)
-{
-    uint64_t o = 0;
-#pragma unroll
-    for (int r = 0; r < kFreeRuns; ++r)
-        o |= ((t >> g.f_src[r]) & ((1ull << g.f_len[r]) - 1ull)) << g.f_dst[r];
-    return o;
-}
 
 // ------------------------------------------------------------ arithmetic
 
@@ -710,12 +690,12 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
 
     // Global index of register r in arrangement A / C: a per-thread part plus a
     // part that depends on r only (the same for every thread of the grid).
-    const uint64_t thrA = base | dep(elem<0, WB>(lane, wave, 0), g);
-    const uint64_t thrC = base | dep(elem<2, WB>(lane, wave, 0), g);
+    const uint64_t thrA = base ^ dep(elem<0, WB>(lane, wave, 0), g);
+    const uint64_t thrC = base ^ dep(elem<2, WB>(lane, wave, 0), g);
     const RegOffsets<0, WB> offA(g);
     const RegOffsets<2, WB> offC(g);
-#define ZA(r) (thrA | offA(r))
-#define ZC(r) (thrC | offC(r))
+#define ZA(r) (thrA ^ offA(r))
+#define ZC(r) (thrC ^ offC(r))
 #define VA(r) (full || elem<0, WB>(lane, wave, (r)) < lim)
 #define VC(r) (full || elem<2, WB>(lane, wave, (r)) < lim)
     // Block sums of the tile's E, <lam|X|phi> and <lam|C|phi> terms, taken
@@ -964,9 +944,9 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
                     // start of the tile they would be spilled
                     uint32_t tid2 = threadIdx.x;
                     asm volatile("" : "+v"(tid2));
-                    const uint64_t thrC2 = base | dep(elem<2, WB>(tid2 & 63u, tid2 >> 6, 0), g);
+                    const uint64_t thrC2 = base ^ dep(elem<2, WB>(tid2 & 63u, tid2 >> 6, 0), g);
 #pragma unroll
-                    for (int r = h; r < h + H; ++r) cv[r] = VC(r) ? ld(&cost[thrC2 | offC(r)], strm) : (CT)0;
+                    for (int r = h; r < h + H; ++r) cv[r] = VC(r) ? ld(&cost[thrC2 ^ offC(r)], strm) : (CT)0;
                 }
 #pragma unroll
                 for (int r = h; r < h + H; ++r)
@@ -1006,12 +986,12 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
             const R sb2 = (R)a.scl_b2;
             uint32_t tid3 = threadIdx.x;
             asm volatile("" : "+v"(tid3));
-            const uint64_t thrA3 = kLateCost ? (base | dep(elem<0, WB>(tid3 & 63u, tid3 >> 6, 0), g)) : thrA;
+            const uint64_t thrA3 = kLateCost ? (base ^ dep(elem<0, WB>(tid3 & 63u, tid3 >> 6, 0), g)) : thrA;
 #pragma unroll
             for (int r = 0; r < NR; ++r)
                 if (VA(r)) {
-                    st(vscale(f[r], sb2), &psi[thrA3 | offA(r)], strm);
-                    st(vscale(l[r], sb2), &lam[thrA3 | offA(r)], strm);
+                    st(vscale(f[r], sb2), &psi[thrA3 ^ offA(r)], strm);
+                    st(vscale(l[r], sb2), &lam[thrA3 ^ offA(r)], strm);
                 }
         } else {
             REDUCE();
@@ -1052,8 +1032,8 @@ __device__ __forceinline__ void tile_pass_fwd_fuse(const PassArgs &a, uint64_t t
     const bool strm = SP >= 0 ? stream_class(SP) : (a.flags & kStream) != 0;
     V *psi = (V *)a.psi;
     const CT *cost = (const CT *)a.cost;
-    const uint64_t thrA = base | dep(elem<0, WB>(lane, wave, 0), g);
-    const uint64_t thrC = base | dep(elem<2, WB>(lane, wave, 0), g);
+    const uint64_t thrA = base ^ dep(elem<0, WB>(lane, wave, 0), g);
+    const uint64_t thrC = base ^ dep(elem<2, WB>(lane, wave, 0), g);
     const RegOffsets<0, WB> offA(g);
     const RegOffsets<2, WB> offC(g);
     const V zero = {(R)0, (R)0};
@@ -1061,10 +1041,10 @@ __device__ __forceinline__ void tile_pass_fwd_fuse(const PassArgs &a, uint64_t t
     V v[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-        cv[r] = (full || elem<2, WB>(lane, wave, r) < lim) ? ld(&cost[thrC | offC(r)], strm) : (CT)0;
+        cv[r] = (full || elem<2, WB>(lane, wave, r) < lim) ? ld(&cost[thrC ^ offC(r)], strm) : (CT)0;
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-        v[r] = (full || elem<0, WB>(lane, wave, r) < lim) ? ld(&psi[thrA | offA(r)], strm) : zero;
+        v[r] = (full || elem<0, WB>(lane, wave, r) < lim) ? ld(&psi[thrA ^ offA(r)], strm) : zero;
     const R m1 = (R)a.mul_f, m2 = (R)a.mul_f2;
     // complex128 passes whose B arrangement holds no target bit go from A to C
     // (and back) with one transpose
@@ -1100,7 +1080,7 @@ __device__ __forceinline__ void tile_pass_fwd_fuse(const PassArgs &a, uint64_t t
     asm volatile("" : "+v"(thrS));
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-        if (full || elem<0, WB>(lane, wave, r) < lim) st(vscale(v[r], s2), &psi[thrS | offA(r)], strm);
+        if (full || elem<0, WB>(lane, wave, r) < lim) st(vscale(v[r], s2), &psi[thrS ^ offA(r)], strm);
 }
 
 }  // namespace
