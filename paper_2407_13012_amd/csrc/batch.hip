@@ -85,6 +85,8 @@ __device__ __forceinline__ void make_args(PassArgs &a, const BatchArgs &B, int n
     }
     a.geo.tmask = uni(gs.tmask);
     a.geo.tbits = uni(gs.tbits);
+    a.geo.fold_bit = 0;  // the slot holds the whole state
+    a.geo.fold = 0;
     a.xcd_g = 0;
     a.flags = 0;
     a.amp0 = 1.0 / sqrt((double)(1ull << n));
