@@ -307,16 +307,21 @@ qaoa_status qaoa_pass_plan(int32_t n, int32_t precision, int32_t cap, int32_t *n
  * optimisation driven by the simulator's gradients; here every instance's loop
  * runs on the device).
  *
- * A fixed grid of workgroups takes instances from an on-device queue, largest
- * n first.  A workgroup runs one instance start to end in its own scratch slot
- * (state, adjoint vector and cost diagonal, 2^nmax amplitudes each, complex128):
+ * Instances of more than 12 qubits run by size, all of one size in lockstep:
+ * every pass of a step is one launch over the tiles of all of them, and the
+ * sizes run side by side on streams of the batch.  For the others a fixed grid
+ * of workgroups takes instances from an on-device queue, largest n first, and a
+ * workgroup runs one instance start to end.  (Larger ones join that queue in a
+ * run whose phases |gamma C| could leave the fast reduction's range, 5e5.)
+ * The vectors live in `workgroups` scratch slots of 2^nmax amplitudes (state,
+ * adjoint vector and cost diagonal, complex128).  An instance's run is its
  * cost diagonal (as qaoa_create_maxcut), then `steps` Adam ascent steps on
  * E(gamma, beta) / sum_k |w_k|, each step one expectation + adjoint gradient
  * with the same tiled passes as qaoa_gradient, then E at the final angles.
  * Adam (Kingma & Ba 2015): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
  * theta += lr (m / (1-b1^t)) / (sqrt(v / (1-b2^t)) + eps), t = 1, 2, ...
- * The queue-reset kernel and the engine are captured once in a hipGraph and
- * replayed by every qaoa_batch_run.
+ * For a batch of instances of at most 12 qubits the queue-reset kernel and the
+ * engine are captured once in a hipGraph and replayed by every qaoa_batch_run.
  *
  * Instances of at most 12 qubits are a single 4096-amplitude tile.  With
  * resident_max_n set, those up to that size run in a second persistent launch
@@ -339,7 +344,7 @@ typedef struct {
     double eps;         /* > 0 */
     int32_t workgroups; /* persistent workgroups (scratch slots); 0 = 2 per compute unit */
     int32_t max_group;  /* most qubits rotated per mixer pass after the first, 1..10 */
-    int32_t use_graph;  /* nonzero: replay a captured hipGraph; 0: launch eagerly */
+    int32_t use_graph;  /* nonzero: replay a captured hipGraph (n <= 12 throughout); 0: launch eagerly */
     int32_t waves_per_simd; /* register budget of the engine kernel: 1 or 2 waves per SIMD (0 = 1) */
     int32_t group_by_n[QAOA_BATCH_MAX_QUBITS + 1]; /* per-n override of max_group; 0 = none */
     int32_t resident_max_n; /* instances with n <= this (0..12) keep state and adjoint vector in
@@ -368,7 +373,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
  * [count][p], finite).  Outputs (host, each may be NULL): gamma, beta
  * [count][p] the final angles; e_first [count] E at the start angles;
  * e_last [count] E at the final angles.  Synchronous.  Results depend only on
- * the inputs (each instance is processed by one workgroup in a fixed order).
+ * the inputs (each instance's sums are taken in a fixed order).
  * Errors: INVALID_ARGUMENT; DEVICE (the batch is then unusable).
  */
 qaoa_status qaoa_batch_run(qaoa_batch b, const double *gamma0, const double *beta0, double *gamma,
@@ -378,8 +383,10 @@ qaoa_status qaoa_batch_run(qaoa_batch b, const double *gamma0, const double *bet
  * Timeline of the last qaoa_batch_run: for every instance (host fp64 [count]
  * each, may be NULL) the time its workgroup took it from the queue and the
  * time it wrote its results, in seconds from the earliest start, read from the
- * device's constant-rate wall clock; which_launch (host int32 [count], may be
- * NULL) is 0 for the streamed launch and 1 for the LDS-resident one.  For
+ * device's constant-rate wall clock (for an instance run by size: the start
+ * and end of the instances that ran together); which_launch (host int32
+ * [count], may be NULL) is 0 for those and the streamed launch and 1 for the
+ * LDS-resident one.  For
  * measuring how evenly the persistent workgroups are loaded.
  * Errors: INVALID_ARGUMENT (no run yet); DEVICE.
  */

@@ -13,7 +13,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libqaoa.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "batch.hip", "mpnn.hip", "api.cpp", "plan.cpp", "lbfgs.cpp", "cost_terms.cpp", "noalloc.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "batch.hip", "batch_many.hip", "mpnn.hip", "api.cpp", "plan.cpp", "lbfgs.cpp", "cost_terms.cpp", "noalloc.hip")]
 # passes.hip is compiled once per precision and spectator class (see its header)
 PASS_SOURCE = os.path.join(HERE, "csrc", "passes.hip")
 PASS_VARIANTS = [(real, sp) for real in ("double", "float") for sp in (-1, 0, 2, 3, 4, 5, 6, 7)]
@@ -24,7 +24,8 @@ def units() -> list[tuple[str, list[str], str]]:
     out = [(s, [], os.path.basename(s) + ".o") for s in SOURCES]
     for real, sp in PASS_VARIANTS:
         tag = f"{'c128' if real == 'double' else 'c64'}_{'rt' if sp < 0 else 's%d' % sp}"
-        out.append((PASS_SOURCE, [f"-DQK_PASS_REAL={real}", f"-DQK_PASS_SP={sp}"], f"passes_{tag}.o"))
+        many = ["-DQK_PASS_MANY=1"] if real == "double" else []
+        out.append((PASS_SOURCE, [f"-DQK_PASS_REAL={real}", f"-DQK_PASS_SP={sp}", *many], f"passes_{tag}.o"))
     return out
 ARCH = os.environ.get("QAOA_OFFLOAD_ARCH", "gfx950")
 

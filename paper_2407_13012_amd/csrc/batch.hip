@@ -1,7 +1,10 @@
 // Batched engine: thousands of small MaxCut instances of uneven size, each
-// optimised with Adam on its QAOA angles, in one persistent launch.
+// optimised with Adam on its QAOA angles.
 //
-// A fixed grid of workgroups pops instances from a work queue (largest n
+// Instances of more than one tile (n > 12) run in lockstep, all of one size
+// together (batch_many.hip).  The others, one tile each, run in the persistent
+// launch below, which also takes every instance of a run whose phases could
+// leave the fast reduction's range (far_phases).  A fixed grid of workgroups pops instances from a work queue (largest n
 // first).  A workgroup owns one instance at a time and runs everything for it
 // in its own scratch slot: the cost diagonal (Sec. IV-A, cut indicator per
 // edge), then for every Adam step one expectation + adjoint gradient (the
@@ -11,6 +14,7 @@
 // the end of the queue, so the launch always drains.  The queue counter is
 // reset by a kernel, and the pair (reset, engine) is captured in a hipGraph.
 #include "qaoa.h"
+#include "batch_internal.h"
 #include "tile_device.h"
 
 #include <algorithm>
@@ -22,33 +26,6 @@
 
 namespace qk {
 namespace {
-
-constexpr int kMaxP = 16;       // depth limit of the batched engine
-constexpr int kMaxPasses = 16;  // passes per mixer layer
-constexpr int kMaxBatchN = QAOA_BATCH_MAX_QUBITS;
-
-struct BatchArgs {
-    int32_t count;
-    int32_t begin, end;     // this launch's range of the processing order
-    const int32_t *order;   // processing order (largest n first)
-    const int32_t *nq;      // [count] qubits
-    const int64_t *eoff;    // [count + 1] edge offsets
-    const int32_t *edges;   // [E][2]
-    const double *w;        // [E] (NULL: unit weights)
-    const double *scale;    // [count] objective scale (1 / sum |w|)
-    double *gamma, *beta;   // [count][p] start in, optimum out
-    double *e_first;        // [count] E at the start angles
-    double *e_last;         // [count] E at the final angles
-    int32_t p, steps;
-    double lr, b1, b2, eps;
-    const Geometry *geo;    // [(kMaxBatchN + 1) * kMaxPasses]
-    const int32_t *npass;   // [kMaxBatchN + 1]
-    double2 *psi, *lam;     // slot arrays, `slot` amplitudes each
-    double *cost;
-    uint64_t slot;
-    uint32_t *counter;      // this launch's queue counter
-    uint64_t *ticks;        // [count][2] device wall clock at an instance's start and end
-};
 
 // Values every lane of the workgroup holds alike (read from LDS or loaded from
 // a uniform address), moved to scalar registers so the tile code keeps its
@@ -469,7 +446,13 @@ struct qaoa_batch_s {
     hipStream_t stream = nullptr;
     std::vector<void *> allocs;
     std::vector<int32_t> order, nq;
-    qk::BatchArgs args{}, args_res{};
+    qk::BatchArgs args{}, args_res{};  // args: every streamed instance, order[0, split)
+    // order[0, nbig): more than one tile each, run by size class on their own streams
+    int nbig = 0;
+    std::vector<qk::SizeClass> classes;
+    hipStream_t streams[qk::kManyStreams] = {};
+    hipEvent_t fork = nullptr, join[qk::kManyStreams] = {};
+    double weight_bound = 0;  // largest sum of |weights| of an instance of the classes
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool use_graph = true;
@@ -503,20 +486,64 @@ qaoa_status upload(qaoa_batch b, T **dst, const T *src, size_t count)
     return QAOA_OK;
 }
 
-qaoa_status launch_engine(qaoa_batch b)
+// The persistent launch over order[begin, split).
+qaoa_status launch_streamed(qaoa_batch b, int begin)
 {
     hipLaunchKernelGGL(qk::k_reset, dim3(1), dim3(1), 0, b->stream, b->args.counter);
     BCHECK(b, hipGetLastError());
-    if (b->split > 0) {
-        const dim3 grid(std::min(b->workgroups, b->split));
-        if (b->wpe == 2) hipLaunchKernelGGL(qk::k_batch<2>, grid, dim3(qk::kThreads), 0, b->stream, b->args);
-        else hipLaunchKernelGGL(qk::k_batch<1>, grid, dim3(qk::kThreads), 0, b->stream, b->args);
+    if (b->split > begin) {
+        const dim3 grid(std::min(b->workgroups, b->split - begin));
+        qk::BatchArgs A = b->args;
+        A.begin = begin;
+        if (begin > 0) A.slot = 1ull << qk::kTileBits;  // one-tile instances, beside the size classes
+        if (b->wpe == 2) hipLaunchKernelGGL(qk::k_batch<2>, grid, dim3(qk::kThreads), 0, b->stream, A);
+        else hipLaunchKernelGGL(qk::k_batch<1>, grid, dim3(qk::kThreads), 0, b->stream, A);
         BCHECK(b, hipGetLastError());
     }
+    return QAOA_OK;
+}
+
+// The LDS-resident launch over order[split, count).
+qaoa_status launch_resident(qaoa_batch b)
+{
     if (b->split < b->count) {
         hipLaunchKernelGGL(qk::k_batch_res, dim3(b->res_workgroups), dim3(qk::kThreads), 0, b->stream,
                            b->args_res);
         BCHECK(b, hipGetLastError());
+    }
+    return QAOA_OK;
+}
+
+// Whether a phase |gamma C| of the size classes could leave the fast
+// reduction's range during a run from gamma0.  A step of Adam moves an angle
+// by at most lr / sqrt((1 - b2)(1 - b1^2 / b2)): Cauchy-Schwarz on the moment
+// sums, and the bias corrections only make it smaller.
+bool far_phases(qaoa_batch b, const double *gamma0)
+{
+    const qk::BatchArgs &A = b->args;
+    const double q = A.b2 > 0.0 ? (1.0 - A.b2) * (1.0 - A.b1 * A.b1 / A.b2) : 0.0;
+    if (!(q > 0.0) && A.steps > 0) return true;
+    double g = 0.0;
+    for (int k = 0; k < b->nbig; ++k)
+        for (int l = 0; l < b->p; ++l) g = std::max(g, std::fabs(gamma0[(size_t)b->order[k] * b->p + l]));
+    if (A.steps > 0) g += A.steps * A.lr / std::sqrt(q);
+    return !(g * b->weight_bound < qk::near_phase_limit(false));
+}
+
+// The streamed instances of a run: the size classes on their streams beside the
+// small instances on the batch's own.
+qaoa_status launch_classes(qaoa_batch b)
+{
+    BCHECK(b, hipEventRecord(b->fork, b->stream));
+    for (hipStream_t s : b->streams) BCHECK(b, hipStreamWaitEvent(s, b->fork, 0));
+    BCHECK(b, qk::run_classes(b->classes, b->args, b->streams));
+    return QAOA_OK;
+}
+qaoa_status join_classes(qaoa_batch b)
+{
+    for (int k = 0; k < qk::kManyStreams; ++k) {
+        BCHECK(b, hipEventRecord(b->join[k], b->streams[k]));
+        BCHECK(b, hipStreamWaitEvent(b->stream, b->join[k], 0));
     }
     return QAOA_OK;
 }
@@ -560,6 +587,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     const int64_t E = edge_offsets[count];
     if (E > 0 && !edges) return bfail(QAOA_ERR_INVALID_ARGUMENT, "edges is NULL");
     std::vector<double> scale(count, 1.0);
+    double weight_bound = 0.0;
     for (int i = 0; i < count; ++i) {
         double s = 0.0;
         for (int64_t k = edge_offsets[i]; k < edge_offsets[i + 1]; ++k) {
@@ -571,6 +599,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
             s += std::fabs(wk);
         }
         if (s > 0.0) scale[i] = 1.0 / s;
+        if (n[i] > qk::kTileBits) weight_bound = std::max(weight_bound, s);
     }
 
     qaoa_batch b = new (std::nothrow) qaoa_batch_s();
@@ -582,6 +611,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     b->use_graph = o.use_graph != 0;
     b->wpe = o.waves_per_simd == 2 ? 2 : 1;
     b->resident_max_n = o.resident_max_n;
+    b->weight_bound = weight_bound;
     auto cleanup = [&](qaoa_status st) {
         std::string keep = qk::error_message();
         qaoa_batch_destroy(b);
@@ -608,6 +638,13 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
         per_cu_res = 1;
     if (hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess)
         return cleanup(bfail(QAOA_ERR_DEVICE, "stream creation failed"));
+    if (nmax > qk::kTileBits) {
+        bool ok = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
+        for (int k = 0; k < qk::kManyStreams; ++k)
+            ok = ok && hipStreamCreateWithFlags(&b->streams[k], hipStreamNonBlocking) == hipSuccess &&
+                 hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming) == hipSuccess;
+        if (!ok) return cleanup(bfail(QAOA_ERR_DEVICE, "stream creation failed"));
+    }
 
     const uint64_t slot = 1ull << nmax;
     size_t fr = 0, tot = 0;
@@ -618,12 +655,14 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     // pass plans of every size in the batch
     std::vector<qk::Geometry> geo((qk::kMaxBatchN + 1) * qk::kMaxPasses);
     std::vector<int32_t> npass(qk::kMaxBatchN + 1, 0);
+    std::vector<std::vector<qk::PassPlan>> plans(qk::kMaxBatchN + 1);
     for (int m = 2; m <= nmax; ++m) {
         const int kg = o.group_by_n[m] ? o.group_by_n[m] : o.max_group;
         const std::vector<qk::PassPlan> pl = qk::plan_passes(m, false, kg);
         if ((int)pl.size() > qk::kMaxPasses) return cleanup(bfail(QAOA_ERR_UNSUPPORTED, "too many passes"));
         npass[m] = (int32_t)pl.size();
         for (size_t j = 0; j < pl.size(); ++j) qk::make_geometry(m, pl[j], &geo[m * qk::kMaxPasses + j]);
+        plans[m] = pl;
     }
     std::vector<int32_t> order(count);
     std::iota(order.begin(), order.end(), 0);
@@ -637,6 +676,18 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     b->res_workgroups = std::min({per_cu_res * prop.multiProcessorCount, b->workgroups, std::max(count - b->split, 1)});
     b->order = order;
     b->nq.assign(n, n + count);
+    // The slots hold `workgroups` whole states of the largest size.  The small
+    // instances use the start of theirs, packed at one tile each, the size
+    // classes what lies behind.
+    while (b->nbig < count && n[order[b->nbig]] > qk::kTileBits) ++b->nbig;
+    const uint64_t small = (uint64_t)b->workgroups << qk::kTileBits;
+    size_t scratch = 0;
+    try {
+        if (b->nbig)
+            b->classes = qk::make_classes(order, n, b->nbig, p, (uint64_t)b->workgroups * slot - small, plans, &scratch);
+    } catch (...) {
+        return cleanup(bfail(QAOA_ERR_OUT_OF_MEMORY, "host allocation"));
+    }
 
     qk::BatchArgs &A = b->args;
     qaoa_status st;
@@ -647,6 +698,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     double2 *d_psi, *d_lam;
     uint32_t *d_cnt;
     uint64_t *d_ticks;
+    char *d_scratch;
     if ((st = upload(b, &d_order, order.data(), count)) != QAOA_OK ||
         (st = upload(b, &d_n, n, count)) != QAOA_OK ||
         (st = upload(b, &d_eoff, edge_offsets, (size_t)count + 1)) != QAOA_OK ||
@@ -663,8 +715,10 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
         (st = upload<double2>(b, &d_lam, nullptr, (size_t)b->workgroups * slot)) != QAOA_OK ||
         (st = upload<double>(b, &d_cost, nullptr, (size_t)b->workgroups * slot)) != QAOA_OK ||
         (st = upload<uint32_t>(b, &d_cnt, nullptr, 2)) != QAOA_OK ||
-        (st = upload<uint64_t>(b, &d_ticks, nullptr, (size_t)count * 2)) != QAOA_OK)
+        (st = upload<uint64_t>(b, &d_ticks, nullptr, (size_t)count * 2)) != QAOA_OK ||
+        (st = upload<char>(b, &d_scratch, nullptr, scratch)) != QAOA_OK)
         return cleanup(st);
+    qk::place_classes(b->classes, p, d_psi + small, d_lam + small, d_cost + small, d_scratch);
     A.count = count;
     A.begin = 0;
     A.end = b->split;
@@ -698,10 +752,12 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     b->args_res.counter = d_cnt + 1;
     if (hipStreamSynchronize(b->stream) != hipSuccess) return cleanup(bfail(QAOA_ERR_DEVICE, "upload failed"));
 
-    if (b->use_graph) {
+    // the graph: the persistent launches of a batch of one-tile instances
+    if (b->use_graph && !b->nbig) {
         if (hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return cleanup(bfail(QAOA_ERR_DEVICE, "graph capture failed"));
-        st = launch_engine(b);
+        st = launch_streamed(b, 0);
+        if (st == QAOA_OK) st = launch_resident(b);
         hipGraph_t gr = nullptr;
         const hipError_t e = hipStreamEndCapture(b->stream, &gr);
         b->graph = gr;
@@ -740,10 +796,15 @@ qaoa_status qaoa_batch_run(qaoa_batch b, const double *gamma0, const double *bet
     qk::BatchArgs &A = b->args;
     BCHECK(b, hipMemcpyAsync(A.gamma, gamma0, np * 8, hipMemcpyHostToDevice, b->stream));
     BCHECK(b, hipMemcpyAsync(A.beta, beta0, np * 8, hipMemcpyHostToDevice, b->stream));
-    if (b->use_graph) {
+    qaoa_status st = QAOA_OK;
+    if (b->exec) {
         BCHECK(b, hipGraphLaunch(b->exec, b->stream));
     } else {
-        qaoa_status st = launch_engine(b);
+        const bool classes = b->nbig && !far_phases(b, gamma0);
+        if (classes) st = launch_classes(b);
+        if (st == QAOA_OK) st = launch_streamed(b, classes ? b->nbig : 0);
+        if (st == QAOA_OK && classes) st = join_classes(b);
+        if (st == QAOA_OK) st = launch_resident(b);
         if (st != QAOA_OK) return st;
     }
     if (gamma) BCHECK(b, hipMemcpyAsync(gamma, A.gamma, np * 8, hipMemcpyDeviceToHost, b->stream));
@@ -783,6 +844,12 @@ qaoa_status qaoa_batch_destroy(qaoa_batch b)
 {
     if (!b) return QAOA_OK;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
+    for (int k = 0; k < qk::kManyStreams; ++k) {
+        if (b->streams[k]) (void)hipStreamSynchronize(b->streams[k]);
+        if (b->join[k]) (void)hipEventDestroy(b->join[k]);
+        if (b->streams[k]) (void)hipStreamDestroy(b->streams[k]);
+    }
+    if (b->fork) (void)hipEventDestroy(b->fork);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (void *p : b->allocs) (void)hipFree(p);

@@ -478,6 +478,23 @@ hipError_t launch_pass(int mode, bool c64, const PassArgs &a, uint64_t nblocks, 
     }
 }
 
+hipError_t launch_many(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
+                       hipStream_t s)
+{
+    int sp = static_spectators(a.geo, false, mode);
+    if (sp >= 0 && stream_class(sp) != ((a.flags & kStream) != 0)) sp = -1;
+    switch (sp) {
+    case 0: return launch_many_sp<0>(mode, a, m, nblocks, count, s);
+    case 2: return launch_many_sp<2>(mode, a, m, nblocks, count, s);
+    case 3: return launch_many_sp<3>(mode, a, m, nblocks, count, s);
+    case 4: return launch_many_sp<4>(mode, a, m, nblocks, count, s);
+    case 5: return launch_many_sp<5>(mode, a, m, nblocks, count, s);
+    case 6: return launch_many_sp<6>(mode, a, m, nblocks, count, s);
+    case 7: return launch_many_sp<7>(mode, a, m, nblocks, count, s);
+    default: return launch_many_sp<-1>(mode, a, m, nblocks, count, s);
+    }
+}
+
 hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots, double scale,
                             double *out, hipStream_t s)
 {

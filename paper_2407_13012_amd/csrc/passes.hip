@@ -22,6 +22,9 @@
 #ifndef QK_PASS_SP
 #error "QK_PASS_SP (spectator class, -1 for the run-time mask) must be defined"
 #endif
+#ifndef QK_PASS_MANY  // 1 in the complex128 units: with the sweeps of the batched engine
+#define QK_PASS_MANY 0
+#endif
 
 namespace qk {
 namespace {
@@ -30,9 +33,8 @@ namespace {
 // complex128, 16 for complex64, whose registers are capped accordingly.  The
 // one-pass turn (n <= TB) runs a single workgroup and keeps the full register file.
 template <typename R, int MODE, bool TM, int SP>
-__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(MODE == kTurnPhase ? 1 : Tr<R>::MINW))) void k_pass(PassArgs a)
+__device__ __forceinline__ void pass_body(const PassArgs &a, typename Tr<R>::V *lds)
 {
-    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
     const uint64_t b = blockIdx.x;
     const uint64_t t = xcd_tile(b, a.xcd_g);
     double sums[4];
@@ -44,6 +46,12 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(MODE 
         if (MODE == kTurnPhase || (MODE == kBwd && (a.flags & kPhaseOut))) a.part_g[b] = sums[2];
     }
 }
+template <typename R, int MODE, bool TM, int SP>
+__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(MODE == kTurnPhase ? 1 : Tr<R>::MINW))) void k_pass(PassArgs a)
+{
+    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
+    pass_body<R, MODE, TM, SP>(a, lds);
+}
 
 // Plain forward sweep (no phase, no E, full tiles of spectator class SP), two
 // tiles per workgroup: tiles 2i and 2i + 1, which differ in the lowest free
@@ -54,12 +62,11 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(MODE 
 // backward sweep does with its two vectors.  Measured at n = 32: 25.2 vs
 // 27.2 ms per complex128 sweep, 12.9 vs 14.9 ms per complex64 sweep.
 template <typename R, bool TM, int SP>
-__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_fwd_pair(PassArgs a)
+__device__ __forceinline__ void fwd_pair_body(const PassArgs &a, typename Tr<R>::V *lds)
 {
     using V = typename Tr<R>::V;
     constexpr int WB = Tr<R>::WB, NR = Tr<R>::NR;
     constexpr bool strm = stream_class(SP);
-    __shared__ V lds[kLdsTotal<R>];
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const uint32_t lane = tid & 63u, wave = tid >> 6;
@@ -109,6 +116,12 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         st(vscale(w[r], sf), &psi[b1 ^ pC ^ off(r)], strm);
     }
 }
+template <typename R, bool TM, int SP>
+__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_fwd_pair(PassArgs a)
+{
+    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
+    fwd_pair_body<R, TM, SP>(a, lds);
+}
 
 // The first sweep of an evolution (layer 1's phase on the uniform state, then
 // its first mixer group: no state is read, the cost entries are), two tiles per
@@ -119,12 +132,11 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
 // with kInit | kPhaseIn, so results are bitwise the same.  Its runs are long,
 // so its accesses are nontemporal (kStream, which the launcher requires).
 template <typename R, bool TM>
-__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_init_pair(PassArgs a)
+__device__ __forceinline__ void init_pair_body(const PassArgs &a, typename Tr<R>::V *lds)
 {
     using V = typename Tr<R>::V;
     using CT = typename Tr<R>::CT;
     constexpr int WB = Tr<R>::WB, NR = Tr<R>::NR, SP = 0;
-    __shared__ V lds[kLdsTotal<R>];
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const uint32_t lane = tid & 63u, wave = tid >> 6;
@@ -186,18 +198,23 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         stnt(vscale(w[r], sf), &psi[b1 ^ pC ^ off(r)]);
     }
 }
+template <typename R, bool TM>
+__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_init_pair(PassArgs a)
+{
+    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
+    init_pair_body<R, TM>(a, lds);
+}
 
 // Layer-boundary forward sweep (tile_pass_fwd_fuse) in tile pairs: the two
 // tiles' rotations of layer l, the phase of layer l + 1 and its rotations,
 // interleaved; the arithmetic per amplitude is tile_pass_fwd_fuse's.
 template <typename R, bool TM, bool TM2, int SP>
-__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_fuse_pair(PassArgs a)
+__device__ __forceinline__ void fuse_pair_body(const PassArgs &a, typename Tr<R>::V *lds)
 {
     using V = typename Tr<R>::V;
     using CT = typename Tr<R>::CT;
     constexpr int WB = Tr<R>::WB, NR = Tr<R>::NR;
     constexpr bool strm = stream_class(SP);
-    __shared__ V lds[kLdsTotal<R>];
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const uint32_t lane = tid & 63u, wave = tid >> 6;
@@ -283,13 +300,18 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         st(vscale(w[r], s2), &psi[b1 ^ pA ^ off(r)], strm);
     }
 }
+template <typename R, bool TM, bool TM2, int SP>
+__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_fuse_pair(PassArgs a)
+{
+    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
+    fuse_pair_body<R, TM, TM2, SP>(a, lds);
+}
 
 // Layer-boundary passes (kFwdFuse, kBwdFuse); TM / TM2 are the factored forms
 // of the two rotations.  Same tile order and partial layout as k_pass.
 template <typename R, int MODE, bool TM, bool TM2, int SP>
-__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_pass_fuse(PassArgs a)
+__device__ __forceinline__ void pass_fuse_body(const PassArgs &a, typename Tr<R>::V *lds)
 {
-    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
     const uint64_t b = blockIdx.x;
     const uint64_t t = xcd_tile(b, a.xcd_g);
     if constexpr (MODE == kFwdFuse) {
@@ -304,6 +326,77 @@ __global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>
         }
     }
 }
+template <typename R, int MODE, bool TM, bool TM2, int SP>
+__global__ __launch_bounds__(Tr<R>::NT) __attribute__((amdgpu_waves_per_eu(Tr<R>::MINW))) void k_pass_fuse(PassArgs a)
+{
+    __shared__ typename Tr<R>::V lds[kLdsTotal<R>];
+    pass_fuse_body<R, MODE, TM, TM2, SP>(a, lds);
+}
+
+// ---- the same sweeps over many instances at once (batched engine)
+//
+// blockIdx.y is the instance, blockIdx.x its tile.  The arithmetic is that of
+// the single-instance kernels; only where the vectors and the angles come from
+// differs.  Every rotation is in the tan form (LayerCoef).
+#if QK_PASS_MANY
+__device__ __forceinline__ double uni_d(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// This workgroup's instance filled into the pass arguments.
+__device__ __forceinline__ void many_args(PassArgs &a, const ManyArgs &m)
+{
+    const uint64_t y = blockIdx.y;
+    a.psi = (double2 *)a.psi + y * m.stride;
+    a.lam = (double2 *)a.lam + y * m.stride;
+    a.cost = (const double *)a.cost + y * m.stride;
+    a.part_e += y * m.tiles;
+    a.part_b += y * m.tiles;
+    a.part_g += y * m.tiles;
+    a.part_b2 += y * m.tiles;
+    const LayerCoef *c = m.coef + y * (uint64_t)m.p;
+    const int k = popc(a.geo.tmask);
+    const LayerCoef &c1 = c[m.layer];
+    a.mul_f = uni_d(c1.mul);
+    a.mul_b = -a.mul_f;
+    a.fac_f = a.fac_b = uni_d(c1.fac);
+    a.scl_f = a.scl_b = uni_d(upow(a.fac_f, k));
+    const LayerCoef &c2 = c[m.layer2];
+    a.mul_f2 = uni_d(c2.mul);
+    a.mul_b2 = -a.mul_f2;
+    a.fac_b2 = uni_d(c2.fac);
+    a.scl_f2 = a.scl_b2 = uni_d(upow(a.fac_b2, k));
+    a.gamma_in = a.gamma_out = uni_d(c[m.layer_phase].gamma);
+}
+
+template <int MODE, int SP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_many_pass(PassArgs a, ManyArgs m)
+{
+    __shared__ double2 lds[kLdsTotal<double>];
+    many_args(a, m);
+    pass_body<double, MODE, true, SP>(a, lds);
+}
+template <int MODE, int SP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_many_fuse(PassArgs a, ManyArgs m)
+{
+    __shared__ double2 lds[kLdsTotal<double>];
+    many_args(a, m);
+    pass_fuse_body<double, MODE, true, true, SP>(a, lds);
+}
+template <int KIND, int SP>  // 0 plain, 1 first sweep, 2 layer boundary
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_many_pair(PassArgs a, ManyArgs m)
+{
+    __shared__ double2 lds[kLdsTotal<double>];
+    many_args(a, m);
+    if constexpr (KIND == 0) fwd_pair_body<double, true, SP>(a, lds);
+    else if constexpr (KIND == 1) init_pair_body<double, true>(a, lds);
+    else fuse_pair_body<double, true, true, SP>(a, lds);
+}
+#endif
 
 // Arguments of a tile-pair launch: the XCD grouping must divide the number of
 // pairs (xcd_tile is a permutation of [0, count) only when 8 * 2^G divides count).
@@ -393,5 +486,43 @@ hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStre
 }
 
 template hipError_t launch_pass_sp<QK_PASS_REAL, QK_PASS_SP>(int, const PassArgs &, uint64_t, hipStream_t);
+
+#if QK_PASS_MANY
+// The kernel choice of launch_single / launch_fuse for many instances.
+template <int SP>
+hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
+                          hipStream_t s)
+{
+    const dim3 grid((unsigned)nblocks, count), block(256);
+    const dim3 half((unsigned)(nblocks / 2), count);
+    if constexpr (SP >= 0) {
+        if (nblocks % 2 == 0) {
+            const PassArgs b = pair_args(a, nblocks / 2);
+            constexpr int kPlainMask = kInit | kPhaseIn | kEOut | kNoStore;
+            if (SP == 0 && mode == kFwd && a.flags == (kInit | kPhaseIn | kStream)) {
+                hipLaunchKernelGGL((k_many_pair<1, 0>), half, block, 0, s, b, m);
+                return hipGetLastError();
+            }
+            if (mode == kFwd && !(a.flags & kPlainMask)) {
+                hipLaunchKernelGGL((k_many_pair<0, SP>), half, block, 0, s, b, m);
+                return hipGetLastError();
+            }
+            if (mode == kFwdFuse) {
+                hipLaunchKernelGGL((k_many_pair<2, SP>), half, block, 0, s, b, m);
+                return hipGetLastError();
+            }
+        }
+    }
+    if (mode == kFwd) hipLaunchKernelGGL((k_many_pass<kFwd, SP>), grid, block, 0, s, a, m);
+    else if (mode == kTurn) hipLaunchKernelGGL((k_many_pass<kTurn, SP>), grid, block, 0, s, a, m);
+    else if (mode == kBwd) hipLaunchKernelGGL((k_many_pass<kBwd, SP>), grid, block, 0, s, a, m);
+    else if (mode == kFwdFuse) hipLaunchKernelGGL((k_many_fuse<kFwdFuse, SP>), grid, block, 0, s, a, m);
+    else if (mode == kBwdFuse) hipLaunchKernelGGL((k_many_fuse<kBwdFuse, SP>), grid, block, 0, s, a, m);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+template hipError_t launch_many_sp<QK_PASS_SP>(int, const PassArgs &, const ManyArgs &, uint64_t, unsigned,
+                                               hipStream_t);
+#endif
 
 }  // namespace qk

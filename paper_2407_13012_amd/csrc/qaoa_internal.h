@@ -172,6 +172,25 @@ hipError_t launch_pass(int mode, bool c64, const PassArgs &a, uint64_t nblocks, 
 // kernels that read the target mask at run time.
 template <typename R, int SP>
 hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s);
+// The same passes over `count` complex128 instances of one size (batched engine).
+// Instance y's vectors start y * stride entries after those of PassArgs, its
+// partials y * tiles doubles after, its angles are coef[y * p + layer]: `layer`
+// gives the first rotation, `layer2` the second (layer-boundary passes),
+// `layer_phase` the phase.
+struct LayerCoef {
+    double gamma;
+    double mul, fac;  // tan(b') and cos(b'), b' = beta reduced to [-pi/4, pi/4]
+};
+struct ManyArgs {
+    const LayerCoef *coef;
+    uint64_t stride, tiles;
+    int32_t p, layer, layer2, layer_phase;
+};
+hipError_t launch_many(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
+                       hipStream_t s);
+template <int SP>
+hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
+                          hipStream_t s);
 // Spectator class of a pass with kernels of its own (0 or 2..7), else -1.
 int static_spectators(const Geometry &g, bool c64, int mode);
 // out[k] = scale * (sum of slot k); scale 2 for the half sums of a folded state.
