@@ -271,15 +271,36 @@ __device__ __forceinline__ double philox_uniform53(uint64_t seed, uint64_t s)
 }
 
 // Mass of each sub-block of 2^sbits amplitudes: one wave per sub-block, each
-// lane sums a fixed set of elements in order, then a shuffle tree.
+// lane sums a fixed set of elements in order, then a shuffle tree.  The mirror
+// image of a folded state's sub-block holds the same elements, lanes and order
+// reversed: its wave takes both sums from one read (sub-blocks of 256, n <= 32;
+// the tree over reversed lanes pairs the same sums).
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_submass(const typename Tr<R>::V *psi, uint64_t N,
                                                       bool folded, int sbits, uint64_t nsub, double *sub)
 {
     const uint64_t j = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
-    if (j >= nsub) return;  // whole wave exits together
+    const bool both = folded && sbits == 8;
+    if (j >= (both ? nsub / 2 : nsub)) return;  // whole wave exits together
     const uint64_t sb = 1ull << sbits, z0 = j << sbits;
+    if (both) {
+        double q[4], a = 0.0, b = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) q[r] = norm2(psi[z0 + lane + 64 * r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            a += q[r];
+            b += q[3 - r];
+        }
+        a = wave_sum(a);
+        b = wave_sum(b);
+        if (lane == 0) {
+            sub[j] = a;
+            sub[nsub - 1 - j] = b;
+        }
+        return;
+    }
     double acc = 0.0;
     for (uint64_t i = lane; i < sb; i += 64) {
         const uint64_t z = z0 + i;
@@ -313,11 +334,18 @@ __device__ __forceinline__ double block_exclusive(double x, double *sh, double *
     sh[threadIdx.x] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
+        // a chain of 256 adds; the reads of 16 of them at a time do not wait for it
+        // (one by one the chain took 6 of the kernel's 8 us)
         double run = 0.0;
-        for (int i = 0; i < kThreads; ++i) {
-            const double v = sh[i];
-            sh[i] = run;
-            run += v;
+        for (int i = 0; i < kThreads; i += 16) {
+            double v[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = sh[i + r];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                sh[i + r] = run;
+                run += v[r];
+            }
         }
         sh[kThreads] = run;
     }
@@ -374,43 +402,84 @@ __global__ __launch_bounds__(kThreads) void k_scan_final(const double *in, uint6
     if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = tot[nchunks];
 }
 
-// One thread per shot (grid-stride): u -> target t = u * total, binary search over the
-// sub-block prefix, then a sequential scan inside the sub-block for the first
+// W shots per wave (grid-stride), a lane each: u -> target t = u * total, binary search
+// over the sub-block prefix, then a sequential scan inside the sub-block for the first
 // z whose cumulative mass exceeds t.  A zero-probability z never satisfies the
 // test (its cumulative mass equals its predecessor's), so it is never returned.
-template <typename R>
+//
+// The 64 scans of a wave are in 64 different sub-blocks.  Read by its own lane, each
+// amplitude costs a cache line (1.20 ms for 10^6 shots at n = 26, complex128, also
+// with 16 loads ahead of the chain of sums).  Here eight lanes read eight consecutive
+// amplitudes of one shot, and the masses go to the shot's lane through LDS: 0.43 ms,
+// of which 0.18 are the chains (n = 14) and the rest 2.1 GB of reads.
+template <typename R, int W>
 __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi,
                                                     const typename Tr<R>::CT *C, uint64_t N,
                                                     bool folded, int sbits, const double *pre, uint64_t nsub,
                                                     int64_t shots, uint64_t seed, uint64_t *zout,
                                                     double *cout)
 {
+    constexpr int kLoads = 8, kRows = W / 8, kStep = 8 * kLoads / kRows;  // loads in flight; amplitudes per turn
+    __shared__ double mass[kThreads / 64][W][kStep + 1];
     const double T = pre[nsub];
-    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-    for (uint64_t s = (uint64_t)blockIdx.x * kThreads + threadIdx.x; s < (uint64_t)shots; s += stride) {
+    const uint32_t lane = threadIdx.x & 63u, sub = lane & 7u, row = lane >> 3;
+    double (*m)[kStep + 1] = mass[threadIdx.x >> 6];
+    const uint64_t sb = 1ull << sbits;
+    const uint64_t stride = (uint64_t)gridDim.x * (kThreads / 64) * W;
+    const uint64_t first = ((uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * W;
+    for (uint64_t s0 = first; s0 < (uint64_t)shots; s0 += stride) {
+        const uint64_t s = s0 + lane;
+        const bool mine = lane < W && s < (uint64_t)shots;
         const double t = philox_uniform53(seed, s) * T;
-        uint64_t lo = 0, hi = nsub - 1;  // smallest j with pre[j+1] > t
+        uint64_t lo = 0, hi = mine ? nsub - 1 : 0;  // smallest j with pre[j+1] > t
         while (lo < hi) {
             const uint64_t mid = lo + (hi - lo) / 2;
             if (pre[mid + 1] > t) hi = mid;
             else lo = mid + 1;
         }
+        // the shots whose amplitudes this lane reads: row, row + 8, ..
+        uint64_t zr[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) zr[k] = (uint64_t)__shfl((long long)lo, k * 8 + row) << sbits;
         const uint64_t z0 = lo << sbits;
-        const uint64_t zend = min(N, z0 + (1ull << sbits));
+        // acc never decreases: the amplitudes with acc <= t are the ones before z
         double acc = pre[lo];
-        uint64_t zsel = ~0ull, zlast = z0;
-        for (uint64_t z = z0; z < zend; ++z) {
-            const double pz = norm2(psi[stored(z, N, folded)]);
-            if (pz > 0.0) zlast = z;
-            acc += pz;
-            if (acc > t) {
-                zsel = z;
-                break;
+        uint32_t before = 0;
+        bool found = !mine;
+        for (uint64_t d = 0; d < sb; d += kStep) {
+            const uint64_t open = __ballot(!found);
+            if (!open) break;
+            typename Tr<R>::V v[kLoads];
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k)
+                if ((open >> ((k % kRows) * 8 + row)) & 1ull)
+                    v[k] = psi[stored(zr[k % kRows] + min(d + (k / kRows) * 8 + sub, sb - 1), N, folded)];
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k) {
+                const uint32_t e = (k / kRows) * 8 + sub;
+                if ((open >> ((k % kRows) * 8 + row)) & 1ull)
+                    m[(k % kRows) * 8 + row][e] = d + e < sb ? norm2(v[k]) : 0.0;
             }
+            __builtin_amdgcn_wave_barrier();
+            if (!found) {
+#pragma unroll
+                for (int r = 0; r < kStep; ++r) {
+                    acc += m[lane][r];
+                    before += acc > t ? 0u : 1u;
+                }
+                found = acc > t;
+            }
+            __builtin_amdgcn_wave_barrier();
         }
-        if (zsel == ~0ull) zsel = zlast;  // rounding left t at the sub-block's end
-        zout[s] = zsel;
-        if (cout) cout[s] = (double)C[stored(zsel, N, folded)];
+        uint64_t zsel = z0 + before;
+        if (!found) {
+            // rounding left t at the sub-block's end: its last amplitude that is not zero
+            for (zsel = z0 + sb - 1; zsel > z0 && !(norm2(psi[stored(zsel, N, folded)]) > 0.0);) --zsel;
+        }
+        if (mine) {
+            zout[s] = zsel;
+            if (cout) cout[s] = (double)C[stored(zsel, N, folded)];
+        }
     }
 }
 
@@ -619,7 +688,7 @@ hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbi
                           hipStream_t s)
 {
     const uint64_t N = 1ull << n, nsub = 1ull << (n - sbits);
-    const unsigned nb = (unsigned)((nsub + 3) / 4);
+    const unsigned nb = (unsigned)(((folded && sbits == 8 ? nsub / 2 : nsub) + 3) / 4);
     if (c64)
         hipLaunchKernelGGL(k_submass<float>, dim3(nb), dim3(kThreads), 0, s, (const Tr<float>::V *)psi,
                            N, folded, sbits, nsub, sub);
@@ -647,15 +716,21 @@ hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool fo
                         uint64_t *z, double *cost, hipStream_t s)
 {
     const uint64_t N = 1ull << n;
-    // one thread per shot up to 2^20 workgroups; beyond that each thread takes several
-    const unsigned nb = grid_for((uint64_t)shots);
-    if (c64)
-        hipLaunchKernelGGL(k_shots<float>, dim3(nb), dim3(kThreads), 0, s, (const Tr<float>::V *)psi,
-                           (const float *)C, N, folded, sbits, pre, nsub, shots, seed, z, cost);
-    else
-        hipLaunchKernelGGL(k_shots<double>, dim3(nb), dim3(kThreads), 0, s,
-                           (const Tr<double>::V *)psi, (const double *)C, N, folded, sbits, pre, nsub, shots,
-                           seed, z, cost);
+    // 8 shots a wave, whose sub-blocks are read 64 amplitudes at a time, while that
+    // gives every SIMD a wave or few; 32 a wave, whose chains of sums fill four times
+    // the lanes, beyond (n = 20, both in us: 16 000 shots 64 and 87, 64 000 89 and 93,
+    // 250 000 164 and 142, 10^6 473 and 327)
+#define QK_SHOTS(R, W)                                                                                         \
+    hipLaunchKernelGGL((k_shots<R, W>), dim3(grid_for((uint64_t)shots * (64 / W))), dim3(kThreads), 0, s,          \
+                       (const Tr<R>::V *)psi, (const Tr<R>::CT *)C, N, folded, sbits, pre, nsub, shots, seed, z, cost)
+    if (shots <= (1 << 16)) {
+        if (c64) QK_SHOTS(float, 8);
+        else QK_SHOTS(double, 8);
+    } else {
+        if (c64) QK_SHOTS(float, 32);
+        else QK_SHOTS(double, 32);
+    }
+#undef QK_SHOTS
     return hipGetLastError();
 }
 
