@@ -46,6 +46,7 @@ struct qaoa_handle_s {
     // MaxCut states of more than one tile are kept folded (qk::fold_state): the
     // M = N / 2 amplitudes and cost entries with bit n-1 clear, at the start of
     // buffers that are sized for all N.
+    bool maxcut = false;
     bool fold = false;
     uint64_t M = 0;  // amplitudes stored: N, or N / 2 when folded
     qaoa_allocator alloc{};  // device-memory provider (alloc == NULL: hipMalloc / hipFree)
@@ -311,6 +312,25 @@ qaoa_status take_event(qaoa_handle h, hipEvent_t *ev)
     return QAOA_OK;
 }
 
+// Runs a launch between a pair of timing events while profiling.
+template <typename Launch>
+qaoa_status timed_launch(qaoa_handle h, int kind, double bytes, Launch launch)
+{
+    if (!h->profiling) {
+        HIPCHECK(h, launch());
+        return QAOA_OK;
+    }
+    qaoa_handle_s::Pending pd{kind, bytes, nullptr, nullptr};
+    qaoa_status st = take_event(h, &pd.t0);
+    if (st == QAOA_OK) st = take_event(h, &pd.t1);
+    if (st != QAOA_OK) return st;
+    HIPCHECK(h, hipEventRecord(pd.t0, h->stream));
+    HIPCHECK(h, launch());
+    HIPCHECK(h, hipEventRecord(pd.t1, h->stream));
+    h->pending.push_back(pd);
+    return QAOA_OK;
+}
+
 qaoa_status run_pass(qaoa_handle h, int mode, const qk::PassArgs &args)
 {
     // passes whose phase arguments |gamma C| could leave the fast reduction's
@@ -318,22 +338,11 @@ qaoa_status run_pass(qaoa_handle h, int mode, const qk::PassArgs &args)
     qk::PassArgs a = args;
     if (std::max(std::fabs(a.gamma_in), std::fabs(a.gamma_out)) * h->cost_bound >= qk::near_phase_limit(c64(h)))
         a.flags |= qk::kFarPhase;
-    if (!h->profiling) {
-        HIPCHECK(h, qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream));
-        return QAOA_OK;
-    }
     // reported kinds: 0 forward, 1 turn, 2 backward, 3 / 4 layer-boundary forward / backward
     const int kind = mode == qk::kFwd ? 0 : (mode == qk::kTurn || mode == qk::kTurnPhase) ? 1
                      : mode == qk::kBwd ? 2 : mode == qk::kFwdFuse ? 3 : 4;
-    qaoa_handle_s::Pending pd{kind, pass_bytes(h, mode, a), nullptr, nullptr};
-    qaoa_status st = take_event(h, &pd.t0);
-    if (st == QAOA_OK) st = take_event(h, &pd.t1);
-    if (st != QAOA_OK) return st;
-    HIPCHECK(h, hipEventRecord(pd.t0, h->stream));
-    HIPCHECK(h, qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream));
-    HIPCHECK(h, hipEventRecord(pd.t1, h->stream));
-    h->pending.push_back(pd);
-    return QAOA_OK;
+    return timed_launch(h, kind, pass_bytes(h, mode, a),
+                        [&] { return qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream); });
 }
 
 qaoa_status drain_profile(qaoa_handle h)
@@ -484,6 +493,19 @@ qaoa_status enqueue_gradient(qaoa_handle h, int p, const double *gamma, const do
     return enqueue_backward(h, p, gamma, beta, lam, sl);
 }
 
+// The whole gradient of a small state in one launch; res receives its 2p + 1 sums.
+bool small_gradient(qaoa_handle h, int p) { return qk::small_fits(h->n, h->maxcut, p); }
+qaoa_status enqueue_small(qaoa_handle h, int p, const double *gamma, const double *beta, double *res)
+{
+    double g = 0.0;
+    for (int l = 0; l < p; ++l) g = std::max(g, std::fabs(gamma[l]));
+    const bool near = g * h->cost_bound < qk::near_phase_limit(c64(h));
+    const qk::SmallArgs a = qk::small_args(h->n, h->maxcut, p, gamma, beta);
+    // timed as a turn, whose cost read is all it moves
+    return timed_launch(h, 1, (double)h->M * cost_bytes(h->prec),
+                        [&] { return qk::launch_small_gradient(c64(h), near, a, h->cost, res, h->stream); });
+}
+
 // Reverse sweep from the final state phi(gamma, beta) held in psi: the first
 // backward pass forms lam = C phi as it loads phi, undoes the last group of
 // layer p-1 on both vectors with its <lam|X|phi> terms (and, with one group
@@ -557,6 +579,7 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
     h->n = n;
     h->prec = precision;
     h->N = 1ull << n;
+    h->maxcut = maxcut;
     h->fold = qk::fold_state(n, precision == QAOA_C64, maxcut);
     h->M = h->fold ? h->N / 2 : h->N;
     h->alloc = g_alloc;
@@ -737,9 +760,14 @@ qaoa_status gradient_on_scratch(qaoa_handle h, int32_t p, const double *gamma, c
         void *lam = base;
         double *parts = (double *)(base + al(h->N * amp_bytes(h->prec)));
         res = (double *)((char *)parts + al((size_t)nslots * T * sizeof(double)));
-        qaoa_status st = enqueue_gradient(h, p, gamma, beta, lam, parts);
-        if (st != QAOA_OK) return st;
-        HIPCHECK(h, launch_sum_slots(parts, T, T, nslots, sum_scale(h), res, h->stream));
+        if (small_gradient(h, p)) {
+            const qaoa_status st = enqueue_small(h, p, gamma, beta, res);
+            if (st != QAOA_OK) return st;
+        } else {
+            const qaoa_status st = enqueue_gradient(h, p, gamma, beta, lam, parts);
+            if (st != QAOA_OK) return st;
+            HIPCHECK(h, launch_sum_slots(parts, T, T, nslots, sum_scale(h), res, h->stream));
+        }
     }
     if (out_is_device) {
         HIPCHECK(h, launch_gradient_out(res, p, E, dgamma, dbeta, h->stream));
@@ -980,16 +1008,23 @@ qaoa_status qaoa_gradient(qaoa_handle h, int32_t p, const double *gamma, const d
         return QAOA_OK;
     }
     DeviceGuard dg(h->device);
-    if ((st = ensure_lam(h)) != QAOA_OK) return st;
     const uint64_t T = nblocks(h);
     const int nslots = 2 * p + 1;
-    if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, (size_t)nslots * T)) != QAOA_OK) return st;
-    if ((st = ensure_doubles(h, &h->res, &h->res_cap, (size_t)nslots)) != QAOA_OK) return st;
-    h->state_valid = false;
-
-    if ((st = enqueue_gradient(h, p, gamma, beta, h->lam, h->parts)) != QAOA_OK) return st;
     std::vector<double> r((size_t)nslots);
-    if ((st = fetch_results(h, nslots, T, r.data())) != QAOA_OK) return st;
+    if (small_gradient(h, p)) {
+        if ((st = ensure_doubles(h, &h->res, &h->res_cap, (size_t)nslots)) != QAOA_OK) return st;
+        h->state_valid = false;
+        if ((st = enqueue_small(h, p, gamma, beta, h->res)) != QAOA_OK) return st;
+        HIPCHECK(h, hipMemcpyAsync(r.data(), h->res, (size_t)nslots * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+        HIPCHECK(h, hipStreamSynchronize(h->stream));
+    } else {
+        if ((st = ensure_lam(h)) != QAOA_OK) return st;
+        if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, (size_t)nslots * T)) != QAOA_OK) return st;
+        if ((st = ensure_doubles(h, &h->res, &h->res_cap, (size_t)nslots)) != QAOA_OK) return st;
+        h->state_valid = false;
+        if ((st = enqueue_gradient(h, p, gamma, beta, h->lam, h->parts)) != QAOA_OK) return st;
+        if ((st = fetch_results(h, nslots, T, r.data())) != QAOA_OK) return st;
+    }
     if (E) *E = r[0];
     for (int l = 0; l < p; ++l) {
         dbeta[l] = 2.0 * r[1 + l];

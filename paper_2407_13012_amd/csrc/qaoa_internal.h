@@ -250,6 +250,30 @@ hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool fo
                         const double *pre, uint64_t nsub, int64_t shots, uint64_t seed,
                         uint64_t *z, double *cost, hipStream_t s);
 
+// Gradient of a small state in one launch (small.hip): at most 2^kSmallBits
+// stored amplitudes and kSmallMaxLayers layers.
+constexpr int kSmallBits = 12;
+constexpr int kSmallMaxLayers = 32;
+struct SmallLayer {
+    double gamma;
+    double mul, fac, scl;  // rotation (1 - i mul X) fac, fac^n
+    int32_t flip;          // and a flip of all qubits
+};
+struct SmallArgs {
+    int32_t bits;    // stored amplitudes 2^bits
+    int32_t folded;  // of a folded state
+    int32_t p;
+    double amp0;
+    SmallLayer layer[kSmallMaxLayers];
+};
+// MaxCut states are folded there from one wave (2^8 amplitudes) on.
+constexpr bool small_folds(int n, bool maxcut) { return maxcut && n > 8; }
+bool small_fits(int n, bool maxcut, int p);
+SmallArgs small_args(int n, bool maxcut, int p, const double *gamma, const double *beta);
+// out: 2p + 1 doubles, the summed slots below.  `cost` holds the (folded) diagonal
+// or the whole one.  near: every phase in the fast reduction's range.
+hipError_t launch_small_gradient(bool c64, bool near, const SmallArgs &a, const void *cost, double *out, hipStream_t s);
+
 // E and the gradient from the summed slots: E = res[0], dbeta[l] = 2 res[1 + l],
 // dgamma[l] = 2 res[1 + p + l] (device pointers; E may be NULL).
 hipError_t launch_gradient_out(const double *res, int p, double *E, double *dgamma, double *dbeta,
