@@ -191,7 +191,7 @@ qaoa_status qaoa_gradient_from_state(qaoa_handle h, int32_t p, const double *gam
  * allocate: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same results as qaoa_gradient (the same kernels in the
  * same order).  The adjoint vector, the partial sums and the summed slots are
- * taken from a fixed scratch array of 16 MiB + 256 KiB that the library holds
+ * taken from a fixed scratch array of 16 MiB + 512 KiB that the library holds
  * on each device it runs on until the process ends; the handle's state and
  * cost diagonal (allocated at creation) are used as by qaoa_gradient.
  *   p                    0 <= p <= 32
@@ -292,7 +292,8 @@ qaoa_status qaoa_profile_read(qaoa_handle h, int32_t kind, int64_t *launches, do
  * tile_bits[i] (TB = 12 for QAOA_C128, 13 for QAOA_C64: 64 KiB of state) and
  * rotates the qubits in target_bits[i]; the remaining tile bits are low
  * spectator bits kept for contiguous memory access (runs of >= 64 bytes).
- * (MaxCut handles run half of the tiles, see qaoa_create_maxcut.)
+ * (MaxCut handles run half of the tiles, see qaoa_create_maxcut; states of up
+ * to 16 MiB take smaller tiles, in two sweeps per layer.)
  *   cap       capacity of the two output arrays
  *   npasses   receives the number of sweeps per layer
  * Errors: INVALID_ARGUMENT for n outside [1, QAOA_MAX_QUBITS], an unknown

@@ -16,6 +16,7 @@ LIB = os.path.join(HERE, "libqaoa.so")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "batch.hip", "batch_many.hip", "small.hip", "mpnn.hip", "api.cpp", "plan.cpp", "lbfgs.cpp", "cost_terms.cpp", "noalloc.hip")]
 # passes.hip is compiled once per precision and spectator class (see its header)
 PASS_SOURCE = os.path.join(HERE, "csrc", "passes.hip")
+QUAD_SOURCE = os.path.join(HERE, "csrc", "quad_pass.hip")
 PASS_VARIANTS = [(real, sp) for real in ("double", "float") for sp in (-1, 0, 2, 3, 4, 5, 6, 7)]
 
 
@@ -26,6 +27,8 @@ def units() -> list[tuple[str, list[str], str]]:
         tag = f"{'c128' if real == 'double' else 'c64'}_{'rt' if sp < 0 else 's%d' % sp}"
         many = ["-DQK_PASS_MANY=1"] if real == "double" else []
         out.append((PASS_SOURCE, [f"-DQK_PASS_REAL={real}", f"-DQK_PASS_SP={sp}", *many], f"passes_{tag}.o"))
+    for real in ("double", "float"):
+        out.append((QUAD_SOURCE, [f"-DQK_QUAD_REAL={real}"], f"quad_{'c128' if real == 'double' else 'c64'}.o"))
     return out
 ARCH = os.environ.get("QAOA_OFFLOAD_ARCH", "gfx950")
 

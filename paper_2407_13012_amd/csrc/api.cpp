@@ -61,6 +61,9 @@ struct qaoa_handle_s {
     double *res = nullptr;
     size_t res_cap = 0;    // doubles
     std::vector<qk::PassPlan> plan;  // mixer sweeps of one layer (fixed by n and precision)
+    int quad = 0;                    // tile bits of the small-tile sweeps (0: none at this n)
+    std::vector<qk::PassPlan> quad_plan;
+    bool on_quad = false;            // the current call's sweeps run on quad_plan (choose_tiles)
     bool state_valid = false;
     std::vector<double> state_angles;  // (gamma, beta) of the current state
     bool poisoned = false;
@@ -150,11 +153,27 @@ inline uint64_t nblocks(int n, bool c64)
     const int tb = qk::tile_bits(c64);
     return n <= tb ? 1ull : (1ull << (n - tb));
 }
-inline uint64_t nblocks(const qaoa_handle h) { return nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0); }
+// Tiles of the current call's sweeps, and the most any call's sweeps have.
+inline uint64_t nblocks(const qaoa_handle h) { return h->on_quad ? h->M >> h->quad : nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0); }
+inline uint64_t max_nblocks(const qaoa_handle h)
+{
+    return std::max(h->quad ? h->M >> h->quad : 0, nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0));
+}
+inline const std::vector<qk::PassPlan> &plan_of(const qaoa_handle h) { return h->on_quad ? h->quad_plan : h->plan; }
 // Factor of the sums over the stored amplitudes.
 inline double sum_scale(const qaoa_handle h) { return h->fold ? 2.0 : 1.0; }
 // Qubits of a plain streaming kernel over the stored entries.
 inline int stored_bits(const qaoa_handle h) { return h->fold ? h->n - 1 : h->n; }
+
+// Sets which plan the sweeps of a call at these angles run on: the small tiles
+// where the state has few of the others (quad_tile_bits), as long as every phase
+// |gamma C| stays in the fast reduction's range, which their kernels assume.
+void choose_tiles(qaoa_handle h, int p, const double *gamma)
+{
+    double g = 0.0;
+    for (int l = 0; l < p; ++l) g = std::max(g, std::fabs(gamma[l]));
+    h->on_quad = h->quad && g * h->cost_bound < qk::near_phase_limit(c64(h));
+}
 
 qaoa_status check_handle(qaoa_handle h)
 {
@@ -342,7 +361,10 @@ qaoa_status run_pass(qaoa_handle h, int mode, const qk::PassArgs &args)
     const int kind = mode == qk::kFwd ? 0 : (mode == qk::kTurn || mode == qk::kTurnPhase) ? 1
                      : mode == qk::kBwd ? 2 : mode == qk::kFwdFuse ? 3 : 4;
     return timed_launch(h, kind, pass_bytes(h, mode, a),
-                        [&] { return qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream); });
+                        [&] {
+                            return h->on_quad ? qk::launch_quad(mode, c64(h), h->quad, a, nblocks(h), h->stream)
+                                              : qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream);
+                        });
 }
 
 qaoa_status drain_profile(qaoa_handle h)
@@ -368,7 +390,7 @@ qaoa_status drain_profile(qaoa_handle h)
 qaoa_status run_forward(qaoa_handle h, int p, const double *gamma, const double *beta,
                         bool skip_last, bool e_out)
 {
-    const std::vector<qk::PassPlan> &G = h->plan;
+    const std::vector<qk::PassPlan> &G = plan_of(h);
     const int P = (int)G.size();
     for (int l = 0; l < p; ++l) {
         for (int idx = 0; idx < P; ++idx) {
@@ -427,7 +449,7 @@ struct Slots {
 qaoa_status enqueue_backward(qaoa_handle h, int p, const double *gamma, const double *beta, void *lam,
                              const Slots &sl)
 {
-    const std::vector<qk::PassPlan> &G = h->plan;
+    const std::vector<qk::PassPlan> &G = plan_of(h);
     const int P = (int)G.size();
     for (int l = p - 1; l >= 0; --l) {
         for (int j = 0; j < P; ++j) {
@@ -469,7 +491,7 @@ qaoa_status enqueue_gradient(qaoa_handle h, int p, const double *gamma, const do
 {
     qaoa_status st;
     const Slots sl{parts, nblocks(h), p};
-    const std::vector<qk::PassPlan> &G = h->plan;
+    const std::vector<qk::PassPlan> &G = plan_of(h);
     const int P = (int)G.size();
 
     // Forward through every group except the last group of the last layer.
@@ -515,7 +537,7 @@ qaoa_status enqueue_reverse(qaoa_handle h, int p, const double *gamma, const dou
                             double *parts)
 {
     const Slots sl{parts, nblocks(h), p};
-    const std::vector<qk::PassPlan> &G = h->plan;
+    const std::vector<qk::PassPlan> &G = plan_of(h);
     const int P = (int)G.size();
     const int l = p - 1;
     qk::PassArgs a = pass_args(h, G[P > 1 ? group_at(l, P - 1, P) : 0], beta[l]);
@@ -585,6 +607,8 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
     h->alloc = g_alloc;
     try {
         h->plan = qk::plan_passes(n, precision == QAOA_C64);
+        h->quad = qk::quad_tile_bits(n, h->fold ? n - 1 : n, precision == QAOA_C64);
+        if (h->quad) h->quad_plan = qk::plan_quad(n, h->quad);
     } catch (...) {
         delete h;
         return fail(QAOA_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -624,7 +648,7 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
         if (e == hipErrorOutOfMemory) return fail(QAOA_ERR_OUT_OF_MEMORY, "state or cost allocation failed");
         return device_fail(nullptr, "hipMalloc", e);
     }
-    qaoa_status st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nblocks(n, precision == QAOA_C64) + 2);
+    qaoa_status st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * max_nblocks(h) + 2);
     if (st == QAOA_OK) st = ensure_doubles(h, &h->res, &h->res_cap, 64);
     if (st != QAOA_OK) {
         std::string keep = g_err;
@@ -706,7 +730,7 @@ size_t noalloc_need(qaoa_handle h, int p)
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     if (p == 0) return al((size_t)((h->N + kTile - 1) / kTile) * sizeof(double)) + sizeof(double);  // (an upper bound when folded)
     const size_t nslots = 2 * (size_t)p + 1;
-    return al(h->N * amp_bytes(h->prec)) + al(nslots * nblocks(h) * sizeof(double)) + nslots * sizeof(double);
+    return al(h->N * amp_bytes(h->prec)) + al(nslots * max_nblocks(h) * sizeof(double)) + nslots * sizeof(double);
 }
 
 qaoa_status noalloc_check(qaoa_handle h, int32_t p, const double *gamma, const double *beta,
@@ -755,6 +779,7 @@ qaoa_status gradient_on_scratch(qaoa_handle h, int32_t p, const double *gamma, c
         HIPCHECK(h, launch_expect(c64(h), h->psi, h->cost, stored_bits(h), parts, h->stream));
         HIPCHECK(h, launch_sum_slots(parts, T0, T0, 1, sum_scale(h), res, h->stream));
     } else {
+        choose_tiles(h, p, gamma);
         const uint64_t T = nblocks(h);
         nslots = 2 * p + 1;
         void *lam = base;
@@ -939,8 +964,9 @@ qaoa_status qaoa_statevector(qaoa_handle h, int32_t p, const double *gamma, cons
     h->state_valid = false;
     if (p == 0) {
         HIPCHECK(h, qk::launch_fill_plus(c64(h), h->psi, h->n, h->M, h->stream));
-    } else if ((st = run_forward(h, p, gamma, beta, false, false)) != QAOA_OK) {
-        return st;
+    } else {
+        choose_tiles(h, p, gamma);
+        if ((st = run_forward(h, p, gamma, beta, false, false)) != QAOA_OK) return st;
     }
     if ((st = keep_angles(h, p, gamma, beta)) != QAOA_OK) return st;
     h->state_valid = true;
@@ -985,6 +1011,7 @@ qaoa_status qaoa_evaluate(qaoa_handle h, int32_t p, const double *gamma, const d
     }
     DeviceGuard dg(h->device);
     h->state_valid = false;
+    choose_tiles(h, p, gamma);
     const uint64_t T = nblocks(h);
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, T)) != QAOA_OK) return st;
     if ((st = run_forward(h, p, gamma, beta, false, true)) != QAOA_OK) return st;
@@ -1008,6 +1035,7 @@ qaoa_status qaoa_gradient(qaoa_handle h, int32_t p, const double *gamma, const d
         return QAOA_OK;
     }
     DeviceGuard dg(h->device);
+    choose_tiles(h, p, gamma);
     const uint64_t T = nblocks(h);
     const int nslots = 2 * p + 1;
     std::vector<double> r((size_t)nslots);
@@ -1048,6 +1076,7 @@ qaoa_status qaoa_gradient_from_state(qaoa_handle h, int32_t p, const double *gam
     if (p == 0) return QAOA_OK;
     DeviceGuard dg(h->device);
     if ((st = ensure_lam(h)) != QAOA_OK) return st;
+    choose_tiles(h, p, gamma);
     const uint64_t T = nblocks(h);
     const int nslots = 2 * p + 1;
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, (size_t)nslots * T)) != QAOA_OK) return st;

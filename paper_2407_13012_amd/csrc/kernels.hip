@@ -547,6 +547,11 @@ hipError_t launch_pass(int mode, bool c64, const PassArgs &a, uint64_t nblocks, 
     }
 }
 
+hipError_t launch_quad(int mode, bool c64, int tbits, const PassArgs &a, uint64_t nblocks, hipStream_t s)
+{
+    return c64 ? launch_quad_real<float>(mode, tbits, a, nblocks, s) : launch_quad_real<double>(mode, tbits, a, nblocks, s);
+}
+
 hipError_t launch_many(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
                        hipStream_t s)
 {

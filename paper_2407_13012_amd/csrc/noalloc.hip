@@ -16,7 +16,7 @@ namespace {
 
 // 16 MiB of adjoint vector (complex128 n <= 20, complex64 n <= 21) plus the
 // partial sums of up to 32 layers.
-constexpr size_t kScratchBytes = ((size_t)16 << 20) + ((size_t)256 << 10);
+constexpr size_t kScratchBytes = ((size_t)16 << 20) + ((size_t)512 << 10);
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

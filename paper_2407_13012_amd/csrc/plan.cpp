@@ -124,6 +124,29 @@ std::vector<PassPlan> plan_passes(int n, bool c64, int kmax)
     return out;
 }
 
+// Two sweeps per layer: the low M bits, then the n - M others over at least 2
+// (complex64: 3) spectators, runs of 64 bytes.  M is the smallest of 10, 11, 12
+// that leaves room for them.
+// Up to 16 MiB of stored state a sweep is bound by the time of one workgroup;
+// beyond, by memory, where the large tiles are better (E + G, p = 6, large and
+// small tiles, us: complex128 MaxCut n = 14 236 and 110, 17 230 and 122, 20 288
+// and 204, 21 (16 MiB) 331 and 269, 22 431 and 447; QUBO n = 20 (16 MiB) 318 and
+// 262, 21 425 and 446; complex64 MaxCut n = 21 311 and 222).
+int quad_tile_bits(int n, int stored_bits, bool c64)
+{
+    const int spect = c64 ? 3 : 2;
+    if (n <= kSmallBits || stored_bits > (c64 ? 21 : 20)) return 0;
+    for (int M = 10; M <= 12; ++M)
+        if (n - M <= M - spect && n - M >= M - 8) return M;
+    return 0;
+}
+
+std::vector<PassPlan> plan_quad(int n, int M)
+{
+    const int k = n - M;
+    return {{low_mask(M), low_mask(M)}, {low_mask(M - k) | (low_mask(k) << M), low_mask(k) << M}};
+}
+
 bool make_geometry(int n, const PassPlan &pp, Geometry *g)
 {
     *g = Geometry{};

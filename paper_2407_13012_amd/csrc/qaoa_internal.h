@@ -85,6 +85,10 @@ struct Geometry {
 // kmax bounds the qubits rotated by each pass after the first (at most 10, so
 // that at least TB - 10 spectator bits give runs of >= 64 bytes).
 std::vector<PassPlan> plan_passes(int n, bool c64, int kmax = 10);
+// States of few tiles run on smaller ones (quad_pass.hip): tile bits for n qubits
+// stored as 2^stored_bits amplitudes (0: the tiles above), and their plan.
+int quad_tile_bits(int n, int stored_bits, bool c64);
+std::vector<PassPlan> plan_quad(int n, int tile_bits);
 // Kernel geometry of a plan entry; returns false if it needs more runs than supported.
 bool make_geometry(int n, const PassPlan &pp, Geometry *g);
 // Whether a state on n qubits is kept folded.  A cut does not change when every
@@ -194,6 +198,10 @@ hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64
 // Spectator class of a pass with kernels of its own (0 or 2..7), else -1.
 int static_spectators(const Geometry &g, bool c64, int mode);
 // out[k] = scale * (sum of slot k); scale 2 for the half sums of a folded state.
+// The passes of a plan_quad plan (phases within the fast reduction's range).
+hipError_t launch_quad(int mode, bool c64, int tbits, const PassArgs &a, uint64_t nblocks, hipStream_t s);
+template <typename R>
+hipError_t launch_quad_real(int mode, int tbits, const PassArgs &a, uint64_t nblocks, hipStream_t s);
 hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots, double scale,
                             double *out, hipStream_t s);
 

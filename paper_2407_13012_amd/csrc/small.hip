@@ -9,257 +9,18 @@
 // arithmetic goes.  n = 12 (unit MaxCut),
 // p = 2, complex128: 14.8 us, the call 60.7 -> 36.7 us.
 //
-// Layout.  Position p = lane (bits 0-5), register (6-7), wave (8..).  Within a
-// wave bits 0-3 are rotated through DPP moves, 6-7 in registers, and 4-5 after
-// v_permlane16/32_swap has exchanged them with 6-7 (two instructions per
-// amplitude where a lane exchange costs four moves).  The wave bits need LDS:
-// in arrangement A element e sits at position e, in B the positions are rotated
-// by the number h of wave bits, which puts them at positions 8-h .. 7.  A layer
-// starts in the arrangement the last one ended in, so it has one exchange.  The
-// partner across bit n-1 of a folded state is the complement ~e; it is read
-// during the exchange, from the same LDS image.
+// The layout is that of quad.h: bits 0-7 rotate in arrangement A, the wave bits in
+// B.  A layer starts in the arrangement the last one ended in, so it has one
+// exchange through LDS.  The partner across bit n-1 of a folded state is the
+// complement ~e; it is read during the exchange, from the same LDS image.
 //
 // Every rotation is in the tan form: exp(-i b X) = -i sin b X (1 + i cot b X)
 // where |sin b| > |cos b|, and the flip X of all qubits only exchanges z and ~z
 // (nothing at all for a folded state); `flip` tracks it in the cost index.
-#include "tile_device.h"
+#include "quad.h"
 
 namespace qk {
 namespace {
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v)
-{
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-// Amplitude of lane l ^ (1 << BIT), BIT < 4.
-template <int BIT, typename V>
-__device__ __forceinline__ V lane_x(V v)
-{
-    constexpr int kQuad1 = 0xB1, kQuad2 = 0x4E, kQuad3 = 0x1B, kHalfMirror = 0x141, kRor8 = 0x128;
-    V o;
-    if constexpr (BIT == 0) {
-        o.x = dpp<kQuad1>(v.x);
-        o.y = dpp<kQuad1>(v.y);
-    } else if constexpr (BIT == 1) {
-        o.x = dpp<kQuad2>(v.x);
-        o.y = dpp<kQuad2>(v.y);
-    } else if constexpr (BIT == 2) {  // l ^ 7, then l ^ 3
-        o.x = dpp<kQuad3>(dpp<kHalfMirror>(v.x));
-        o.y = dpp<kQuad3>(dpp<kHalfMirror>(v.y));
-    } else {
-        o.x = dpp<kRor8>(v.x);
-        o.y = dpp<kRor8>(v.y);
-    }
-    return o;
-}
-
-// Exchanges the bit that tells a from b with lane bit 4 (WIDE: 5).
-template <bool WIDE>
-__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b)
-{
-    if constexpr (WIDE) {
-        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-        a = r[0];
-        b = r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-        a = r[0];
-        b = r[1];
-    }
-}
-template <bool WIDE>
-__device__ __forceinline__ void swap_lane(float &a, float &b)
-{
-    uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
-    swap32<WIDE>(x, y);
-    a = __builtin_bit_cast(float, x);
-    b = __builtin_bit_cast(float, y);
-}
-template <bool WIDE>
-__device__ __forceinline__ void swap_lane(double &a, double &b)
-{
-    const uint64_t u = __builtin_bit_cast(uint64_t, a), v = __builtin_bit_cast(uint64_t, b);
-    uint32_t ul = (uint32_t)u, uh = (uint32_t)(u >> 32), vl = (uint32_t)v, vh = (uint32_t)(v >> 32);
-    swap32<WIDE>(ul, vl);
-    swap32<WIDE>(uh, vh);
-    a = __builtin_bit_cast(double, ((uint64_t)uh << 32) | ul);
-    b = __builtin_bit_cast(double, ((uint64_t)vh << 32) | vl);
-}
-// Positions 6 and 7 <-> 4 and 5.
-template <typename V>
-__device__ __forceinline__ void swap_quad(V (&v)[4])
-{
-#pragma unroll
-    for (int k = 0; k < 4; k += 2) {
-        swap_lane<false>(v[k].x, v[k + 1].x);
-        swap_lane<false>(v[k].y, v[k + 1].y);
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        swap_lane<true>(v[k].x, v[k + 2].x);
-        swap_lane<true>(v[k].y, v[k + 2].y);
-    }
-}
-
-// The rotations of one layer as they are applied: one vector (forward), or both
-// with the <lam|X|phi> terms taken before each rotation (adjoint).
-template <typename R>
-struct One {
-    using V = typename Tr<R>::V;
-    V f[4];
-    R m;
-    template <int Q>
-    __device__ __forceinline__ void reg()
-    {
-        bfly<true>(f[0], f[Q ? 2 : 1], m);
-        bfly<true>(f[Q ? 1 : 2], f[3], m);
-    }
-    template <int BIT>
-    __device__ __forceinline__ void lane()
-    {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bfly_lane<true>(f[r], lane_x<BIT>(f[r]), m);
-    }
-    __device__ __forceinline__ void swap() { swap_quad(f); }
-};
-
-template <typename R>
-struct Two {
-    using V = typename Tr<R>::V;
-    V f[4], l[4];
-    R m;
-    double acc, sig2, f2;
-    __device__ __forceinline__ void add(typename PairSum<V>::T ps)
-    {
-        acc = fma(sig2, (double)ps, acc);
-        asm volatile("" : "+v"(acc));
-        sig2 *= f2;
-    }
-    template <int Q>
-    __device__ __forceinline__ void reg()
-    {
-        constexpr int a0 = 0, a1 = Q ? 2 : 1, b0 = Q ? 1 : 2, b1 = 3;
-        typename PairSum<V>::T ps = 0;
-        ps = imcx_acc(l[a1], f[a0], imcx_acc(l[a0], f[a1], ps));
-        ps = imcx_acc(l[b1], f[b0], imcx_acc(l[b0], f[b1], ps));
-        add(ps);
-        bfly<true>(l[a0], l[a1], m);
-        bfly<true>(f[a0], f[a1], m);
-        bfly<true>(l[b0], l[b1], m);
-        bfly<true>(f[b0], f[b1], m);
-    }
-    template <int BIT>
-    __device__ __forceinline__ void lane()
-    {
-        typename PairSum<V>::T ps = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const V fp = lane_x<BIT>(f[r]), lp = lane_x<BIT>(l[r]);
-            ps = imcx_acc(l[r], fp, ps);
-            bfly_lane<true>(l[r], lp, m);
-            bfly_lane<true>(f[r], fp, m);
-        }
-        add(ps);
-    }
-    __device__ __forceinline__ void swap()
-    {
-        swap_quad(f);
-        swap_quad(l);
-    }
-};
-
-// Where a thread's amplitudes are: arrangement (0 A, 1 B) and whether positions
-// 6-7 and 4-5 are exchanged.  Uniform.
-struct Place {
-    int arr, sw;
-};
-
-// Element of register r.
-template <int M>
-__device__ __forceinline__ uint32_t elem_at(Place w, uint32_t tid, uint32_t r)
-{
-    constexpr int H = M > 8 ? M - 8 : 0;
-    const uint32_t lane = tid & 63u;
-    const uint32_t p = (w.sw ? ((lane & 15u) | (r << 4) | ((lane >> 4) << 6)) : (lane | (r << 6))) | ((tid >> 6) << 8);
-    return w.arr ? ((p << H) | (p >> (M - H))) & ((1u << M) - 1u) : p;
-}
-// LDS slot of an element: strides 1 (A) and 2^H (B) over the lanes hit distinct banks.
-template <int M>
-__device__ __forceinline__ uint32_t slot_of(uint32_t e)
-{
-    constexpr int H = M > 8 ? M - 8 : 0;
-    return H ? e + (e >> H) : e;
-}
-template <int M>
-constexpr int kSmallSlots = (1 << M) + (M > 8 ? (1 << M) >> (M - 8) : 0);
-
-// Rotates positions [0, bits) of A (bits = 8 except in the M = 8 kernel).
-template <int M, typename S>
-__device__ __forceinline__ void mix_a(S &s, Place &w, int bits)
-{
-    // positions 6-7 (sw: 4-5) are in the registers
-    const int q0 = w.sw ? 4 : 6;
-    if (M > 8 || q0 < bits) s.template reg<0>();
-    if (M > 8 || q0 + 1 < bits) s.template reg<1>();
-    s.swap();
-    w.sw ^= 1;
-    const int q1 = w.sw ? 4 : 6;
-    if (M > 8 || q1 < bits) s.template reg<0>();
-    if (M > 8 || q1 + 1 < bits) s.template reg<1>();
-    if (M > 8 || 0 < bits) s.template lane<0>();
-    if (M > 8 || 1 < bits) s.template lane<1>();
-    if (M > 8 || 2 < bits) s.template lane<2>();
-    if (M > 8 || 3 < bits) s.template lane<3>();
-}
-// Rotates positions 8-H .. 7 of B.
-template <int M, typename S>
-__device__ __forceinline__ void mix_b(S &s, Place &w)
-{
-    constexpr int H = M > 8 ? M - 8 : 0;
-    if constexpr (H == 1) s.template reg<1>();
-    if constexpr (H == 2 || H == 4) {
-        s.template reg<0>();
-        s.template reg<1>();
-    }
-    if constexpr (H == 3) {  // 5, 6, 7
-        if (!w.sw) s.template reg<0>();
-        s.template reg<1>();
-    }
-    if constexpr (H >= 3) {
-        s.swap();
-        w.sw ^= 1;
-    }
-    if constexpr (H == 3) {
-        if (!w.sw) s.template reg<0>();
-        s.template reg<1>();
-    }
-    if constexpr (H == 4) {
-        s.template reg<0>();
-        s.template reg<1>();
-    }
-}
-
-template <int M, typename V>
-__device__ __forceinline__ void put(const V (&v)[4], V *buf, Place w, uint32_t tid)
-{
-#pragma unroll
-    for (int r = 0; r < 4; ++r) buf[slot_of<M>(elem_at<M>(w, tid, r))] = v[r];
-}
-template <int M, typename V>
-__device__ __forceinline__ void get(V (&v)[4], const V *buf, Place w, uint32_t tid, uint32_t flip)
-{
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = buf[slot_of<M>(elem_at<M>(w, tid, r) ^ flip)];
-}
 
 // The other arrangement, and for a folded state the rotation of bit n-1.
 template <int M, typename R>
@@ -310,16 +71,16 @@ __device__ __forceinline__ void exchange(Two<R> &s, Place &w, typename Tr<R>::V 
 // All rotations of a layer, starting in the arrangement of `w`.
 template <int M, typename R, typename S>
 __device__ __forceinline__ void mix_layer(S &s, Place &w, typename Tr<R>::V *b0, typename Tr<R>::V *b1, uint32_t tid,
-                                          bool folded, int bits)
+                                          bool folded, uint32_t mask)
 {
     if (M == 8 || w.arr == 0) {
-        mix_a<M>(s, w, bits);
+        mix_a<M, (M > 8), true>(s, w, mask);
         exchange<M>(s, w, b0, b1, tid, folded);
-        if (M > 8) mix_b<M>(s, w);
+        if (M > 8) mix_b<M, true>(s, w);
     } else {
-        mix_b<M>(s, w);
+        mix_b<M, true>(s, w);
         exchange<M>(s, w, b0, b1, tid, folded);
-        mix_a<M>(s, w, bits);
+        mix_a<M, (M > 8), true>(s, w, mask);
     }
 }
 
@@ -329,11 +90,11 @@ __global__ __launch_bounds__((1 << M) / 4) void k_small_gradient(SmallArgs a, co
     using V = typename Tr<R>::V;
     using CT = typename Tr<R>::CT;
     constexpr int NW = (1 << M) / 256;
-    __shared__ V b0[kSmallSlots<M>], b1[kSmallSlots<M>];
+    __shared__ V b0[1 << M], b1[1 << M];
     __shared__ double red[2 * kSmallMaxLayers + 1][NW];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const bool folded = a.folded != 0;
-    const int bits = M > 8 ? 8 : a.bits, p = a.p;
+    const int p = a.p;
     const uint32_t size = 1u << (M > 8 ? M : a.bits), all = size - 1u;
     Place w{0, 0};
     uint32_t flip = 0;  // all: amplitude e holds index ~e
@@ -364,7 +125,7 @@ __global__ __launch_bounds__((1 << M) / 4) void k_small_gradient(SmallArgs a, co
                 s.f[r] = cmul(s.f[r], c, sn);
             }
             s.m = (R)a.layer[l].mul;
-            mix_layer<M, R>(s, w, b0, b1, tid, folded, bits);
+            mix_layer<M, R>(s, w, b0, b1, tid, folded, all);
             const R f = (R)a.layer[l].scl;
 #pragma unroll
             for (int r = 0; r < 4; ++r) s.f[r] = vscale(s.f[r], f);
@@ -389,7 +150,7 @@ __global__ __launch_bounds__((1 << M) / 4) void k_small_gradient(SmallArgs a, co
         t.sig2 = 1.0;
         t.f2 = a.layer[l].fac * a.layer[l].fac;
         t.m = (R)-a.layer[l].mul;
-        mix_layer<M, R>(t, w, b0, b1, tid, folded, bits);
+        mix_layer<M, R>(t, w, b0, b1, tid, folded, all);
         if (a.layer[l].flip && !folded) flip ^= all;
         load_cost();
         const R f = (R)a.layer[l].scl;
