@@ -44,11 +44,11 @@ struct qaoa_handle_s {
     int device = 0;
     uint64_t N = 0;
     // MaxCut states of more than one tile are kept folded (qk::fold_state): the
-    // M = N / 2 amplitudes and cost entries with bit n-1 clear, at the start of
-    // buffers that are sized for all N.
+    // M = N / 2 amplitudes and cost entries with bit n-1 clear.
     bool maxcut = false;
     bool fold = false;
     uint64_t M = 0;  // amplitudes stored: N, or N / 2 when folded
+    uint64_t A = 0;  // amplitudes allocated: M, or N from a caller's allocator (which is asked for whole arrays)
     qaoa_allocator alloc{};  // device-memory provider (alloc == NULL: hipMalloc / hipFree)
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -58,8 +58,17 @@ struct qaoa_handle_s {
     double cost_bound = 0; // |offset| + sum of |weights|: bounds |C(z)|
     double *parts = nullptr;
     size_t parts_cap = 0;  // doubles
+    // Results: pinned host memory that kernels write to, so that a call waits for
+    // them once instead of queueing a copy behind them (11 instead of 24 us after a
+    // kernel).  Pinning and unpinning cost about three such copies, so a handle's
+    // first three results, and all where no memory could be pinned, go through
+    // device memory and a copy.
+    double *pin = nullptr;
+    size_t pin_cap = 0;    // doubles
+    int copied = 0;        // results copied so far
     double *res = nullptr;
     size_t res_cap = 0;    // doubles
+    hipEvent_t scanned = nullptr;  // sampling: the total mass has been written
     std::vector<qk::PassPlan> plan;  // mixer sweeps of one layer (fixed by n and precision)
     int quad = 0;                    // tile bits of the small-tile sweeps (0: none at this n)
     std::vector<qk::PassPlan> quad_plan;
@@ -231,6 +240,40 @@ qaoa_status ensure_doubles(qaoa_handle h, double **buf, size_t *cap, size_t coun
     if (dev_alloc(h, (void **)buf, count * sizeof(double)) != hipSuccess)
         return fail(QAOA_ERR_OUT_OF_MEMORY, "scratch buffer allocation failed");
     *cap = count;
+    return QAOA_OK;
+}
+
+// Ensure that kernels have `count` doubles to write their results to.
+qaoa_status ensure_results(qaoa_handle h, size_t count)
+{
+    if (h->pin_cap >= count) return QAOA_OK;
+    if (!h->pin && h->copied < 3) {
+        ++h->copied;
+        return ensure_doubles(h, &h->res, &h->res_cap, count);
+    }
+    if (h->pin) {
+        HIPCHECK(h, hipStreamSynchronize(h->stream));
+        (void)hipHostFree(h->pin);
+    }
+    h->pin = nullptr;
+    h->pin_cap = 0;
+    const size_t cap = std::max<size_t>(count, 72);
+    if (hipHostMalloc((void **)&h->pin, cap * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->pin = nullptr;
+        return ensure_doubles(h, &h->res, &h->res_cap, count);
+    }
+    h->pin_cap = cap;
+    return QAOA_OK;
+}
+double *results(qaoa_handle h) { return h->pin ? h->pin : h->res; }
+
+// Waits for the stream and copies the first `count` results.
+qaoa_status collect(qaoa_handle h, size_t count, double *host)
+{
+    if (!h->pin) HIPCHECK(h, hipMemcpyAsync(host, h->res, count * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPCHECK(h, hipStreamSynchronize(h->stream));
+    if (h->pin) std::memcpy(host, h->pin, count * sizeof(double));
     return QAOA_OK;
 }
 
@@ -576,16 +619,33 @@ qaoa_status ensure_lam(qaoa_handle h)
     HIPCHECK(h, hipMemGetInfo(&fr, &tot));
     if (!fits(h, (double)h->N * amp_bytes(h->prec), fr))
         return fail(QAOA_ERR_OUT_OF_MEMORY, "adjoint vector does not fit in free device memory");
-    if (dev_alloc(h, &h->lam, h->N * amp_bytes(h->prec)) != hipSuccess)
+    if (dev_alloc(h, &h->lam, h->A * amp_bytes(h->prec)) != hipSuccess)
         return fail(QAOA_ERR_OUT_OF_MEMORY, "adjoint vector allocation failed");
     return QAOA_OK;
 }
 
 qaoa_status fetch_results(qaoa_handle h, int nslots, uint64_t count, double *host)
 {
-    HIPCHECK(h, qk::launch_sum_slots(h->parts, count, count, nslots, sum_scale(h), h->res, h->stream));
-    HIPCHECK(h, hipMemcpyAsync(host, h->res, (size_t)nslots * sizeof(double), hipMemcpyDeviceToHost,
-                               h->stream));
+    const qaoa_status st = ensure_results(h, (size_t)nslots);
+    if (st != QAOA_OK) return st;
+    HIPCHECK(h, qk::launch_sum_slots(h->parts, count, count, nslots, sum_scale(h), results(h), h->stream));
+    return collect(h, (size_t)nslots, host);
+}
+
+// Whole host array of a folded one: the stored half, then its mirror image, turned
+// round on the device a scratch buffer at a time.
+qaoa_status unfold_to_host(qaoa_handle h, const void *half, size_t entry, void *out)
+{
+    const qaoa_status st = ensure_doubles(h, &h->parts, &h->parts_cap,
+                                          (size_t)std::min<uint64_t>(h->M * entry / 8, 1 << 20));
+    if (st != QAOA_OK) return st;
+    HIPCHECK(h, hipMemcpyAsync(out, half, h->M * entry, hipMemcpyDeviceToHost, h->stream));
+    const uint64_t step = h->parts_cap * 8 / entry;
+    for (uint64_t done = 0; done < h->M; done += step) {
+        const uint64_t k = std::min(step, h->M - done);
+        HIPCHECK(h, qk::launch_reverse((const char *)half + (h->M - done - k) * entry, k, (int)entry, h->parts, h->stream));
+        HIPCHECK(h, hipMemcpyAsync((char *)out + (h->M + done) * entry, h->parts, k * entry, hipMemcpyDeviceToHost, h->stream));
+    }
     HIPCHECK(h, hipStreamSynchronize(h->stream));
     return QAOA_OK;
 }
@@ -605,6 +665,7 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
     h->fold = qk::fold_state(n, precision == QAOA_C64, maxcut);
     h->M = h->fold ? h->N / 2 : h->N;
     h->alloc = g_alloc;
+    h->A = h->alloc.alloc ? h->N : h->M;
     try {
         h->plan = qk::plan_passes(n, precision == QAOA_C64);
         h->quad = qk::quad_tile_bits(n, h->fold ? n - 1 : n, precision == QAOA_C64);
@@ -641,8 +702,8 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
         h->own_stream = true;
     }
     *hh = h;
-    if ((e = dev_alloc(h, &h->psi, h->N * amp_bytes(precision))) != hipSuccess ||
-        (e = dev_alloc(h, &h->cost, h->N * cost_bytes(precision))) != hipSuccess) {
+    if ((e = dev_alloc(h, &h->psi, h->A * amp_bytes(precision))) != hipSuccess ||
+        (e = dev_alloc(h, &h->cost, h->A * cost_bytes(precision))) != hipSuccess) {
         qaoa_destroy(h);
         *hh = nullptr;
         if (e == hipErrorOutOfMemory) return fail(QAOA_ERR_OUT_OF_MEMORY, "state or cost allocation failed");
@@ -870,11 +931,13 @@ qaoa_status qaoa_destroy(qaoa_handle h)
     if (!h) return QAOA_OK;
     DeviceGuard dg(h->device);
     if (h->stream) (void)hipStreamSynchronize(h->stream);
-    dev_free(h, h->psi, h->N * amp_bytes(h->prec));
-    dev_free(h, h->lam, h->N * amp_bytes(h->prec));
-    dev_free(h, h->cost, h->N * cost_bytes(h->prec));
+    dev_free(h, h->psi, h->A * amp_bytes(h->prec));
+    dev_free(h, h->lam, h->A * amp_bytes(h->prec));
+    dev_free(h, h->cost, h->A * cost_bytes(h->prec));
     dev_free(h, h->parts, h->parts_cap * sizeof(double));
     dev_free(h, h->res, h->res_cap * sizeof(double));
+    if (h->pin) (void)hipHostFree(h->pin);
+    if (h->scanned) (void)hipEventDestroy(h->scanned);
     for (auto &pd : h->pending) {
         (void)hipEventDestroy(pd.t0);
         (void)hipEventDestroy(pd.t1);
@@ -900,13 +963,12 @@ qaoa_status qaoa_cost_diagonal(qaoa_handle h, double *out, int32_t out_is_device
     if (!out) return fail(QAOA_ERR_INVALID_ARGUMENT, "out is NULL");
     DeviceGuard dg(h->device);
     if (h->fold) {
-        if (out_is_device && (uintptr_t)out % sizeof(double) == 0) {
-            HIPCHECK(h, qk::launch_unfold_cost(c64(h), h->cost, h->M, out, h->stream));
+        if (out_is_device) {
+            HIPCHECK(h, c64(h) ? qk::launch_unfold_widen((const float *)h->cost, h->M, out, h->stream)
+                               : qk::launch_unfold(h->cost, h->M, 8, out, h->stream));
             return QAOA_OK;
         }
-        // the other half of the buffer takes the other half of the diagonal
-        HIPCHECK(h, c64(h) ? qk::launch_unfold_f32((const float *)h->cost, h->M, (float *)h->cost, h->stream)
-                           : qk::launch_unfold_cost(false, h->cost, h->M, (double *)h->cost, h->stream));
+        if (!c64(h)) return unfold_to_host(h, h->cost, 8, out);
     }
     if (!c64(h)) {
         HIPCHECK(h, hipMemcpyAsync(out, h->cost, h->N * 8,
@@ -921,13 +983,14 @@ qaoa_status qaoa_cost_diagonal(qaoa_handle h, double *out, int32_t out_is_device
     }
     std::vector<float> tmp;
     try {
-        tmp.resize(h->N);
+        tmp.resize(h->M);
     } catch (...) {
         return fail(QAOA_ERR_OUT_OF_MEMORY, "host staging buffer");
     }
-    HIPCHECK(h, hipMemcpyAsync(tmp.data(), h->cost, h->N * 4, hipMemcpyDeviceToHost, h->stream));
+    HIPCHECK(h, hipMemcpyAsync(tmp.data(), h->cost, h->M * 4, hipMemcpyDeviceToHost, h->stream));
     HIPCHECK(h, hipStreamSynchronize(h->stream));
-    for (uint64_t z = 0; z < h->N; ++z) out[z] = (double)tmp[z];
+    for (uint64_t z = 0; z < h->M; ++z) out[z] = (double)tmp[z];
+    for (uint64_t z = h->M; z < h->N; ++z) out[z] = (double)tmp[h->N - 1 - z];
     return QAOA_OK;
 }
 
@@ -940,11 +1003,11 @@ qaoa_status qaoa_cost_extrema(qaoa_handle h, double *cmin, double *cmax)
         DeviceGuard dg(h->device);
         const uint64_t T = (h->M + qk::kTile - 1) / qk::kTile;
         if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * T)) != QAOA_OK) return st;
+        if ((st = ensure_results(h, 2)) != QAOA_OK) return st;
         HIPCHECK(h, qk::launch_minmax(c64(h), h->cost, stored_bits(h), h->parts, h->parts + T, h->stream));
-        HIPCHECK(h, qk::launch_minmax_final(h->parts, h->parts + T, T, h->res, h->stream));
+        HIPCHECK(h, qk::launch_minmax_final(h->parts, h->parts + T, T, results(h), h->stream));
         double r[2];
-        HIPCHECK(h, hipMemcpyAsync(r, h->res, sizeof r, hipMemcpyDeviceToHost, h->stream));
-        HIPCHECK(h, hipStreamSynchronize(h->stream));
+        if ((st = collect(h, 2, r)) != QAOA_OK) return st;
         h->cmin = r[0];
         h->cmax = r[1];
         h->extrema_valid = true;
@@ -971,12 +1034,11 @@ qaoa_status qaoa_statevector(qaoa_handle h, int32_t p, const double *gamma, cons
     if ((st = keep_angles(h, p, gamma, beta)) != QAOA_OK) return st;
     h->state_valid = true;
     if (out) {
-        if (h->fold) {
-            const bool direct = out_is_device && (uintptr_t)out % amp_bytes(h->prec) == 0;
-            // not direct: the other half of the buffer takes the other half of the state
-            HIPCHECK(h, qk::launch_unfold_state(c64(h), h->psi, h->M, direct ? out : h->psi, h->stream));
-            if (direct) return QAOA_OK;
+        if (h->fold && out_is_device) {
+            HIPCHECK(h, qk::launch_unfold(h->psi, h->M, (int)amp_bytes(h->prec), out, h->stream));
+            return QAOA_OK;
         }
+        if (h->fold) return unfold_to_host(h, h->psi, amp_bytes(h->prec), out);
         HIPCHECK(h, hipMemcpyAsync(out, h->psi, h->N * amp_bytes(h->prec),
                                    out_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                                    h->stream));
@@ -1039,16 +1101,14 @@ qaoa_status qaoa_gradient(qaoa_handle h, int32_t p, const double *gamma, const d
     const uint64_t T = nblocks(h);
     const int nslots = 2 * p + 1;
     std::vector<double> r((size_t)nslots);
+    if ((st = ensure_results(h, (size_t)nslots)) != QAOA_OK) return st;
     if (small_gradient(h, p)) {
-        if ((st = ensure_doubles(h, &h->res, &h->res_cap, (size_t)nslots)) != QAOA_OK) return st;
         h->state_valid = false;
-        if ((st = enqueue_small(h, p, gamma, beta, h->res)) != QAOA_OK) return st;
-        HIPCHECK(h, hipMemcpyAsync(r.data(), h->res, (size_t)nslots * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-        HIPCHECK(h, hipStreamSynchronize(h->stream));
+        if ((st = enqueue_small(h, p, gamma, beta, results(h))) != QAOA_OK) return st;
+        if ((st = collect(h, (size_t)nslots, r.data())) != QAOA_OK) return st;
     } else {
         if ((st = ensure_lam(h)) != QAOA_OK) return st;
         if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, (size_t)nslots * T)) != QAOA_OK) return st;
-        if ((st = ensure_doubles(h, &h->res, &h->res_cap, (size_t)nslots)) != QAOA_OK) return st;
         h->state_valid = false;
         if ((st = enqueue_gradient(h, p, gamma, beta, h->lam, h->parts)) != QAOA_OK) return st;
         if ((st = fetch_results(h, nslots, T, r.data())) != QAOA_OK) return st;
@@ -1080,15 +1140,13 @@ qaoa_status qaoa_gradient_from_state(qaoa_handle h, int32_t p, const double *gam
     const uint64_t T = nblocks(h);
     const int nslots = 2 * p + 1;
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, (size_t)nslots * T)) != QAOA_OK) return st;
-    if ((st = ensure_doubles(h, &h->res, &h->res_cap, (size_t)nslots)) != QAOA_OK) return st;
+    if ((st = ensure_results(h, (size_t)nslots)) != QAOA_OK) return st;
     h->state_valid = false;
     if ((st = enqueue_reverse(h, p, gamma, beta, h->lam, h->parts)) != QAOA_OK) return st;
     // slots 1 .. 2p (slot 0, E, is not written by the reverse sweep)
-    HIPCHECK(h, qk::launch_sum_slots(h->parts + T, T, T, 2 * p, sum_scale(h), h->res, h->stream));
+    HIPCHECK(h, qk::launch_sum_slots(h->parts + T, T, T, 2 * p, sum_scale(h), results(h), h->stream));
     std::vector<double> r((size_t)(2 * p));
-    HIPCHECK(h, hipMemcpyAsync(r.data(), h->res, (size_t)(2 * p) * sizeof(double), hipMemcpyDeviceToHost,
-                               h->stream));
-    HIPCHECK(h, hipStreamSynchronize(h->stream));
+    if ((st = collect(h, r.size(), r.data())) != QAOA_OK) return st;
     for (int l = 0; l < p; ++l) {
         dbeta[l] = 2.0 * r[l];
         dgamma[l] = 2.0 * r[p + l];
@@ -1115,13 +1173,12 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     const size_t base = 2 * nsub + 1 + nscr;
     const size_t stage = out_is_device ? 0 : (size_t)shots * 2;
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, base + stage)) != QAOA_OK) return st;
+    if ((st = ensure_results(h, 1)) != QAOA_OK) return st;
+    if (h->pin && !h->scanned) HIPCHECK(h, hipEventCreateWithFlags(&h->scanned, hipEventDisableTiming));
     double *sub = h->parts, *pre = sub + nsub, *scr = pre + nsub + 1;
     HIPCHECK(h, qk::launch_submass(c64(h), h->psi, h->n, h->fold, sbits, sub, h->stream));
-    HIPCHECK(h, qk::launch_exclusive_scan(sub, nsub, pre, scr, h->stream));
-    double T = 0;
-    HIPCHECK(h, hipMemcpyAsync(&T, pre + nsub, sizeof T, hipMemcpyDeviceToHost, h->stream));
-    HIPCHECK(h, hipStreamSynchronize(h->stream));
-    if (!(T > 0.0) || !std::isfinite(T)) return fail(QAOA_ERR_INVALID_ARGUMENT, "state has zero norm");
+    HIPCHECK(h, qk::launch_exclusive_scan(sub, nsub, pre, scr, results(h), h->stream));
+    if (h->pin) HIPCHECK(h, hipEventRecord(h->scanned, h->stream));
     uint64_t *dz = z;
     double *dc = cost;
     if (!out_is_device) {
@@ -1130,6 +1187,15 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     }
     HIPCHECK(h, qk::launch_shots(c64(h), h->psi, h->cost, h->n, h->fold, sbits, pre, nsub, shots, seed, dz,
                                  dc, h->stream));
+    // the shots run while the total is waited for; without norm they write nothing
+    double T = 0;
+    if (h->pin) {
+        HIPCHECK(h, hipEventSynchronize(h->scanned));
+        T = h->pin[0];
+    } else if ((st = collect(h, 1, &T)) != QAOA_OK) {
+        return st;
+    }
+    if (!(T > 0.0) || !std::isfinite(T)) return fail(QAOA_ERR_INVALID_ARGUMENT, "state has zero norm");
     if (!out_is_device) {
         HIPCHECK(h, hipMemcpyAsync(z, dz, (size_t)shots * 8, hipMemcpyDeviceToHost, h->stream));
         if (cost)

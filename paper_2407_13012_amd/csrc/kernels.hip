@@ -52,8 +52,14 @@ __global__ __launch_bounds__(kThreads) void k_sum_slots(const double *parts, uin
 {
     __shared__ double red[4];
     const double *p = parts + (uint64_t)blockIdx.x * stride;
-    double acc = 0.0;
-    for (uint64_t i = threadIdx.x; i < count; i += kThreads) acc += p[i];
+    // eight loads in flight per thread (one by one: 430 us for 2^18 partials a slot, n = 30)
+    double a[8] = {};
+    for (uint64_t i = threadIdx.x; i < count; i += 8 * kThreads) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (i + r * kThreads < count) a[r] += p[i + r * kThreads];
+    }
+    const double acc = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
     const double s = block_sum(acc, red);
     if (threadIdx.x == 0) out[blockIdx.x] = scale * s;
 }
@@ -219,22 +225,33 @@ __global__ __launch_bounds__(kThreads) void k_widen(const float *C32, double *ou
 
 // out[z] = out[2 half - 1 - z] = in[z]: a whole array from the half of a folded
 // one (z and ~z hold the same value).  Bound by memory: the half is read once,
-// where copying an unfolded array would read it all.  in == out leaves the
-// first half as it is.
-template <typename A, typename B>
-__device__ __forceinline__ B widen_to(A v)
-{
-    if constexpr (std::is_same<A, B>::value) return v;
-    else return (B)v;
-}
-template <typename A, typename B>
-__global__ __launch_bounds__(kThreads) void k_unfold(const A *in, uint64_t half, B *out)
+// where copying an unfolded array would read it all.
+// W is the unit of the copy: the entry, or a part of it that the output's
+// alignment allows (`words` of them make an entry).
+template <typename W>
+__global__ __launch_bounds__(kThreads) void k_unfold_words(const W *in, uint64_t half, uint32_t words, W *out)
 {
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-    const bool self = (const void *)in == (const void *)out;
+    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < half * words; i += stride) {
+        const W v = in[i];
+        out[i] = v;
+        out[(2 * half - 1 - i / words) * words + i % words] = v;
+    }
+}
+// out[i] = in[count - 1 - i]
+template <typename W>
+__global__ __launch_bounds__(kThreads) void k_reverse(const W *in, uint64_t count, W *out)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
+    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < count; i += stride) out[i] = in[count - 1 - i];
+}
+// The same for cost entries, fp32 widened to fp64.
+__global__ __launch_bounds__(kThreads) void k_unfold_widen(const float *in, uint64_t half, double *out)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t z = (uint64_t)blockIdx.x * kThreads + threadIdx.x; z < half; z += stride) {
-        const B v = widen_to<A, B>(in[z]);
-        if (!self) out[z] = v;
+        const double v = (double)in[z];
+        out[z] = v;
         out[2 * half - 1 - z] = v;
     }
 }
@@ -378,10 +395,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_top(double *tot, uint64_t nch
     if (threadIdx.x == 0) tot[nchunks] = total;
 }
 
-// out[i] = sum_{k < i} in[k] for i <= count (out[count] = total).
+// out[i] = sum_{k < i} in[k] for i <= count (out[count] = *total_out = total).
 __global__ __launch_bounds__(kThreads) void k_scan_final(const double *in, uint64_t count,
                                                          const double *tot, uint64_t nchunks,
-                                                         double *out)
+                                                         double *out, double *total_out)
 {
     __shared__ double sh[kThreads + 1];
     const uint64_t c0 = (uint64_t)blockIdx.x * kScanChunk;
@@ -399,7 +416,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_final(const double *in, uint6
         if (i < count) out[i] = run;
         run += v[r];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = tot[nchunks];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out[count] = tot[nchunks];
+        *total_out = tot[nchunks];
+    }
 }
 
 // W shots per wave (grid-stride), a lane each: u -> target t = u * total, binary search
@@ -422,6 +442,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
     constexpr int kLoads = 8, kRows = W / 8, kStep = 8 * kLoads / kRows;  // loads in flight; amplitudes per turn
     __shared__ double mass[kThreads / 64][W][kStep + 1];
     const double T = pre[nsub];
+    if (!(T > 0.0) || T == INFINITY) return;  // no shots from such a state (the caller reports it)
     const uint32_t lane = threadIdx.x & 63u, sub = lane & 7u, row = lane >> 3;
     double (*m)[kStep + 1] = mass[threadIdx.x >> 6];
     const uint64_t sb = 1ull << sbits;
@@ -609,31 +630,33 @@ hipError_t launch_fill_plus(bool c64, void *psi, int n, uint64_t count, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_unfold_state(bool c64, const void *in, uint64_t half, void *out, hipStream_t s)
+hipError_t launch_unfold(const void *in, uint64_t half, int entry_bytes, void *out, hipStream_t s)
 {
-    if (c64)
-        hipLaunchKernelGGL((k_unfold<float2, float2>), dim3(grid_for(half)), dim3(kThreads), 0, s,
-                           (const float2 *)in, half, (float2 *)out);
-    else
-        hipLaunchKernelGGL((k_unfold<double2, double2>), dim3(grid_for(half)), dim3(kThreads), 0, s,
-                           (const double2 *)in, half, (double2 *)out);
+    const uintptr_t a = (uintptr_t)out;
+    const auto go = [&](auto w) {
+        using W = decltype(w);
+        const uint32_t words = (uint32_t)(entry_bytes / sizeof(W));
+        hipLaunchKernelGGL(k_unfold_words<W>, dim3(grid_for(half * words)), dim3(kThreads), 0, s, (const W *)in, half,
+                           words, (W *)out);
+        return hipGetLastError();
+    };
+    if (entry_bytes == 16 && a % 16 == 0) return go(uint4{});
+    if (entry_bytes >= 8 && a % 8 == 0) return go(uint64_t{});
+    return a % 4 == 0 ? go(uint32_t{}) : go(uint8_t{});
+}
+
+hipError_t launch_reverse(const void *in, uint64_t count, int entry_bytes, void *out, hipStream_t s)
+{
+    const dim3 grid(grid_for(count)), block(kThreads);
+    if (entry_bytes == 16) hipLaunchKernelGGL(k_reverse<uint4>, grid, block, 0, s, (const uint4 *)in, count, (uint4 *)out);
+    else if (entry_bytes == 8) hipLaunchKernelGGL(k_reverse<uint64_t>, grid, block, 0, s, (const uint64_t *)in, count, (uint64_t *)out);
+    else hipLaunchKernelGGL(k_reverse<uint32_t>, grid, block, 0, s, (const uint32_t *)in, count, (uint32_t *)out);
     return hipGetLastError();
 }
 
-hipError_t launch_unfold_f32(const float *in, uint64_t half, float *out, hipStream_t s)
+hipError_t launch_unfold_widen(const float *in, uint64_t half, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_unfold<float, float>), dim3(grid_for(half)), dim3(kThreads), 0, s, in, half, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_unfold_cost(bool c64, const void *in, uint64_t half, double *out, hipStream_t s)
-{
-    if (c64)
-        hipLaunchKernelGGL((k_unfold<float, double>), dim3(grid_for(half)), dim3(kThreads), 0, s,
-                           (const float *)in, half, out);
-    else
-        hipLaunchKernelGGL((k_unfold<double, double>), dim3(grid_for(half)), dim3(kThreads), 0, s,
-                           (const double *)in, half, out);
+    hipLaunchKernelGGL(k_unfold_widen, dim3(grid_for(half)), dim3(kThreads), 0, s, in, half, out);
     return hipGetLastError();
 }
 
@@ -704,7 +727,7 @@ hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbi
 }
 
 hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, double *scratch,
-                                 hipStream_t s)
+                                 double *total, hipStream_t s)
 {
     const uint64_t nchunks = (count + kScanChunk - 1) / kScanChunk;
     if (nchunks > (uint64_t)kScanChunk) return hipErrorInvalidValue;
@@ -712,7 +735,7 @@ hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, 
                        scratch);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kThreads), 0, s, scratch, nchunks);
     hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nchunks), dim3(kThreads), 0, s, in, count,
-                       scratch, nchunks, out);
+                       scratch, nchunks, out, total);
     return hipGetLastError();
 }
 

@@ -232,11 +232,12 @@ hipError_t launch_cost_pieces(bool c64, void *C, int n, const CostPiece *pieces,
                               double offset, hipStream_t s);
 // psi[0 .. count) = 2^{-n/2}
 hipError_t launch_fill_plus(bool c64, void *psi, int n, uint64_t count, hipStream_t s);
-// Whole arrays from folded ones: out[z] = out[2 half - 1 - z] = in[z], z < half
-// (amplitudes; cost entries widened to fp64).  out may be `in` itself (same type).
-hipError_t launch_unfold_state(bool c64, const void *in, uint64_t half, void *out, hipStream_t s);
-hipError_t launch_unfold_cost(bool c64, const void *in, uint64_t half, double *out, hipStream_t s);
-hipError_t launch_unfold_f32(const float *in, uint64_t half, float *out, hipStream_t s);
+// Whole arrays from folded ones: out[z] = out[2 half - 1 - z] = in[z], z < half, for
+// entries of 8 or 16 bytes at any address, or fp32 entries widened to fp64.
+hipError_t launch_unfold(const void *in, uint64_t half, int entry_bytes, void *out, hipStream_t s);
+hipError_t launch_unfold_widen(const float *in, uint64_t half, double *out, hipStream_t s);
+// out[i] = in[count - 1 - i], entries of 4, 8 or 16 bytes
+hipError_t launch_reverse(const void *in, uint64_t count, int entry_bytes, void *out, hipStream_t s);
 hipError_t launch_expect(bool c64, const void *psi, const void *C, int n, double *parts,
                          hipStream_t s);
 hipError_t launch_minmax(bool c64, const void *C, int n, double *pmin, double *pmax,
@@ -252,8 +253,9 @@ int sample_subblock_bits(int n);
 uint64_t scan_scratch_doubles(uint64_t count);
 hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub,
                           hipStream_t s);
+// *total (may be host memory) also receives the sum.
 hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, double *scratch,
-                                 hipStream_t s);
+                                 double *total, hipStream_t s);
 hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool folded, int sbits,
                         const double *pre, uint64_t nsub, int64_t shots, uint64_t seed,
                         uint64_t *z, double *cost, hipStream_t s);
