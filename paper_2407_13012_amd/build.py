@@ -28,7 +28,8 @@ def units() -> list[tuple[str, list[str], str]]:
         many = ["-DQK_PASS_MANY=1"] if real == "double" else []
         out.append((PASS_SOURCE, [f"-DQK_PASS_REAL={real}", f"-DQK_PASS_SP={sp}", *many], f"passes_{tag}.o"))
     for real in ("double", "float"):
-        out.append((QUAD_SOURCE, [f"-DQK_QUAD_REAL={real}"], f"quad_{'c128' if real == 'double' else 'c64'}.o"))
+        many = ["-DQK_PASS_MANY=1"] if real == "double" else []
+        out.append((QUAD_SOURCE, [f"-DQK_QUAD_REAL={real}", *many], f"quad_{'c128' if real == 'double' else 'c64'}.o"))
     return out
 ARCH = os.environ.get("QAOA_OFFLOAD_ARCH", "gfx950")
 

@@ -69,9 +69,9 @@ struct qaoa_handle_s {
     double *res = nullptr;
     size_t res_cap = 0;    // doubles
     hipEvent_t scanned = nullptr;  // sampling: the total mass has been written
-    std::vector<qk::PassPlan> plan;  // mixer sweeps of one layer (fixed by n and precision)
+    std::vector<qk::Geometry> plan;  // mixer sweeps of one layer (fixed by n and precision)
     int quad = 0;                    // tile bits of the small-tile sweeps (0: none at this n)
-    std::vector<qk::PassPlan> quad_plan;
+    std::vector<qk::Geometry> quad_plan;
     bool on_quad = false;            // the current call's sweeps run on quad_plan (choose_tiles)
     bool state_valid = false;
     std::vector<double> state_angles;  // (gamma, beta) of the current state
@@ -168,7 +168,7 @@ inline uint64_t max_nblocks(const qaoa_handle h)
 {
     return std::max(h->quad ? h->M >> h->quad : 0, nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0));
 }
-inline const std::vector<qk::PassPlan> &plan_of(const qaoa_handle h) { return h->on_quad ? h->quad_plan : h->plan; }
+inline const std::vector<qk::Geometry> &plan_of(const qaoa_handle h) { return h->on_quad ? h->quad_plan : h->plan; }
 // Factor of the sums over the stored amplitudes.
 inline double sum_scale(const qaoa_handle h) { return h->fold ? 2.0 : 1.0; }
 // Qubits of a plain streaming kernel over the stored entries.
@@ -277,16 +277,15 @@ qaoa_status collect(qaoa_handle h, size_t count, double *host)
     return QAOA_OK;
 }
 
-// Kernel arguments of one pass over plan entry `pp` with mixer angle `beta`.
-qk::PassArgs pass_args(qaoa_handle h, const qk::PassPlan &pp, double beta)
+// Kernel arguments of one pass over a plan entry with mixer angle `beta`.
+qk::PassArgs pass_args(qaoa_handle h, const qk::Geometry &geo, double beta)
 {
     qk::PassArgs a;
     std::memset(&a, 0, sizeof a);
     a.psi = h->psi;
     a.lam = h->lam;
     a.cost = h->cost;
-    qk::make_geometry(h->n, pp, &a.geo);  // plans are validated when made
-    if (h->fold) qk::fold_geometry(h->n, pp, &a.geo);
+    a.geo = geo;
     // Nontemporal accesses pay off for runs of >= 64 consecutive amplitudes; for
     // short runs the L2 must keep each line for the neighbouring tile.
     if (a.geo.t_dst[0] == 0 && a.geo.t_len[0] >= 6) a.flags |= qk::kStream;
@@ -433,7 +432,7 @@ qaoa_status drain_profile(qaoa_handle h)
 qaoa_status run_forward(qaoa_handle h, int p, const double *gamma, const double *beta,
                         bool skip_last, bool e_out)
 {
-    const std::vector<qk::PassPlan> &G = plan_of(h);
+    const std::vector<qk::Geometry> &G = plan_of(h);
     const int P = (int)G.size();
     for (int l = 0; l < p; ++l) {
         for (int idx = 0; idx < P; ++idx) {
@@ -492,7 +491,7 @@ struct Slots {
 qaoa_status enqueue_backward(qaoa_handle h, int p, const double *gamma, const double *beta, void *lam,
                              const Slots &sl)
 {
-    const std::vector<qk::PassPlan> &G = plan_of(h);
+    const std::vector<qk::Geometry> &G = plan_of(h);
     const int P = (int)G.size();
     for (int l = p - 1; l >= 0; --l) {
         for (int j = 0; j < P; ++j) {
@@ -534,7 +533,7 @@ qaoa_status enqueue_gradient(qaoa_handle h, int p, const double *gamma, const do
 {
     qaoa_status st;
     const Slots sl{parts, nblocks(h), p};
-    const std::vector<qk::PassPlan> &G = plan_of(h);
+    const std::vector<qk::Geometry> &G = plan_of(h);
     const int P = (int)G.size();
 
     // Forward through every group except the last group of the last layer.
@@ -580,7 +579,7 @@ qaoa_status enqueue_reverse(qaoa_handle h, int p, const double *gamma, const dou
                             double *parts)
 {
     const Slots sl{parts, nblocks(h), p};
-    const std::vector<qk::PassPlan> &G = plan_of(h);
+    const std::vector<qk::Geometry> &G = plan_of(h);
     const int P = (int)G.size();
     const int l = p - 1;
     qk::PassArgs a = pass_args(h, G[P > 1 ? group_at(l, P - 1, P) : 0], beta[l]);
@@ -632,6 +631,19 @@ qaoa_status fetch_results(qaoa_handle h, int nslots, uint64_t count, double *hos
     return collect(h, (size_t)nslots, host);
 }
 
+// Kernel form of a plan's passes over the handle's state (plans are validated when made).
+std::vector<qk::Geometry> geometries(qaoa_handle h, const std::vector<qk::PassPlan> &plan)
+{
+    std::vector<qk::Geometry> out;
+    for (const qk::PassPlan &pp : plan) {
+        qk::Geometry g;
+        qk::make_geometry(h->n, pp, &g);
+        if (h->fold) qk::fold_geometry(h->n, pp, &g);
+        out.push_back(g);
+    }
+    return out;
+}
+
 // Whole host array of a folded one: the stored half, then its mirror image, turned
 // round on the device a scratch buffer at a time.
 qaoa_status unfold_to_host(qaoa_handle h, const void *half, size_t entry, void *out)
@@ -667,9 +679,9 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
     h->alloc = g_alloc;
     h->A = h->alloc.alloc ? h->N : h->M;
     try {
-        h->plan = qk::plan_passes(n, precision == QAOA_C64);
+        h->plan = geometries(h, qk::plan_passes(n, precision == QAOA_C64));
         h->quad = qk::quad_tile_bits(n, h->fold ? n - 1 : n, precision == QAOA_C64);
-        if (h->quad) h->quad_plan = qk::plan_quad(n, h->quad);
+        if (h->quad) h->quad_plan = geometries(h, qk::plan_quad(n, h->quad));
     } catch (...) {
         delete h;
         return fail(QAOA_ERR_OUT_OF_MEMORY, "host allocation failed");

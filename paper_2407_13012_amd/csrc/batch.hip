@@ -656,6 +656,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     std::vector<qk::Geometry> geo((qk::kMaxBatchN + 1) * qk::kMaxPasses);
     std::vector<int32_t> npass(qk::kMaxBatchN + 1, 0);
     std::vector<std::vector<qk::PassPlan>> plans(qk::kMaxBatchN + 1);
+    int depth[qk::kMaxBatchN + 1] = {};
     for (int m = 2; m <= nmax; ++m) {
         const int kg = o.group_by_n[m] ? o.group_by_n[m] : o.max_group;
         const std::vector<qk::PassPlan> pl = qk::plan_passes(m, false, kg);
@@ -663,6 +664,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
         npass[m] = (int32_t)pl.size();
         for (size_t j = 0; j < pl.size(); ++j) qk::make_geometry(m, pl[j], &geo[m * qk::kMaxPasses + j]);
         plans[m] = pl;
+        depth[m] = kg;
     }
     std::vector<int32_t> order(count);
     std::iota(order.begin(), order.end(), 0);
@@ -684,7 +686,8 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     size_t scratch = 0;
     try {
         if (b->nbig)
-            b->classes = qk::make_classes(order, n, b->nbig, p, (uint64_t)b->workgroups * slot - small, plans, &scratch);
+            b->classes = qk::make_classes(order, n, b->nbig, p, (uint64_t)b->workgroups * slot - small, plans, depth,
+                                            &scratch);
     } catch (...) {
         return cleanup(bfail(QAOA_ERR_OUT_OF_MEMORY, "host allocation"));
     }

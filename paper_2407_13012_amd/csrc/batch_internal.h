@@ -44,6 +44,7 @@ struct SizeClass {
     int cap = 0;               // instances at a time
     int stream = 0;
     uint64_t M = 0, T = 0;     // stored amplitudes and tiles per instance
+    int quad = 0;              // tile bits of the small-tile sweeps (0: the large tiles)
     std::vector<Geometry> geo; // folded passes of one layer
     double2 *psi = nullptr, *lam = nullptr;
     double *cost = nullptr;
@@ -54,9 +55,10 @@ struct SizeClass {
 };
 
 // Size classes of the instances order[0 .. nbig), cut out of `amps` amplitudes
-// of vector space; small buffers are counted in *scratch (bytes).
+// of vector space; small buffers are counted in *scratch (bytes).  depth[n]: most
+// qubits a pass after the first may rotate, which `plans` keep to.
 std::vector<SizeClass> make_classes(const std::vector<int32_t> &order, const int32_t *n, int nbig, int p,
-                                    uint64_t amps, const std::vector<std::vector<PassPlan>> &plans, size_t *scratch);
+                                    uint64_t amps, const std::vector<std::vector<PassPlan>> &plans, const int *depth, size_t *scratch);
 // Carves the classes' vectors (from psi, lam, cost) and small buffers (from scratch).
 void place_classes(std::vector<SizeClass> &cls, int p, double2 *psi, double2 *lam, double *cost, void *scratch);
 // Enqueues the whole optimisation of the classes on the kManyStreams streams.

@@ -6,11 +6,11 @@
 // 47 others (48 ms beside 511) and the batch ends with its last large instances
 // on a nearly idle card.  Swept together, a pass of one n = 20 instance is 128
 // workgroups, and the kernels are those of the single-instance path, compiled
-// per spectator class.  The angles stay on the device: k_many_adam sums the
+// per spectator class, or on small tiles.  The angles stay on the device: k_many_adam sums the
 // partials of a step, updates the angles and leaves the rotations' coefficients
 // for the next step's passes.  Sizes are independent of each other and run on
 // three streams.  Measured (p = 4, n ~ U{10..20}): 48 graphs x 8 steps
-// 323 -> 6.0 ms, 1024 graphs x 3 steps 210 -> 26.9 ms (there at 5.5 TB/s;
+// 323 -> 5.1 ms, 1024 graphs x 3 steps 210 -> 26.9 ms (there at 5.5 TB/s;
 // fewer instances at a time, so that their vectors stay in the last-level cache,
 // are slower: 28.0 ms with 192 MB per size, 33.8 with 64 MB).
 //
@@ -186,7 +186,7 @@ struct Chunk {
         a.part_g = pg;
         a.part_b2 = pb2;
         const ManyArgs m{c.coef, c.M, c.T, B.p, layer, layer2, layer_phase};
-        return launch_many(mode, a, m, c.T, count, s);
+        return c.quad ? launch_many_quad(mode, c.quad, a, m, c.T, count, s) : launch_many(mode, a, m, c.T, count, s);
     }
 
     // Layers forward; grad: without the last layer's last group (the turn pass).
@@ -216,7 +216,7 @@ struct Chunk {
         hipLaunchKernelGGL(k_many_start, dim3(count), dim3(64), 0, s, B, begin, c.am, c.av, c.coef, c.step);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_many_cost, dim3((unsigned)c.T, count), dim3(kThreads), 0, s, B, begin, c.cost, c.M);
+        hipLaunchKernelGGL(k_many_cost, dim3((unsigned)(c.M >> kTileBits), count), dim3(kThreads), 0, s, B, begin, c.cost, c.M);
         return hipGetLastError();
     }
 
@@ -261,7 +261,7 @@ size_t class_scratch(const SizeClass &c, int p)
 }  // namespace
 
 std::vector<SizeClass> make_classes(const std::vector<int32_t> &order, const int32_t *n, int nbig, int p,
-                                    uint64_t amps, const std::vector<std::vector<PassPlan>> &plans, size_t *scratch)
+                                    uint64_t amps, const std::vector<std::vector<PassPlan>> &plans, const int *depth, size_t *scratch)
 {
     std::vector<SizeClass> cls;
     for (int k = 0; k < nbig; ++k) {
@@ -271,13 +271,6 @@ std::vector<SizeClass> make_classes(const std::vector<int32_t> &order, const int
             c.n = m;
             c.begin = k;
             c.M = 1ull << (m - 1);
-            c.T = c.M >> kTileBits;
-            for (const PassPlan &pp : plans[m]) {
-                Geometry g;
-                make_geometry(m, pp, &g);
-                fold_geometry(m, pp, &g);
-                c.geo.push_back(g);
-            }
             cls.push_back(c);
         }
         ++cls.back().count;
@@ -295,6 +288,25 @@ std::vector<SizeClass> make_classes(const std::vector<int32_t> &order, const int
         const uint64_t more = std::min<uint64_t>({(uint64_t)c.count - 1, left / c.M, 65534});
         c.cap += (int)more;
         left -= more * c.M;
+    }
+    // Small tiles while all that runs together makes up at most the 16 MiB up to
+    // which one state takes them, and the depth asked for allows their two passes.
+    // Beside larger classes, which fill the card, only classes of up to 2 MiB gain
+    // (48 graphs, n = 10 .. 20: 6.58 ms with none on small tiles, 5.13 with classes
+    // of up to 2 MiB, 5.32 with 8, 5.45 with 32).
+    uint64_t together = 0;
+    for (const SizeClass &c : cls) together += (uint64_t)c.cap * c.M;
+    const uint64_t most = together <= (1ull << 20) ? 1ull << 20 : 1ull << 17;
+    for (SizeClass &c : cls) {
+        c.quad = (uint64_t)c.cap * c.M <= most ? quad_tile_bits(c.n, c.n - 1, false) : 0;
+        if (c.quad && c.n - c.quad > depth[c.n]) c.quad = 0;
+        c.T = c.M >> (c.quad ? c.quad : kTileBits);
+        for (const PassPlan &pp : c.quad ? plan_quad(c.n, c.quad) : plans[c.n]) {
+            Geometry g;
+            make_geometry(c.n, pp, &g);
+            fold_geometry(c.n, pp, &g);
+            c.geo.push_back(g);
+        }
     }
     // three streams, the most work first to the least loaded: a sweep costs its
     // traffic (440 B per stored amplitude and step) or a launch's latency

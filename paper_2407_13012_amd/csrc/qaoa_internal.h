@@ -192,6 +192,9 @@ struct ManyArgs {
 };
 hipError_t launch_many(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
                        hipStream_t s);
+// on the small tiles of a plan_quad plan
+hipError_t launch_many_quad(int mode, int tbits, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
+                            hipStream_t s);
 template <int SP>
 hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
                           hipStream_t s);

@@ -9,10 +9,14 @@
 // E + G at p = 6, complex128 MaxCut: n = 17 230 -> 122 us (a sweep 14-19 -> 7 us).
 //
 // Compiled once per QK_QUAD_REAL (double or float).
+#include "many_device.h"
 #include "quad.h"
 
 #ifndef QK_QUAD_REAL
 #error "QK_QUAD_REAL (double or float) must be defined"
+#endif
+#ifndef QK_PASS_MANY  // 1 in the complex128 unit: with the sweeps of the batched engine
+#define QK_PASS_MANY 0
 #endif
 
 namespace qk {
@@ -272,6 +276,45 @@ hipError_t launch_quad_real(int mode, int tbits, const PassArgs &a, uint64_t nbl
     default: return hipErrorInvalidValue;
     }
 }
+#if QK_PASS_MANY
+namespace {
+// many instances (k_many_pass): every rotation in the tan form
+template <int M, int MODE>
+__global__ __launch_bounds__((1 << M) / 4) void k_many_quad(PassArgs a, ManyArgs n)
+{
+    __shared__ QuadLds<double, M> m;
+    many_args(a, n);
+    quad_body<double, M, MODE, true, true>(a, m);
+}
+template <int M>
+hipError_t launch_many_quad_m(int mode, const PassArgs &a, const ManyArgs &m, dim3 grid, hipStream_t s)
+{
+    const dim3 block((1 << M) / 4);
+    switch (mode) {
+    case kFwd: hipLaunchKernelGGL((k_many_quad<M, kFwd>), grid, block, 0, s, a, m); break;
+    case kTurn: hipLaunchKernelGGL((k_many_quad<M, kTurn>), grid, block, 0, s, a, m); break;
+    case kBwd: hipLaunchKernelGGL((k_many_quad<M, kBwd>), grid, block, 0, s, a, m); break;
+    case kFwdFuse: hipLaunchKernelGGL((k_many_quad<M, kFwdFuse>), grid, block, 0, s, a, m); break;
+    case kBwdFuse: hipLaunchKernelGGL((k_many_quad<M, kBwdFuse>), grid, block, 0, s, a, m); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_many_quad(int mode, int tbits, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
+                            hipStream_t s)
+{
+    if ((int)a.geo.tbits != tbits || (a.geo.tmask >> 8) != ((1u << tbits) - 1u) >> 8) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nblocks, count);
+    switch (tbits) {
+    case 10: return launch_many_quad_m<10>(mode, a, m, grid, s);
+    case 11: return launch_many_quad_m<11>(mode, a, m, grid, s);
+    case 12: return launch_many_quad_m<12>(mode, a, m, grid, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+#endif
 template hipError_t launch_quad_real<QK_QUAD_REAL>(int, int, const PassArgs &, uint64_t, hipStream_t);
 
 }  // namespace qk

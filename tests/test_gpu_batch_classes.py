@@ -68,3 +68,20 @@ def test_far_phases_take_the_persistent_launch():
         E = oracle.expectation(g.n, C, oracle.state(g.n, C, g0[i], b0[i]))
         assert abs(e0[i] - E) <= 1e-7 * float(np.abs(g.weight_array()).sum())
     assert np.all(np.isfinite(gam)) and np.all(np.isfinite(e1))
+
+
+def test_small_tiles_of_a_class():
+    """A class on small tiles (three instances of n = 14) and, with a depth that
+    their second pass exceeds or beside a class that fills the card, on the large
+    ones: the same results to rounding, and the oracle's."""
+    graphs = _graphs([14, 14, 18, 14], seed=7)
+    p, steps = 3, 3
+    g0, b0 = np.tile(qi.linear_ramp(p)[0], (4, 1)), np.tile(qi.linear_ramp(p)[1], (4, 1))
+    small, _ = _run(graphs, p, g0, b0, steps=steps)
+    large, _ = _run(graphs, p, g0, b0, steps=steps, group_by_n={14: 3, 18: 6})
+    big = _graphs([20, 20, 20], seed=8)
+    beside, _ = _run(graphs + big, p, np.tile(g0[0], (7, 1)), np.tile(b0[0], (7, 1)), steps=steps)
+    for a, b, c in zip(small, large, beside):
+        np.testing.assert_allclose(a, b, rtol=0, atol=1e-9)
+        np.testing.assert_allclose(a, c[:4], rtol=0, atol=1e-9)
+    _check(graphs, g0, b0, small, steps, 1e-8)
