@@ -53,28 +53,9 @@ union Frag {
     bf16x8 v;
 };
 
-// Eight consecutive-k bf16 values of one row (A) or column (B) of an operand:
-// element (outer, k) sits at P[outer * s_outer + k * s_k].  Out-of-range
-// entries read as zero.
-__device__ __forceinline__ bf16x8 load_frag(const uint16_t *P, int64_t s_outer, int64_t s_k, int outer,
-                                            int OUT, int k, int kend, bool contig)
-{
-    Frag r;
-    if (contig && outer < OUT && k + 8 <= kend) {
-        r.u = *(const uint4 *)(P + (int64_t)outer * s_outer + k);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            r.h[j] = (outer < OUT && k + j < kend) ? P[(int64_t)outer * s_outer + (int64_t)(k + j) * s_k] : 0;
-    }
-    return r.v;
-}
-
 struct GemmArgs {
-    const uint16_t *A;  // op(A)[m][k] = A[m * sam + k * sak]
-    int64_t sam, sak;
-    const uint16_t *B;  // op(B)[k][n] = B[k * sbk + n * sbn]
-    int64_t sbk, sbn;
+    const uint16_t *A, *B;  // op(A)[m][k], op(B)[k][n]: k (AK, BK) or m, n consecutive,
+    int64_t lda, ldb;       // the other index at these strides
     int M, N, K;
     int kchunk;          // K range of one blockIdx.z (a multiple of 32)
     float *C32;          // fp32 result (split: partial of slice z at C32 + z * split_stride)
@@ -85,91 +66,246 @@ struct GemmArgs {
     const float *mask;   // optional: result multiplied by (mask[m][n] > 0)
     int64_t ldmask;
     int relu;
-    int contigA, contigB;
+    int splits;          // K slices (blockIdx.z below it)
+    // column sums of a fp32 matrix that ride along in the blocks from `splits` on
+    // (X == nullptr: none): rows_per rows a chunk, chunk c's sums at part + c * C
+    struct {
+        const float *X;
+        int R, C;
+        int64_t ld;
+        int rows_per, chunks;
+        float *part;
+    } cs;
 };
+
+__device__ __forceinline__ float ordered_sum(const float *x, int64_t stride, int count);
+
+// Eight bf16 values in memory order; those from `keep` on are made zero.
+__device__ __forceinline__ uint4 load8(const uint16_t *p, int keep)
+{
+    uint4 u = *(const uint4 *)p;
+    uint32_t *w = (uint32_t *)&u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = keep >= 2 * j + 2 ? w[j] : keep == 2 * j + 1 ? w[j] & 0xFFFFu : 0u;
+    return u;
+}
+
+// Operand tiles in LDS: 64 outer indices (rows of A, columns of B) x 64 k, row
+// stride 68 so that the fragment reads of 16 rows hit distinct banks.
+constexpr int kTileK = 64, kTileLd = kTileK + 4;
+
+// One thread's share of an operand tile, two groups of 8 values on their way from
+// memory to LDS.  KC: k are consecutive in memory, a group is 8 k of one outer
+// index; else outer indices are, a group is 8 of them at one k.  Values at k
+// outside the range are zero; those of outer indices outside it are read from
+// inside (they only reach results that are not stored).
+template <bool KC>
+struct TileLoad {
+    uint4 f[2];
+    __device__ __forceinline__ void load(const uint16_t *P, int64_t ld, int o0, int OUT, int k0, int kend)
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int g = threadIdx.x + 256 * h;
+            const int o = o0 + (KC ? g >> 3 : 8 * (g & 7)), k = k0 + (KC ? 8 * (g & 7) : g >> 3);
+            if constexpr (KC) f[h] = load8(P + (int64_t)min(o, OUT - 1) * ld + min(k, (kend - 1) & ~7), kend - k);
+            else f[h] = load8(P + (int64_t)min(k, kend - 1) * ld + min(o, (OUT - 1) & ~7), k < kend ? 8 : 0);
+        }
+    }
+    __device__ __forceinline__ void store(uint16_t (*t)[kTileLd]) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int g = threadIdx.x + 256 * h;
+            if constexpr (KC) {
+                uint64_t *p = (uint64_t *)&t[g >> 3][8 * (g & 7)];
+                p[0] = ((uint64_t)f[h].y << 32) | f[h].x;
+                p[1] = ((uint64_t)f[h].w << 32) | f[h].z;
+            } else {
+                Frag v;
+                v.u = f[h];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) t[8 * (g & 7) + j][g >> 3] = v.h[j];
+            }
+        }
+    }
+};
+
+__device__ __forceinline__ bf16x8 tile_frag(const uint16_t (*t)[kTileLd], int row, int k)
+{
+    const uint64_t *p = (const uint64_t *)&t[row][k];
+    Frag f;
+    f.u = make_uint4((uint32_t)p[0], (uint32_t)(p[0] >> 32), (uint32_t)p[1], (uint32_t)(p[1] >> 32));
+    return f.v;
+}
+
+// Eight k of one row of an operand whose k are consecutive, straight from memory.
+__device__ __forceinline__ bf16x8 row_frag(const uint16_t *P, int64_t ld, int outer, int OUT, int k, int kend)
+{
+    Frag r;
+    r.u = load8(P + (int64_t)min(outer, OUT - 1) * ld + min(k, (kend - 1) & ~7), kend - k);
+    return r.v;
+}
 
 // C = op(A) op(B) on 64 x 64 output tiles: four waves of 32 x 32, each a 2 x 2
 // grid of 16x16x32 bf16 MFMAs accumulating in fp32.  Per MFMA, lane l holds
 // row l % 16 of A and column l % 16 of B over k = 8 (l / 16) .. + 8, and
-// receives C rows 4 (l / 16) .. + 4 of column l % 16.
+// receives C rows 4 (l / 16) .. + 4 of column l % 16.  AK, BK: k are consecutive
+// in the memory of A, of B; else the outer indices are.  Every load is 16 bytes
+// (the launcher checks strides and alignment).
+//
+// The products are small (K = 32 .. 288 per workgroup), so a workgroup is bound by
+// its chain of waits, and by fetching code that runs once: with guarded loads that
+// fell back to single values and a bias load in each result's branch a product
+// took 9 to 17 us.  Operands with consecutive k go straight to fragments, two
+// steps at a time; others are turned round in LDS, the next tile on its way while
+// one is multiplied; bias and mask are loaded before they are needed: 5 to 10 us
+// (a layer of 3800 nodes 10.5 -> 9.5, its weight gradient 17.5 -> 8.5 us).
+template <bool AK, bool BK>
 __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m_base = blockIdx.x * 64 + (wave >> 1) * 32;
-    const int n_base = blockIdx.y * 64 + (wave & 1) * 32;
+    const int m_tile = blockIdx.x * 64, n_tile = blockIdx.y * 64;
+    const int m_base = m_tile + (wave >> 1) * 32;
+    const int n_base = n_tile + (wave & 1) * 32;
     const int k_begin = blockIdx.z * g.kchunk;
     const int k_end = min(g.K, k_begin + g.kchunk);
     const int r = lane & 15, kq = (lane >> 4) * 8;
+    const bool split = g.splits > 1;
+    if ((int)blockIdx.z >= g.splits) {
+        // two chunks of the column sums, 128 columns each
+        const int c = 2 * (((int)blockIdx.z - g.splits) * gridDim.x * gridDim.y + blockIdx.y * gridDim.x + blockIdx.x) +
+                      (threadIdx.x >> 7);
+        const int col = threadIdx.x & 127, r0 = c * g.cs.rows_per;
+        if (c < g.cs.chunks && col < g.cs.C)
+            g.cs.part[(int64_t)c * g.cs.C + col] =
+                ordered_sum(g.cs.X + (int64_t)r0 * g.cs.ld + col, g.cs.ld, min(g.cs.R, r0 + g.cs.rows_per) - r0);
+        return;
+    }
     floatx4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = k_begin; k0 < k_end; k0 += 32) {
-        bf16x8 a[2], b[2];
+    if constexpr (AK && BK) {
+#pragma nounroll
+        for (int k0 = k_begin; k0 < k_end; k0 += 64) {
+            bf16x8 a[2][2], b[2][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            a[i] = load_frag(g.A, g.sam, g.sak, m_base + 16 * i + r, g.M, k0 + kq, k_end, g.contigA);
+            for (int u = 0; u < 2; ++u) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            b[j] = load_frag(g.B, g.sbn, g.sbk, n_base + 16 * j + r, g.N, k0 + kq, k_end, g.contigB);
+                for (int i = 0; i < 2; ++i) a[u][i] = row_frag(g.A, g.lda, m_base + 16 * i + r, g.M, k0 + 32 * u + kq, k_end);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+                for (int j = 0; j < 2; ++j) b[u][j] = row_frag(g.B, g.ldb, n_base + 16 * j + r, g.N, k0 + 32 * u + kq, k_end);
+            }
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            for (int u = 0; u < 2; ++u)
+                if (k0 + 32 * u < k_end) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+                }
+        }
+    } else {
+        __shared__ uint16_t ta[64][kTileLd], tb[64][kTileLd];
+        TileLoad<AK> la;
+        TileLoad<BK> lb;
+        la.load(g.A, g.lda, m_tile, g.M, k_begin, k_end);
+        lb.load(g.B, g.ldb, n_tile, g.N, k_begin, k_end);
+#pragma nounroll
+        for (int k0 = k_begin; k0 < k_end; k0 += kTileK) {
+            __syncthreads();
+            la.store(ta);
+            lb.store(tb);
+            __syncthreads();
+            // (past the end: zeros that are not used)
+            la.load(g.A, g.lda, m_tile, g.M, k0 + kTileK, k_end);
+            lb.load(g.B, g.ldb, n_tile, g.N, k0 + kTileK, k_end);
+#pragma unroll
+            for (int kk = 0; kk < kTileK; kk += 32)
+                if (k0 + kk < k_end) {
+                    bf16x8 a[2], b[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) a[i] = tile_frag(ta, (wave >> 1) * 32 + 16 * i + r, kk + kq);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) b[j] = tile_frag(tb, (wave & 1) * 32 + 16 * j + r, kk + kq);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                }
+        }
     }
-    const bool split = gridDim.z > 1;
     float *C32 = g.C32 + (split ? (int64_t)blockIdx.z * g.split_stride : 0);
+    const int mq = m_base + 4 * (lane >> 4);
+    if (!split && g.bias) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float b = g.bias[min(n_base + 16 * j + r, g.N - 1)];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[i][j][q] += b;
+        }
+    }
+    if (!split && g.mask) {
+        float z[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+            z[t] = g.mask[(int64_t)min(mq + 16 * (t >> 3) + (t & 3), g.M - 1) * g.ldmask +
+                          min(n_base + 16 * ((t >> 2) & 1) + r, g.N - 1)];
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+            if (!(z[t] > 0.f)) acc[t >> 3][(t >> 2) & 1][t & 3] = 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int m = m_base + 16 * i + 4 * (lane >> 4) + q;
-                const int n = n_base + 16 * j + r;
+                const int m = mq + 16 * i + q, n = n_base + 16 * j + r;
                 if (m >= g.M || n >= g.N) continue;
-                float v = acc[i][j][q];
-                if (!split) {
-                    if (g.bias) v += g.bias[n];
-                    if (g.mask && !(g.mask[(int64_t)m * g.ldmask + n] > 0.f)) v = 0.f;
-                }
+                const float v = acc[i][j][q];
                 if (C32) C32[(int64_t)m * g.ldc32 + n] = v;
                 if (!split && g.C16) g.C16[(int64_t)m * g.ldc16 + n] = f2bf(g.relu ? fmaxf(v, 0.f) : v);
             }
 }
 
-// out[m][n] (ld ldo) = sum over z = 0 .. S-1 of part[z][m][n] (row length N), in order.
-__global__ __launch_bounds__(256) void k_split_sum(const float *part, int S, int64_t stride, int M, int N,
-                                                   float *out, int64_t ldo)
+// x[0] + x[stride] + .. (count terms) in order, with 16 loads in flight: the sums
+// below are chains whose loads do not depend on each other.
+__device__ __forceinline__ float ordered_sum(const float *x, int64_t stride, int count)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)M * N) return;
     float s = 0.f;
-    for (int z = 0; z < S; ++z) s += part[z * stride + i];
-    out[(i / N) * ldo + i % N] = s;
+    int z = 0;
+    for (; z + 16 <= count; z += 16) {
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = x[(z + j) * stride];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s += v[j];
+    }
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = z + j < count ? x[(z + j) * stride] : 0.f;
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (z + j < count) s += v[j];
+    return s;
 }
 
-// Column sums of X [R][C] (ld ldx): stage 1 writes per-chunk partials [S][C].
-__global__ __launch_bounds__(256) void k_colsum_part(const float *X, int R, int C, int64_t ldx, int rows_per,
-                                                     float *part)
+// The sums of a weight gradient's slices and of its bias gradient's chunks, in
+// order: out[m][n] (ld ldo) = sum over z < S of part[z][m][n] (row length N; S = 1:
+// already in place), then bias[c] = sum over chunks of cpart[chunk][c].
+__global__ __launch_bounds__(256) void k_finish(const float *part, int S, int64_t stride, int M, int N, float *out,
+                                                int64_t ldo, const float *cpart, int chunks, int C, float *bias)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= C) return;
-    const int r0 = blockIdx.y * rows_per, r1 = min(R, r0 + rows_per);
-    float s = 0.f;
-    for (int r = r0; r < r1; ++r) s += X[(int64_t)r * ldx + c];
-    part[(int64_t)blockIdx.y * C + c] = s;
-}
-
-__global__ __launch_bounds__(256) void k_colsum_final(const float *part, int S, int C, float *out)
-{
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= C) return;
-    float s = 0.f;
-    for (int z = 0; z < S; ++z) s += part[(int64_t)z * C + c];
-    out[c] = s;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n = S > 1 ? (int64_t)M * N : 0;
+    if (i < n) out[(i / N) * ldo + i % N] = ordered_sum(part + i, stride, S);
+    else if (i - n < C) bias[i - n] = ordered_sum(cpart + (i - n), C, chunks);
 }
 
 // Node input features into the left half of XC0 [N][2 * kFin] (bf16).
@@ -188,6 +324,26 @@ __global__ __launch_bounds__(256) void k_features(const int32_t *rowp, const flo
     XC0[(int64_t)v * 2 * kFin + f] = f2bf(x);
 }
 
+// s + sum over the row's entries j in [j0, j1) of val[j] x(col[j]), in order, with
+// eight neighbours' values on their way at a time.
+template <typename X>
+__device__ __forceinline__ float neighbour_sum(int j0, int j1, const int32_t *col, const float *val, float s, X x)
+{
+    for (int j = j0; j < j1; j += 8) {
+        float w[8], h[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int i = min(j + k, j1 - 1);
+            w[k] = val[i];
+            h[k] = x(col[i]);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (j + k < j1) s += w[k] * h[k];
+    }
+    return s;
+}
+
 // Messages: XC[v][d + f] = bf16(sum_j val[j] * XC[col[j]][f]) (left half = H, bf16).
 template <int D>
 __global__ __launch_bounds__(256) void k_aggregate(const int32_t *rowp, const int32_t *col, const float *val,
@@ -196,8 +352,8 @@ __global__ __launch_bounds__(256) void k_aggregate(const int32_t *rowp, const in
     constexpr int PER = 256 / D;
     const int v = blockIdx.x * PER + threadIdx.x / D, f = threadIdx.x % D;
     if (v >= N) return;
-    float s = 0.f;
-    for (int j = rowp[v]; j < rowp[v + 1]; ++j) s += val[j] * bf2f(XC[(int64_t)col[j] * 2 * D + f]);
+    const float s = neighbour_sum(rowp[v], rowp[v + 1], col, val, 0.f,
+                                  [&](int u) { return bf2f(XC[(int64_t)u * 2 * D + f]); });
     XC[(int64_t)v * 2 * D + D + f] = f2bf(s);
 }
 
@@ -211,8 +367,8 @@ __global__ __launch_bounds__(256) void k_aggregate_bwd(const int32_t *rowp, cons
     constexpr int PER = 256 / D;
     const int v = blockIdx.x * PER + threadIdx.x / D, f = threadIdx.x % D;
     if (v >= N) return;
-    float s = dXC[(int64_t)v * 2 * D + f];
-    for (int j = rowp[v]; j < rowp[v + 1]; ++j) s += val[j] * dXC[(int64_t)col[j] * 2 * D + D + f];
+    const float s = neighbour_sum(rowp[v], rowp[v + 1], col, val, dXC[(int64_t)v * 2 * D + f],
+                                  [&](int u) { return dXC[(int64_t)u * 2 * D + D + f]; });
     const float d = Zprev[(int64_t)v * kHid + f] > 0.f ? s : 0.f;
     dZ[(int64_t)v * kHid + f] = d;
     dZ16[(int64_t)v * kHid + f] = f2bf(d);
@@ -224,7 +380,14 @@ __global__ __launch_bounds__(kHid) void k_pool(const int32_t *noff, const float 
     const int gi = blockIdx.x, f = threadIdx.x;
     const int v0 = noff[gi], v1 = noff[gi + 1];
     float s = 0.f;
-    for (int v = v0; v < v1; ++v) s += fmaxf(Z3[(int64_t)v * kHid + f], 0.f);
+    for (int v = v0; v < v1; v += 8) {
+        float z[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) z[k] = Z3[(int64_t)min(v + k, v1 - 1) * kHid + f];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (v + k < v1) s += fmaxf(z[k], 0.f);
+    }
     const float m = v1 > v0 ? s / (float)(v1 - v0) : 0.f;
     g[(int64_t)gi * kHid + f] = m;
     g16[(int64_t)gi * kHid + f] = f2bf(m);
@@ -430,9 +593,10 @@ struct qaoa_mpnn_s {
     float *val;
     uint16_t *XC[3];        // [N][2 d_l]
     float *Z[3];            // [N][128]
-    float *g, *Z1, *Y, *dY, *dZ1, *dg, *dZ, *dXC, *part, *loss_sq_f;
+    float *g, *Z1, *Y, *dY, *dZ1, *dg, *dZ, *dXC, *part, *cpart;
     uint16_t *g16, *A1, *dY16, *dZ116, *dZ16;
-    double *gam, *bet, *gt, *bt, *sq, *loss;
+    double *gam, *bet, *gt, *bt, *sq;
+    double *loss = nullptr;  // pinned host memory, written by the kernel that sums it
 };
 
 namespace {
@@ -477,7 +641,7 @@ qaoa_status ensure_ws(qaoa_mpnn m, int G, int N, int E2)
         {(void **)&m->dXC, Nc * 2 * qm::kHid * 4}, {(void **)&m->part, partN * 4},
         {(void **)&m->gam, Gc * m->p * 8}, {(void **)&m->bet, Gc * m->p * 8},
         {(void **)&m->gt, Gc * m->p * 8}, {(void **)&m->bt, Gc * m->p * 8},
-        {(void **)&m->sq, Gc * p2 * 8}, {(void **)&m->loss, 8},
+        {(void **)&m->sq, Gc * p2 * 8}, {(void **)&m->cpart, (size_t)kSplitMax * qm::kHid * 4},
     };
     size_t total = 0;
     for (const Item &it : items) total += align256(it.bytes);
@@ -507,68 +671,102 @@ qaoa_status ensure_ws(qaoa_mpnn m, int G, int N, int E2)
     return QAOA_OK;
 }
 
-// Launch one product; K splits (when > 1) go to m->part and are summed into C32.
-qaoa_status gemm(qaoa_mpnn m, const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk,
-                 int64_t sbn, int M, int N, int K, float *C32, int64_t ldc32, uint16_t *C16 = nullptr,
-                 int64_t ldc16 = 0, const float *bias = nullptr, const float *mask = nullptr,
-                 int64_t ldmask = 0, bool relu = false, int splits = 1)
-{
-    if (M <= 0 || N <= 0) return QAOA_OK;
+// Launch one product.
+struct Product {
     qm::GemmArgs g{};
+    bool ak = false, bk = false;
+    dim3 grid;
+};
+qaoa_status make_product(Product &pr, const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk,
+                         int64_t sbn, int M, int N, int K, int splits)
+{
+    qm::GemmArgs &g = pr.g;
+    pr.ak = sak == 1;
+    pr.bk = sbk == 1;
     g.A = A;
-    g.sam = sam;
-    g.sak = sak;
+    g.lda = pr.ak ? sam : sak;
     g.B = B;
-    g.sbk = sbk;
-    g.sbn = sbn;
+    g.ldb = pr.bk ? sbn : sbk;
     g.M = M;
     g.N = N;
     g.K = K;
-    auto aligned = [](const void *p, int64_t s_outer) {
-        return ((uintptr_t)p % 16 == 0) && (s_outer % 8 == 0);
+    // what the kernels assume: one stride of each operand is 1, the other holds whole
+    // groups of 8 values, and groups are aligned
+    const auto fits8 = [](const void *p, int64_t ld, int len) {
+        return (uintptr_t)p % 16 == 0 && ld % 8 == 0 && (len + 7) / 8 * 8 <= ld;
     };
-    g.contigA = (sak == 1 && aligned(A, sam)) ? 1 : 0;
-    g.contigB = (sbk == 1 && aligned(B, sbn)) ? 1 : 0;
-    const int kblocks = std::max(1, (K + 31) / 32);
+    if (M < 1 || N < 1 || K < 1 || (!pr.ak && sam != 1) || (!pr.bk && sbn != 1) || !fits8(A, g.lda, pr.ak ? K : M) ||
+        !fits8(B, g.ldb, pr.bk ? K : N))
+        return mfail(QAOA_ERR_UNSUPPORTED, "operand layout of a product");
+    const int kblocks = (K + 31) / 32;
     splits = std::max(1, std::min(splits, std::min(kSplitMax, kblocks)));
-    if ((size_t)M * N > (size_t)qm::kHid * 2 * qm::kHid) splits = 1;  // partial buffer bound
     g.kchunk = ((kblocks + splits - 1) / splits) * 32;
-    splits = std::max(1, (K + g.kchunk - 1) / g.kchunk);
-    dim3 grid((M + 63) / 64, (N + 63) / 64, splits);
-    if (splits > 1) {
-        g.C32 = m->part;
-        g.ldc32 = N;
-        g.split_stride = (int64_t)M * N;
-    } else {
-        g.C32 = C32;
-        g.ldc32 = ldc32;
-        g.C16 = C16;
-        g.ldc16 = ldc16;
-        g.bias = bias;
-        g.mask = mask;
-        g.ldmask = ldmask;
-        g.relu = relu ? 1 : 0;
-    }
-    hipLaunchKernelGGL(qm::k_gemm, grid, dim3(256), 0, m->stream, g);
+    g.splits = (K + g.kchunk - 1) / g.kchunk;
+    pr.grid = dim3((M + 63) / 64, (N + 63) / 64, g.splits);
+    return QAOA_OK;
+}
+qaoa_status launch_product(qaoa_mpnn m, const Product &pr)
+{
+    const dim3 block(256);
+    if (pr.ak && pr.bk) hipLaunchKernelGGL((qm::k_gemm<true, true>), pr.grid, block, 0, m->stream, pr.g);
+    else if (pr.ak) hipLaunchKernelGGL((qm::k_gemm<true, false>), pr.grid, block, 0, m->stream, pr.g);
+    else if (pr.bk) hipLaunchKernelGGL((qm::k_gemm<false, true>), pr.grid, block, 0, m->stream, pr.g);
+    else hipLaunchKernelGGL((qm::k_gemm<false, false>), pr.grid, block, 0, m->stream, pr.g);
     MCHECK(m, hipGetLastError());
-    if (splits > 1) {
-        const int64_t tot = (int64_t)M * N;
-        hipLaunchKernelGGL(qm::k_split_sum, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, m->stream,
-                           (const float *)m->part, splits, (int64_t)M * N, M, N, C32, ldc32);
-        MCHECK(m, hipGetLastError());
-    }
     return QAOA_OK;
 }
 
-qaoa_status colsum(qaoa_mpnn m, const float *X, int R, int C, int64_t ldx, float *out)
+qaoa_status gemm(qaoa_mpnn m, const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk,
+                 int64_t sbn, int M, int N, int K, float *C32, int64_t ldc32, uint16_t *C16 = nullptr,
+                 int64_t ldc16 = 0, const float *bias = nullptr, const float *mask = nullptr,
+                 int64_t ldmask = 0, bool relu = false)
 {
-    const int S = std::max(1, std::min(kSplitMax, (R + 127) / 128));
-    const int rows_per = (R + S - 1) / S;
-    hipLaunchKernelGGL(qm::k_colsum_part, dim3((C + 255) / 256, S), dim3(256), 0, m->stream, X, R, C, ldx,
-                       rows_per, m->part);
-    MCHECK(m, hipGetLastError());
-    hipLaunchKernelGGL(qm::k_colsum_final, dim3((C + 255) / 256), dim3(256), 0, m->stream, (const float *)m->part,
-                       S, C, out);
+    Product pr;
+    const qaoa_status st = make_product(pr, A, sam, sak, B, sbk, sbn, M, N, K, 1);
+    if (st != QAOA_OK) return st;
+    qm::GemmArgs &g = pr.g;
+    g.C32 = C32;
+    g.ldc32 = ldc32;
+    g.C16 = C16;
+    g.ldc16 = ldc16;
+    g.bias = bias;
+    g.mask = mask;
+    g.ldmask = ldmask;
+    g.relu = relu ? 1 : 0;
+    return launch_product(m, pr);
+}
+
+// Gradients of a layer's weights, dW[M][N] = dY16^T X (dY16 [K][M], X [K][N], K rows
+// of nodes or graphs), and bias, the column sums of dY, in two launches: the
+// product's K slices with the chunks of the column sums, then the sums of both.
+qaoa_status weight_grad(qaoa_mpnn m, const uint16_t *dY16, const float *dY, int64_t ldy, const uint16_t *X, int64_t ldx,
+                        int M, int N, int K, float *dW, float *dbias, int splits)
+{
+    if ((size_t)M * N > (size_t)qm::kHid * 2 * qm::kHid || M > qm::kHid)
+        return mfail(QAOA_ERR_UNSUPPORTED, "weight gradient larger than its buffers");
+    Product pr;
+    const qaoa_status st = make_product(pr, dY16, 1, ldy, X, ldx, 1, M, N, K, splits);
+    if (st != QAOA_OK) return st;
+    qm::GemmArgs &g = pr.g;
+    const bool split = g.splits > 1;
+    g.C32 = split ? m->part : dW;
+    g.ldc32 = N;
+    g.split_stride = (int64_t)M * N;
+    const int S = std::max(1, std::min(kSplitMax, (K + 127) / 128));
+    g.cs.X = dY;
+    g.cs.R = K;
+    g.cs.C = M;
+    g.cs.ld = ldy;
+    g.cs.rows_per = (K + S - 1) / S;
+    g.cs.chunks = (K + g.cs.rows_per - 1) / g.cs.rows_per;
+    g.cs.part = m->cpart;
+    const int per = 2 * (int)(pr.grid.x * pr.grid.y);
+    pr.grid.z += (g.cs.chunks + per - 1) / per;
+    const qaoa_status s2 = launch_product(m, pr);
+    if (s2 != QAOA_OK) return s2;
+    const int64_t tot = (split ? (int64_t)M * N : 0) + M;
+    hipLaunchKernelGGL(qm::k_finish, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, m->stream, (const float *)m->part,
+                       g.splits, (int64_t)M * N, M, N, dW, (int64_t)N, (const float *)m->cpart, g.cs.chunks, M, dbias);
     MCHECK(m, hipGetLastError());
     return QAOA_OK;
 }
@@ -579,17 +777,21 @@ qaoa_status colsum(qaoa_mpnn m, const float *X, int R, int C, int64_t ldx, float
         if (s_ != QAOA_OK) return s_;         \
     } while (0)
 
-qaoa_status upload_batch(qaoa_mpnn m, const GraphBatch &B)
+// Copies the graphs, and with gt and bt the target angles, to the workspace.
+qaoa_status upload_batch(qaoa_mpnn m, const GraphBatch &B, const double *gt = nullptr, const double *bt = nullptr)
 {
     MTRY(ensure_ws(m, B.G, B.N, B.E2));
-    MCHECK(m, hipMemcpyAsync(m->rowp, B.rowp.data(), (B.N + 1) * 4, hipMemcpyHostToDevice, m->stream));
-    if (B.E2) {
-        MCHECK(m, hipMemcpyAsync(m->col, B.col.data(), (size_t)B.E2 * 4, hipMemcpyHostToDevice, m->stream));
-        MCHECK(m, hipMemcpyAsync(m->val, B.val.data(), (size_t)B.E2 * 4, hipMemcpyHostToDevice, m->stream));
-    }
-    MCHECK(m, hipMemcpyAsync(m->noff, B.noff.data(), (B.G + 1) * 4, hipMemcpyHostToDevice, m->stream));
-    MCHECK(m, hipMemcpyAsync(m->node_graph, B.node_graph.data(), (size_t)B.N * 4, hipMemcpyHostToDevice,
-                             m->stream));
+    const size_t angles = (size_t)B.G * m->p * 8;
+    const struct {
+        void *dst;
+        const void *src;
+        size_t bytes;
+    } items[] = {{m->rowp, B.rowp.data(), ((size_t)B.N + 1) * 4}, {m->col, B.col.data(), (size_t)B.E2 * 4},
+                 {m->val, B.val.data(), (size_t)B.E2 * 4},        {m->noff, B.noff.data(), ((size_t)B.G + 1) * 4},
+                 {m->node_graph, B.node_graph.data(), (size_t)B.N * 4},
+                 {m->gt, gt, gt ? angles : 0},                    {m->bt, bt, bt ? angles : 0}};
+    for (const auto &it : items)
+        if (it.bytes) MCHECK(m, hipMemcpyAsync(it.dst, it.src, it.bytes, hipMemcpyHostToDevice, m->stream));
     return QAOA_OK;
 }
 
@@ -633,14 +835,11 @@ qaoa_status backward(qaoa_mpnn m, const GraphBatch &B)
     const Layout &L = m->lay;
     const int N = B.N, G = B.G, p2 = 2 * m->p;
     // head
-    MTRY(gemm(m, m->dY16, 1, qm::kOutPad, m->A1, qm::kHid, 1, p2, qm::kHid, G, m->grad + L.Wh2, qm::kHid, nullptr,
-              0, nullptr, nullptr, 0, false, 8));
-    MTRY(colsum(m, m->dY, G, p2, qm::kOutPad, m->grad + L.bh2));
+    MTRY(weight_grad(m, m->dY16, m->dY, qm::kOutPad, m->A1, qm::kHid, p2, qm::kHid, G, m->grad + L.Wh2, m->grad + L.bh2, 8));
     MTRY(gemm(m, m->dY16, qm::kOutPad, 1, m->theta16 + L.Wh2, qm::kHid, 1, G, qm::kHid, p2, m->dZ1, qm::kHid,
               m->dZ116, qm::kHid, nullptr, m->Z1, qm::kHid));
-    MTRY(gemm(m, m->dZ116, 1, qm::kHid, m->g16, qm::kHid, 1, qm::kHid, qm::kHid, G, m->grad + L.Wh1, qm::kHid,
-              nullptr, 0, nullptr, nullptr, 0, false, 8));
-    MTRY(colsum(m, m->dZ1, G, qm::kHid, qm::kHid, m->grad + L.bh1));
+    MTRY(weight_grad(m, m->dZ116, m->dZ1, qm::kHid, m->g16, qm::kHid, qm::kHid, qm::kHid, G, m->grad + L.Wh1,
+                     m->grad + L.bh1, 8));
     MTRY(gemm(m, m->dZ116, qm::kHid, 1, m->theta16 + L.Wh1, qm::kHid, 1, G, qm::kHid, qm::kHid, m->dg, qm::kHid));
     // readout and the last layer's ReLU
     hipLaunchKernelGGL(qm::k_unpool, dim3((N + 1) / 2), dim3(256), 0, m->stream, (const int32_t *)m->node_graph,
@@ -649,9 +848,8 @@ qaoa_status backward(qaoa_mpnn m, const GraphBatch &B)
     for (int l = qm::kLayers - 1; l >= 0; --l) {
         const int d = L.din[l];
         const int splits = std::max(1, std::min(kSplitMax, N / 256));
-        MTRY(gemm(m, m->dZ16, 1, qm::kHid, m->XC[l], 2 * d, 1, qm::kHid, 2 * d, N, m->grad + L.W[l], 2 * d, nullptr,
-                  0, nullptr, nullptr, 0, false, splits));
-        MTRY(colsum(m, m->dZ, N, qm::kHid, qm::kHid, m->grad + L.b[l]));
+        MTRY(weight_grad(m, m->dZ16, m->dZ, qm::kHid, m->XC[l], 2 * d, qm::kHid, 2 * d, N, m->grad + L.W[l],
+                         m->grad + L.b[l], splits));
         if (l == 0) break;
         MTRY(gemm(m, m->dZ16, qm::kHid, 1, m->theta16 + L.W[l], 2 * d, 1, N, 2 * d, qm::kHid, m->dXC, 2 * d));
         hipLaunchKernelGGL(qm::k_aggregate_bwd<qm::kHid>, dim3((N + 1) / 2), dim3(256), 0, m->stream,
@@ -662,16 +860,11 @@ qaoa_status backward(qaoa_mpnn m, const GraphBatch &B)
     return QAOA_OK;
 }
 
-// Angles, and with targets the loss and dY; optional host copies of the angles.
-qaoa_status angles_and_loss(qaoa_mpnn m, const GraphBatch &B, const double *gt, const double *bt, double *gamma,
-                            double *beta, double *loss)
+// Angles, and with targets the sum of squared errors (into *m->loss) and dY; optional
+// host copies of the angles.  Only enqueues.
+qaoa_status angles_and_loss(qaoa_mpnn m, const GraphBatch &B, bool tgt, double *gamma, double *beta)
 {
     const int G = B.G, p = m->p;
-    const bool tgt = gt != nullptr;
-    if (tgt) {
-        MCHECK(m, hipMemcpyAsync(m->gt, gt, (size_t)G * p * 8, hipMemcpyHostToDevice, m->stream));
-        MCHECK(m, hipMemcpyAsync(m->bt, bt, (size_t)G * p * 8, hipMemcpyHostToDevice, m->stream));
-    }
     const int tot = G * qm::kOutPad;
     hipLaunchKernelGGL(qm::k_angles, dim3((tot + 255) / 256), dim3(256), 0, m->stream, (const float *)m->Y, G, p,
                        m->gam, m->bet, tgt ? (const double *)m->gt : nullptr,
@@ -685,13 +878,14 @@ qaoa_status angles_and_loss(qaoa_mpnn m, const GraphBatch &B, const double *gt, 
     }
     if (gamma) MCHECK(m, hipMemcpyAsync(gamma, m->gam, (size_t)G * p * 8, hipMemcpyDeviceToHost, m->stream));
     if (beta) MCHECK(m, hipMemcpyAsync(beta, m->bet, (size_t)G * p * 8, hipMemcpyDeviceToHost, m->stream));
-    if (loss && tgt) {
-        double s = 0.0;
-        MCHECK(m, hipMemcpyAsync(&s, m->loss, 8, hipMemcpyDeviceToHost, m->stream));
-        MCHECK(m, hipStreamSynchronize(m->stream));
-        *loss = s / (2.0 * p * G);
-    }
+    return QAOA_OK;
+}
+
+// Waits for the stream; the loss of the step that has run.
+qaoa_status finish(qaoa_mpnn m, const GraphBatch &B, double *loss)
+{
     MCHECK(m, hipStreamSynchronize(m->stream));
+    if (loss) *loss = *m->loss / (2.0 * m->p * B.G);
     return QAOA_OK;
 }
 
@@ -753,7 +947,8 @@ qaoa_status qaoa_mpnn_create(int32_t p, qaoa_mpnn *out)
     const size_t P = (size_t)m->lay.total;
     if (hipMalloc((void **)&m->theta, P * 4) != hipSuccess || hipMalloc((void **)&m->grad, P * 4) != hipSuccess ||
         hipMalloc((void **)&m->am, P * 4) != hipSuccess || hipMalloc((void **)&m->av, P * 4) != hipSuccess ||
-        hipMalloc((void **)&m->theta16, P * 2) != hipSuccess)
+        hipMalloc((void **)&m->theta16, P * 2) != hipSuccess ||
+        hipHostMalloc((void **)&m->loss, sizeof(double), hipHostMallocDefault) != hipSuccess)
         return bad("parameter allocation failed");
     if (hipMemsetAsync(m->theta, 0, P * 4, m->stream) != hipSuccess ||
         hipMemsetAsync(m->grad, 0, P * 4, m->stream) != hipSuccess ||
@@ -772,6 +967,7 @@ qaoa_status qaoa_mpnn_destroy(qaoa_mpnn m)
     if (m->stream) (void)hipStreamSynchronize(m->stream);
     for (void *p : {(void *)m->theta, (void *)m->grad, (void *)m->am, (void *)m->av, (void *)m->theta16, m->ws})
         if (p) (void)hipFree(p);
+    if (m->loss) (void)hipHostFree(m->loss);
     if (m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
     return QAOA_OK;
@@ -816,7 +1012,8 @@ qaoa_status qaoa_mpnn_predict(qaoa_mpnn m, int32_t count, const int32_t *n, cons
     MDevice dg(m->device);
     MTRY(upload_batch(m, B));
     MTRY(forward(m, B));
-    return angles_and_loss(m, B, nullptr, nullptr, gamma, beta, nullptr);
+    MTRY(angles_and_loss(m, B, false, gamma, beta));
+    return finish(m, B, nullptr);
 }
 
 qaoa_status qaoa_mpnn_loss_grad(qaoa_mpnn m, int32_t count, const int32_t *n, const int64_t *edge_offsets,
@@ -828,13 +1025,12 @@ qaoa_status qaoa_mpnn_loss_grad(qaoa_mpnn m, int32_t count, const int32_t *n, co
     GraphBatch B;
     MTRY(build_batch(count, n, edge_offsets, edges, w, B));
     MDevice dg(m->device);
-    MTRY(upload_batch(m, B));
+    MTRY(upload_batch(m, B, gamma_t, beta_t));
     MTRY(forward(m, B));
-    MTRY(angles_and_loss(m, B, gamma_t, beta_t, nullptr, nullptr, loss));
+    MTRY(angles_and_loss(m, B, true, nullptr, nullptr));
     MTRY(backward(m, B));
     if (grad) MCHECK(m, hipMemcpyAsync(grad, m->grad, m->lay.total * 4, hipMemcpyDeviceToHost, m->stream));
-    MCHECK(m, hipStreamSynchronize(m->stream));
-    return QAOA_OK;
+    return finish(m, B, loss);
 }
 
 qaoa_status qaoa_mpnn_train_step(qaoa_mpnn m, int32_t count, const int32_t *n, const int64_t *edge_offsets,
@@ -851,9 +1047,9 @@ qaoa_status qaoa_mpnn_train_step(qaoa_mpnn m, int32_t count, const int32_t *n, c
     GraphBatch B;
     MTRY(build_batch(count, n, edge_offsets, edges, w, B));
     MDevice dg(m->device);
-    MTRY(upload_batch(m, B));
+    MTRY(upload_batch(m, B, gamma_t, beta_t));
     MTRY(forward(m, B));
-    MTRY(angles_and_loss(m, B, gamma_t, beta_t, nullptr, nullptr, loss));
+    MTRY(angles_and_loss(m, B, true, nullptr, nullptr));
     MTRY(backward(m, B));
     const int64_t t = m->step + 1;
     const float c1 = (float)(1.0 - std::pow(o.beta1, (double)t)), c2 = (float)(1.0 - std::pow(o.beta2, (double)t));
@@ -862,7 +1058,7 @@ qaoa_status qaoa_mpnn_train_step(qaoa_mpnn m, int32_t count, const int32_t *n, c
                        (const float *)m->grad, m->am, m->av, m->theta16, P, (float)o.lr, (float)o.beta1,
                        (float)o.beta2, (float)o.eps, c1, c2);
     MCHECK(m, hipGetLastError());
-    MCHECK(m, hipStreamSynchronize(m->stream));
+    MTRY(finish(m, B, loss));
     m->step = t;
     return QAOA_OK;
 }
