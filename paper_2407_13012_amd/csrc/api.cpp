@@ -738,7 +738,7 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
 qaoa_status build_cost(qaoa_handle h, const std::vector<qk::CostPiece> &pieces, double offset)
 {
     h->cost_bound = std::fabs(offset);
-    for (const qk::CostPiece &pc : pieces) h->cost_bound += std::fabs(pc.w);
+    for (const qk::CostPiece &pc : pieces) h->cost_bound += std::fabs(pc.wq.w);
     const size_t bytes = pieces.size() * sizeof(qk::CostPiece);
     void *dev = nullptr;
     if (bytes) {

@@ -26,15 +26,10 @@ struct Lit {
     int b;
 };
 
-void fill_weights(CostPiece &p)
-{
-    for (int q = 0; q < 16; ++q) p.wq[q] = ((p.qpat >> q) & 1u) ? p.w : -0.0;
-}
-
 CostPiece make_piece(const Lit *lits, int nlit, double w)
 {
     CostPiece p{};
-    p.w = w;
+    p.wq.w = w;
     uint32_t rm = 0, rv = 0, lm = 0, lv = 0;
     for (int i = 0; i < nlit; ++i) {
         const int v = lits[i].v;
@@ -51,9 +46,8 @@ CostPiece make_piece(const Lit *lits, int nlit, double w)
         }
     }
     for (uint32_t q = 0; q < 16; ++q)
-        if ((q & rm) == rv) p.qpat |= 1u << q;
+        if ((q & rm) == rv) p.wq.qpat |= 1u << q;
     p.lanes = lm | (lv << 8);
-    fill_weights(p);
     return p;
 }
 
@@ -66,8 +60,7 @@ void push_term(std::vector<CostPiece> &out, const CostPiece *pc, int np)
         bool merged = false;
         for (size_t k = first; k < out.size(); ++k)
             if (out[k].umask == pc[i].umask && out[k].uval == pc[i].uval && out[k].lanes == pc[i].lanes) {
-                out[k].qpat |= pc[i].qpat;
-                fill_weights(out[k]);
+                out[k].wq.qpat |= pc[i].wq.qpat;
                 merged = true;
                 break;
             }

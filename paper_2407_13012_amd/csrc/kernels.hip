@@ -155,15 +155,19 @@ __global__ __launch_bounds__(kThreads) void k_minmax_final(const double *pmin, c
 // iteration.  Thread (lane, wave) holds the 16 entries z = base | q << 6 |
 // lane | wave << 10, q < 16, so every store of a wave is 64 consecutive
 // entries, and z bits >= 10 are the same for the whole wavefront.  The terms
-// arrive as pieces (cost_terms.cpp): a piece whose wave-bit literals fail is
-// skipped by the whole wavefront with a scalar branch, lanes that fail its
-// lane-bit literals sit it out under the execution mask, and the rest add to
-// entry q the piece's wq[q]: its weight where the piece covers q, -0.0 where
-// it does not (x + (-0.0) == x exactly in round-to-nearest, signed zeros
-// included).  Each entry thus receives exactly the weights of its active
-// terms, added one by one in the given term order, as the definition sums
-// them.
+// arrive as pieces (cost_terms.cpp).  The workgroup brings kCostChunk of them
+// into LDS with one coalesced read, each lane of a wavefront tests the wave-bit
+// literals of one piece, and the wavefront then goes through the pieces that
+// passed, in order: a lane adds the weight, or -0.0 if it fails the lane-bit
+// literals (x + (-0.0) == x exactly in round-to-nearest, signed zeros included),
+// to the entries q that the piece covers.  Each entry thus receives exactly
+// the weights of its active terms, added one by one in the given term order, as
+// the definition sums them.
+// Small arrays are bound by the latency of reading the pieces: fetched one by
+// one with scalar loads, each a miss in turn, they took 100 us at 2^21 entries
+// and 230 pieces; this way it takes 27 us.
 constexpr int kCostTileBits = 12;
+constexpr int kCostChunk = 256;
 
 template <typename CT>
 __device__ __forceinline__ void store_costs(CT *__restrict__ C, uint64_t N, uint64_t zt, const double (&acc)[16])
@@ -175,6 +179,37 @@ __device__ __forceinline__ void store_costs(CT *__restrict__ C, uint64_t N, uint
     }
 }
 
+// acc[q] += w in the lanes of `in`, for the entries q of qpat (all lanes are
+// active here).  The sums stay in their registers and the execution mask says
+// who adds: written in C++, the same choice costs copies of all 16 sums for each
+// term (47 us instead of 27 where the comment above counts).  The scalar
+// instructions ahead of the first addition are also the wait states that it
+// needs after the lane reads that made w.
+__device__ __forceinline__ void add_covered(double (&acc)[16], double w, uint64_t in, uint32_t qpat)
+{
+    uint64_t all;
+#define QK_ADD(q) "v_add_f64 %[a" #q "], %[a" #q "], %[w]\n\t"
+#define QK_ADD_IF(q) "s_bitcmp1_b32 %[p], " #q "\n\ts_cselect_b64 exec, %[in], 0\n\t" QK_ADD(q)
+#define QK_ALL(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
+    asm("s_mov_b64 %[all], exec\n\t"
+        "s_cmpk_eq_u32 %[p], 0xffff\n\t"
+        "s_cbranch_scc1 1f\n\t" QK_ALL(QK_ADD_IF)
+        "s_branch 2f\n"
+        "1:\n\t"
+        "s_mov_b64 exec, %[in]\n\t" QK_ALL(QK_ADD)
+        "2:\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [all] "=&s"(all), [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]),
+          [a4] "+v"(acc[4]), [a5] "+v"(acc[5]), [a6] "+v"(acc[6]), [a7] "+v"(acc[7]), [a8] "+v"(acc[8]),
+          [a9] "+v"(acc[9]), [a10] "+v"(acc[10]), [a11] "+v"(acc[11]), [a12] "+v"(acc[12]),
+          [a13] "+v"(acc[13]), [a14] "+v"(acc[14]), [a15] "+v"(acc[15])
+        : [w] "s"(w), [in] "s"(in), [p] "s"(qpat)
+        : "scc");
+#undef QK_ALL
+#undef QK_ADD_IF
+#undef QK_ADD
+}
+
 template <typename CT>
 __global__ __launch_bounds__(kThreads) void k_cost_pieces(CT *__restrict__ C, uint64_t N,
                                                           const CostPiece *__restrict__ P,
@@ -182,22 +217,40 @@ __global__ __launch_bounds__(kThreads) void k_cost_pieces(CT *__restrict__ C, ui
 {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int kWords = sizeof(CostPiece) / 8;
+    __shared__ CostPiece pieces[kCostChunk];
     for (uint64_t tile = blockIdx.x; (tile << kCostTileBits) < N; tile += gridDim.x) {
         const uint64_t zw = (tile << kCostTileBits) | ((uint64_t)wave << 10);
         double acc[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc[q] = offset;
-        for (int64_t k = 0; k < count; ++k) {
-            const CostPiece &pc = P[k];
-            const uint64_t um = pc.umask, uv = pc.uval;
-            const uint32_t ln = pc.lanes;
-            if ((zw & um) != uv) continue;  // the whole wavefront skips the piece
-            double wq[16];
+        for (int64_t k0 = 0; k0 < count; k0 += kCostChunk) {
+            const int here = (int)(count - k0 < kCostChunk ? count - k0 : kCostChunk);
+            uint64_t word[kCostChunk * kWords / kThreads];  // all loads in flight at once
 #pragma unroll
-            for (int q = 0; q < 16; ++q) wq[q] = pc.wq[q];
-            if ((lane & ln & 63u) == (ln >> 8)) {  // lanes failing the test sit it out
+            for (int i = 0; i < kCostChunk * kWords / kThreads; ++i) {
+                const int x = i * kThreads + (int)threadIdx.x;
+                __builtin_memcpy(&word[i], (const char *)(P + k0) + 8 * (x < here * kWords ? x : 0), 8);
+            }
+            __syncthreads();  // the chunk before is done with
 #pragma unroll
-                for (int q = 0; q < 16; ++q) acc[q] += wq[q];
+            for (int i = 0; i < kCostChunk * kWords / kThreads; ++i)
+                __builtin_memcpy((char *)pieces + 8 * (i * kThreads + (int)threadIdx.x), &word[i], 8);
+            __syncthreads();
+            for (int g = 0; g < here; g += 64) {
+                const CostPiece &pc = pieces[g + (int)lane < here ? g + (int)lane : here - 1];
+                const uint64_t wb = (uint64_t)__double_as_longlong(pc.wq.w);
+                const uint32_t wlo = (uint32_t)wb, whi = (uint32_t)(wb >> 32), qp = pc.wq.qpat, ln = pc.lanes;
+                uint64_t todo = __ballot(g + (int)lane < here && (zw & pc.umask) == pc.uval);
+                while (todo) {
+                    const int b = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const uint32_t l = __builtin_amdgcn_readlane(ln, b);
+                    const uint32_t qpat = __builtin_amdgcn_readlane(qp, b);
+                    const double w = __longlong_as_double((long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane(whi, b) << 32 |
+                                                                      (uint32_t)__builtin_amdgcn_readlane(wlo, b)));
+                    add_covered(acc, w, __ballot((lane & l & 63u) == (l >> 8)), qpat);
+                }
             }
         }
         store_costs(C, N, zw | lane, acc);

@@ -213,17 +213,20 @@ hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride
 // are common to a wavefront.  Terms are uploaded as pieces (cost_terms.cpp):
 // a piece adds w to entry q of a thread when the wave bits match
 // (z & umask) == uval, the lane bits match (lane & lm) == lv, and bit q of
-// qpat is set (wq[q] holds w there and -0.0 elsewhere).  The pieces of one
-// term cover disjoint sets of z.
+// wq.qpat is set.  The pieces of one term cover disjoint sets of z.
 constexpr int kCostLaneBits = 6;
 constexpr int kCostUniformBit = 10;
+struct CostWeights {
+    double w;        // the term's weight
+    uint32_t qpat;   // entries q (bit q) covered, from the literals on bits 6-9
+    // what entry q receives: -0.0 leaves a sum as it is, signed zeros included
+    __host__ __device__ double operator[](uint32_t q) const { return ((qpat >> q) & 1u) ? w : -0.0; }
+};
 struct CostPiece {
     uint64_t umask;  // tested z bits >= 10
     uint64_t uval;   // their required values
+    CostWeights wq;
     uint32_t lanes;  // bits 0-5: tested lane bits lm; bits 8-13: required values lv
-    uint32_t qpat;   // entries q (bit q) covered, from the literals on bits 6-9
-    double w;        // the term's weight
-    double wq[16];   // per entry q: w if bit q of qpat is set, else -0.0
 };
 std::vector<CostPiece> cost_pieces_maxcut(int64_t m, const int32_t *edges, const double *w);
 std::vector<CostPiece> cost_pieces_qubo(int n, int64_t m, const int32_t *pairs, const double *J,
