@@ -18,6 +18,8 @@ SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "batch.hip", "
 PASS_SOURCE = os.path.join(HERE, "csrc", "passes.hip")
 QUAD_SOURCE = os.path.join(HERE, "csrc", "quad_pass.hip")
 PASS_VARIANTS = [(real, sp) for real in ("double", "float") for sp in (-1, 0, 2, 3, 4, 5, 6, 7)]
+# and for the large tiles in the classes that their plans have (plan.cpp, plan_large)
+LARGE_VARIANTS = [("double", 0), ("double", 2), ("double", 3), ("float", 0), ("float", 3), ("float", 4)]
 
 
 def units() -> list[tuple[str, list[str], str]]:
@@ -27,6 +29,9 @@ def units() -> list[tuple[str, list[str], str]]:
         tag = f"{'c128' if real == 'double' else 'c64'}_{'rt' if sp < 0 else 's%d' % sp}"
         many = ["-DQK_PASS_MANY=1"] if real == "double" else []
         out.append((PASS_SOURCE, [f"-DQK_PASS_REAL={real}", f"-DQK_PASS_SP={sp}", *many], f"passes_{tag}.o"))
+    for real, sp in LARGE_VARIANTS:
+        tag = f"{'c128' if real == 'double' else 'c64'}_s{sp}"
+        out.append((PASS_SOURCE, [f"-DQK_PASS_REAL={real}", f"-DQK_PASS_SP={sp}", "-DQK_TILE_EXTRA=1"], f"large_{tag}.o"))
     for real in ("double", "float"):
         many = ["-DQK_PASS_MANY=1"] if real == "double" else []
         out.append((QUAD_SOURCE, [f"-DQK_QUAD_REAL={real}", *many], f"quad_{'c128' if real == 'double' else 'c64'}.o"))

@@ -70,9 +70,9 @@ struct qaoa_handle_s {
     size_t res_cap = 0;    // doubles
     hipEvent_t scanned = nullptr;  // sampling: the total mass has been written
     std::vector<qk::Geometry> plan;  // mixer sweeps of one layer (fixed by n and precision)
-    int quad = 0;                    // tile bits of the small-tile sweeps (0: none at this n)
-    std::vector<qk::Geometry> quad_plan;
-    bool on_quad = false;            // the current call's sweeps run on quad_plan (choose_tiles)
+    int near = 0;                    // tile bits of the small- or large-tile sweeps (0: none at this n)
+    std::vector<qk::Geometry> near_plan;
+    bool on_near = false;            // the current call's sweeps run on near_plan (choose_tiles)
     bool state_valid = false;
     std::vector<double> state_angles;  // (gamma, beta) of the current state
     bool poisoned = false;
@@ -163,25 +163,26 @@ inline uint64_t nblocks(int n, bool c64)
     return n <= tb ? 1ull : (1ull << (n - tb));
 }
 // Tiles of the current call's sweeps, and the most any call's sweeps have.
-inline uint64_t nblocks(const qaoa_handle h) { return h->on_quad ? h->M >> h->quad : nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0); }
+inline uint64_t nblocks(const qaoa_handle h) { return h->on_near ? h->M >> h->near : nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0); }
 inline uint64_t max_nblocks(const qaoa_handle h)
 {
-    return std::max(h->quad ? h->M >> h->quad : 0, nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0));
+    return std::max(h->near ? h->M >> h->near : 0, nblocks(h->n, c64(h)) >> (h->fold ? 1 : 0));
 }
-inline const std::vector<qk::Geometry> &plan_of(const qaoa_handle h) { return h->on_quad ? h->quad_plan : h->plan; }
+inline const std::vector<qk::Geometry> &plan_of(const qaoa_handle h) { return h->on_near ? h->near_plan : h->plan; }
 // Factor of the sums over the stored amplitudes.
 inline double sum_scale(const qaoa_handle h) { return h->fold ? 2.0 : 1.0; }
 // Qubits of a plain streaming kernel over the stored entries.
 inline int stored_bits(const qaoa_handle h) { return h->fold ? h->n - 1 : h->n; }
 
 // Sets which plan the sweeps of a call at these angles run on: the small tiles
-// where the state has few of the others (quad_tile_bits), as long as every phase
-// |gamma C| stays in the fast reduction's range, which their kernels assume.
+// where the state has few of the others (quad_tile_bits) or the large ones where
+// they save a sweep (large_tile_bits), as long as every phase |gamma C| stays in
+// the fast reduction's range, which their kernels assume.
 void choose_tiles(qaoa_handle h, int p, const double *gamma)
 {
     double g = 0.0;
     for (int l = 0; l < p; ++l) g = std::max(g, std::fabs(gamma[l]));
-    h->on_quad = h->quad && g * h->cost_bound < qk::near_phase_limit(c64(h));
+    h->on_near = h->near && g * h->cost_bound < qk::near_phase_limit(c64(h));
 }
 
 qaoa_status check_handle(qaoa_handle h)
@@ -404,8 +405,10 @@ qaoa_status run_pass(qaoa_handle h, int mode, const qk::PassArgs &args)
                      : mode == qk::kBwd ? 2 : mode == qk::kFwdFuse ? 3 : 4;
     return timed_launch(h, kind, pass_bytes(h, mode, a),
                         [&] {
-                            return h->on_quad ? qk::launch_quad(mode, c64(h), h->quad, a, nblocks(h), h->stream)
-                                              : qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream);
+                            if (!h->on_near) return qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream);
+                            return h->near > qk::tile_bits(c64(h))
+                                       ? qk::launch_large(mode, c64(h), a, nblocks(h), h->stream)
+                                       : qk::launch_quad(mode, c64(h), h->near, a, nblocks(h), h->stream);
                         });
 }
 
@@ -680,8 +683,10 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
     h->A = h->alloc.alloc ? h->N : h->M;
     try {
         h->plan = geometries(h, qk::plan_passes(n, precision == QAOA_C64));
-        h->quad = qk::quad_tile_bits(n, h->fold ? n - 1 : n, precision == QAOA_C64);
-        if (h->quad) h->quad_plan = geometries(h, qk::plan_quad(n, h->quad));
+        h->near = qk::quad_tile_bits(n, h->fold ? n - 1 : n, precision == QAOA_C64);
+        if (h->near) h->near_plan = geometries(h, qk::plan_quad(n, h->near));
+        else if ((h->near = qk::large_tile_bits(n, precision == QAOA_C64)))
+            h->near_plan = geometries(h, qk::plan_large(n, precision == QAOA_C64));
     } catch (...) {
         delete h;
         return fail(QAOA_ERR_OUT_OF_MEMORY, "host allocation failed");

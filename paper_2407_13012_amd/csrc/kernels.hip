@@ -576,9 +576,8 @@ inline unsigned grid_for(uint64_t N, uint64_t cap = 1ull << 20)
 
 // ------------------------------------------------------------ launchers
 
-int static_spectators(const Geometry &g, bool c64, int mode)
+int static_spectators(const Geometry &g, int TB, int mode)
 {
-    const int TB = tile_bits(c64);
     const uint32_t t = g.tmask;
     if ((int)g.tbits != TB || t == 0) return -1;
     const int S = __builtin_ctz(t);
@@ -592,7 +591,7 @@ int static_spectators(const Geometry &g, bool c64, int mode)
 // any other pass runs the kernels that read the target mask at run time.
 hipError_t launch_pass(int mode, bool c64, const PassArgs &a, uint64_t nblocks, hipStream_t s)
 {
-    int sp = static_spectators(a.geo, c64, mode);
+    int sp = static_spectators(a.geo, tile_bits(c64), mode);
     // a class's kernels fix whether their accesses stream, and take every phase
     // argument in the fast reduction's range
     if (sp >= 0 && stream_class(sp) != ((a.flags & kStream) != 0)) sp = -1;
@@ -629,7 +628,7 @@ hipError_t launch_quad(int mode, bool c64, int tbits, const PassArgs &a, uint64_
 hipError_t launch_many(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
                        hipStream_t s)
 {
-    int sp = static_spectators(a.geo, false, mode);
+    int sp = static_spectators(a.geo, kTileBits, mode);
     if (sp >= 0 && stream_class(sp) != ((a.flags & kStream) != 0)) sp = -1;
     switch (sp) {
     case 0: return launch_many_sp<0>(mode, a, m, nblocks, count, s);
@@ -641,6 +640,26 @@ hipError_t launch_many(int mode, const PassArgs &a, const ManyArgs &m, uint64_t 
     case 7: return launch_many_sp<7>(mode, a, m, nblocks, count, s);
     default: return launch_many_sp<-1>(mode, a, m, nblocks, count, s);
     }
+}
+
+hipError_t launch_large(int mode, bool c64, const PassArgs &a, uint64_t nblocks, hipStream_t s)
+{
+    const int sp = static_spectators(a.geo, tile_bits(c64) + 1, mode);
+    if (sp < 0 || stream_class(sp) != ((a.flags & kStream) != 0) || (a.flags & kFarPhase)) return hipErrorInvalidValue;
+    if (!c64) {
+        switch (sp) {
+        case 0: return launch_large_sp<double, 0>(mode, a, nblocks, s);
+        case 2: return launch_large_sp<double, 2>(mode, a, nblocks, s);
+        case 3: return launch_large_sp<double, 3>(mode, a, nblocks, s);
+        }
+        return hipErrorInvalidValue;
+    }
+    switch (sp) {
+    case 0: return launch_large_sp<float, 0>(mode, a, nblocks, s);
+    case 3: return launch_large_sp<float, 3>(mode, a, nblocks, s);
+    case 4: return launch_large_sp<float, 4>(mode, a, nblocks, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots, double scale,

@@ -14,6 +14,9 @@
 // code itself (load, phase, rotations, transposes, reductions, stores) is in
 // tile_device.h; the kernels and the host launcher of each translation unit
 // are its own.
+//
+// With QK_TILE_EXTRA = 1 the kernels are those of the large tiles, of twice the
+// amplitudes (plan.cpp, large_tile_bits), for the classes that their plans have.
 #include "many_device.h"
 
 #ifndef QK_PASS_REAL
@@ -24,6 +27,12 @@
 #endif
 #ifndef QK_PASS_MANY  // 1 in the complex128 units: with the sweeps of the batched engine
 #define QK_PASS_MANY 0
+#endif
+
+#if QK_TILE_EXTRA
+#define QK_LAUNCH_PASS launch_large_sp
+#else
+#define QK_LAUNCH_PASS launch_pass_sp
 #endif
 
 namespace qk {
@@ -428,7 +437,7 @@ void launch_fuse(const PassArgs &a, dim3 grid, hipStream_t s)
 }  // namespace
 
 template <typename R, int SP>
-hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s)
+hipError_t QK_LAUNCH_PASS(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s)
 {
     const dim3 grid((unsigned)nblocks);
     if (mode == kFwdFuse) {
@@ -437,7 +446,7 @@ hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStre
         launch_fuse<R, kBwdFuse, SP>(a, grid, s);
     } else if (mode == kTurnPhase) {
         // the one-pass turn (n <= TB): its tile holds every qubit, no spectators
-        if constexpr (SP > 0) return hipErrorInvalidValue;
+        if constexpr (SP > 0 || QK_TILE_EXTRA) return hipErrorInvalidValue;
         else {
             const dim3 block(Tr<R>::NT);
             if (a.tan_mode) hipLaunchKernelGGL((k_pass<R, kTurnPhase, true, SP>), grid, block, 0, s, a);
@@ -451,7 +460,7 @@ hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStre
     return hipGetLastError();
 }
 
-template hipError_t launch_pass_sp<QK_PASS_REAL, QK_PASS_SP>(int, const PassArgs &, uint64_t, hipStream_t);
+template hipError_t QK_LAUNCH_PASS<QK_PASS_REAL, QK_PASS_SP>(int, const PassArgs &, uint64_t, hipStream_t);
 
 #if QK_PASS_MANY
 // The kernel choice of launch_single / launch_fuse for many instances.

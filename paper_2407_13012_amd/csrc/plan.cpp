@@ -74,13 +74,10 @@ bool plan_ok(int n, int TB, const std::vector<PassPlan> &pl)
 
 }  // namespace
 
-std::vector<PassPlan> plan_passes(int n, bool c64, int kmax)
+// Plan on tiles of 2^TB amplitudes.
+static std::vector<PassPlan> plan_tiles(int n, bool c64, int TB, int kmax)
 {
-    const int TB = tile_bits(c64);
     if (n <= TB) return {{low_mask(n), low_mask(n)}};
-    if (kmax < 1) kmax = 1;
-    // >= TB - 10 spectator bits: runs of >= 4 (16-byte) or >= 8 (8-byte) amplitudes
-    if (kmax > 10) kmax = 10;
     const int page = c64 ? 18 : 17;
     const int r = n - TB, P1 = (r + kmax - 1) / kmax;
     std::vector<int> k(P1 + 1), x(P1 + 1, 0), cap(P1 + 1);
@@ -122,6 +119,34 @@ std::vector<PassPlan> plan_passes(int n, bool c64, int kmax)
     }
     if (!plan_ok(n, TB, out)) out = plan_simple(n, TB, kmax);
     return out;
+}
+
+std::vector<PassPlan> plan_passes(int n, bool c64, int kmax)
+{
+    // >= TB - 10 spectator bits: runs of >= 4 (16-byte) or >= 8 (8-byte) amplitudes
+    return plan_tiles(n, c64, tile_bits(c64), std::min(std::max(kmax, 1), 10));
+}
+
+// Tiles of twice the size where two groups of qubits then make a layer instead of
+// three, that is one sweep less per layer and direction of two: n = 23 and 24
+// (complex64 24 and 25).  One workgroup fills the LDS of a CU, so its loads, its
+// arithmetic and its stores have less beside them to hide in: a sweep takes longer
+// per byte (a complex128 backward layer-boundary sweep 3.3 instead of 4.7 TB/s:
+// the CUs load, compute and store at the same time), and where no sweep is saved
+// the smaller tiles are better.  E + G, p = 4, smaller and large tiles, us:
+// complex128 MaxCut n = 23 692 and 540, 24 1340 and 1030, QUBO n = 24 2610 and
+// 2056; complex64 MaxCut n = 25 1443 and 1159, QUBO n = 25 2806 and 2276; states
+// alone gain as much (n = 25, complex64: 1024 and 869).
+int large_tile_bits(int n, bool c64)
+{
+    const int tb = tile_bits(c64), most = tb + 1 - (c64 ? 3 : 2);  // targets above runs of 64 bytes
+    return n - tb > 10 && n - (tb + 1) <= most ? tb + 1 : 0;
+}
+
+std::vector<PassPlan> plan_large(int n, bool c64)
+{
+    const int TB = tile_bits(c64) + 1;
+    return plan_tiles(n, c64, TB, TB - (c64 ? 3 : 2));
 }
 
 // Two sweeps per layer: the low M bits, then the n - M others over at least 2

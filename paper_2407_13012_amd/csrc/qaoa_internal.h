@@ -89,6 +89,10 @@ std::vector<PassPlan> plan_passes(int n, bool c64, int kmax = 10);
 // stored as 2^stored_bits amplitudes (0: the tiles above), and their plan.
 int quad_tile_bits(int n, int stored_bits, bool c64);
 std::vector<PassPlan> plan_quad(int n, int tile_bits);
+// States of which larger tiles save a sweep (passes.hip with QK_TILE_EXTRA): tile
+// bits (0: the tiles above), and their plan.
+int large_tile_bits(int n, bool c64);
+std::vector<PassPlan> plan_large(int n, bool c64);
 // Kernel geometry of a plan entry; returns false if it needs more runs than supported.
 bool make_geometry(int n, const PassPlan &pp, Geometry *g);
 // Whether a state on n qubits is kept folded.  A cut does not change when every
@@ -176,6 +180,10 @@ hipError_t launch_pass(int mode, bool c64, const PassArgs &a, uint64_t nblocks, 
 // kernels that read the target mask at run time.
 template <typename R, int SP>
 hipError_t launch_pass_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s);
+// The passes of a plan_large plan (phases within the fast reduction's range).
+hipError_t launch_large(int mode, bool c64, const PassArgs &a, uint64_t nblocks, hipStream_t s);
+template <typename R, int SP>
+hipError_t launch_large_sp(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s);
 // The same passes over `count` complex128 instances of one size (batched engine).
 // Instance y's vectors start y * stride entries after those of PassArgs, its
 // partials y * tiles doubles after, its angles are coef[y * p + layer]: `layer`
@@ -198,8 +206,8 @@ hipError_t launch_many_quad(int mode, int tbits, const PassArgs &a, const ManyAr
 template <int SP>
 hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64_t nblocks, unsigned count,
                           hipStream_t s);
-// Spectator class of a pass with kernels of its own (0 or 2..7), else -1.
-int static_spectators(const Geometry &g, bool c64, int mode);
+// Spectator class of a pass on tiles of TB bits with kernels of its own (0 or 2..7), else -1.
+int static_spectators(const Geometry &g, int TB, int mode);
 // out[k] = scale * (sum of slot k); scale 2 for the half sums of a folded state.
 // The passes of a plan_quad plan (phases within the fast reduction's range).
 hipError_t launch_quad(int mode, bool c64, int tbits, const PassArgs &a, uint64_t nblocks, hipStream_t s);

@@ -8,6 +8,10 @@
 
 #include <type_traits>
 
+#ifndef QK_TILE_EXTRA  // 1 in the units of the large tiles: one bit more per tile
+#define QK_TILE_EXTRA 0
+#endif
+
 namespace qk {
 namespace {
 
@@ -15,23 +19,24 @@ template <typename R>
 struct Tr;
 // Amplitude type, cost-entry type and tile shape per precision: 2^TB
 // amplitudes per workgroup of NT = 2^(TB-4) threads (NW = 2^WB waves of 64),
-// NR = 16 amplitudes per thread.
+// NR = 16 amplitudes per thread.  A large tile has twice the threads, and as
+// its LDS leaves room for one workgroup per CU, the same waves per SIMD.
 template <>
 struct Tr<double> {
     using V = double2;
     using CT = double;
-    static constexpr int TB = kTileBits;
+    static constexpr int TB = kTileBits + QK_TILE_EXTRA;
     static constexpr int WB = TB - 10;
     static constexpr int NW = 1 << WB;
     static constexpr int NT = 64 * NW;
     static constexpr int NR = 16;
-    static constexpr int MINW = 2;  // waves per SIMD the pass kernels must allow (two workgroups per CU)
+    static constexpr int MINW = 2;  // waves per SIMD the pass kernels must allow (two workgroups per CU, one on large tiles)
 };
 template <>
 struct Tr<float> {
     using V = float2;
     using CT = float;
-    static constexpr int TB = kTileBits64;
+    static constexpr int TB = kTileBits64 + QK_TILE_EXTRA;
     static constexpr int WB = TB - 10;
     static constexpr int NW = 1 << WB;
     static constexpr int NT = 64 * NW;
@@ -75,12 +80,12 @@ __device__ __forceinline__ void stnt(float2 v, float2 *p)
 // ------------------------------------------------------------ tile geometry
 
 // LDS slot of tile element e: one padding slot after every 16 elements, and 8
-// more before the upper half of a 13-bit tile.  In all three arrangements any
+// more after every 4096.  In all three arrangements any
 // 16 consecutive lanes then hit distinct banks, and the slot is additive over
 // the thread part and the register part of e, so every access is one base
 // register plus an immediate offset.
 template <typename R>
-constexpr int kLdsSlots = (1 << Tr<R>::TB) + (1 << Tr<R>::TB) / 16 + 8 * ((1 << Tr<R>::TB) >> 13);
+constexpr int kLdsSlots = (1 << Tr<R>::TB) + (1 << Tr<R>::TB) / 16 + 8 * (((1 << Tr<R>::TB) >> 12) - 1);
 // The workgroup's LDS: the padded transpose slots plus room for the per-wave
 // partial sums of the block reduction (4 values x NW waves of doubles).
 template <typename R>
@@ -88,25 +93,29 @@ constexpr int kLdsTotal = kLdsSlots<R> + (int)(4 * Tr<R>::NW * sizeof(double) / 
 template <int WB>
 __host__ __device__ __forceinline__ constexpr uint32_t lds_slot(uint32_t e)
 {
-    return e + (e >> 4) + (WB == 3 ? ((e >> 12) << 3) : 0u);
+    return e + (e >> 4) + (WB >= 3 ? ((e >> 12) << 3) : 0u);
 }
 
 // Register arrangements of a tile of 2^(10+WB) elements (lane: 6 bits,
-// register index: 4 bits, wave: WB = 2 or 3 bits).  With WB = 2:
+// register index: 4 bits, wave: WB = 2, 3 or 4 bits).  With WB = 2:
 //   A: lane = bits 0-5,      reg = bits 6-9,         wave = bits 10-11
 //   B: reg = bits 0-3,       lane = bits 4-9,        wave = bits 10-11
 //   C: lane = bits 0-3,6,7,  reg = bits 4,5,10,11,   wave = bits 8-9
 // With WB = 3 the extra tile bit 12 is the top wave bit in A and C, and lane
 // bit 1 in B (where the lanes hold bits 4, 12, 5-8 and the waves bits 9-11):
 // it is never a register bit, and its rotation pairs lanes l and l ^ 2 in B,
-// which a DPP quad permutation reaches without LDS traffic.
+// which a DPP quad permutation reaches without LDS traffic.  With WB = 4 tile
+// bit 13 is one more wave bit in A and C and lane bit 0 in B (where the lanes
+// hold bits 13, 12, 4-7 and the waves bits 8-11), paired in the same way.
 template <int ARR, int WB>
 __host__ __device__ __forceinline__ constexpr uint32_t elem(uint32_t lane, uint32_t wave,
                                                             uint32_t r)
 {
     return ARR == 0   ? (lane | (r << 6) | (wave << 10))
-           : ARR == 1 ? (WB == 2 ? (r | (lane << 4) | (wave << 10))
-                                 : (r | ((lane & 1u) << 4) | (((lane >> 1) & 1u) << 12) | ((lane >> 2) << 5) |
+           : ARR == 1 ? (WB == 2   ? (r | (lane << 4) | (wave << 10))
+                         : WB == 4 ? (r | ((lane & 1u) << 13) | (((lane >> 1) & 1u) << 12) | ((lane >> 2) << 4) |
+                                      (wave << 8))
+                                   : (r | ((lane & 1u) << 4) | (((lane >> 1) & 1u) << 12) | ((lane >> 2) << 5) |
                                     (wave << 9)))
            : WB == 2 ? ((lane & 15u) | ((r & 3u) << 4) | ((lane >> 4) << 6) | (wave << 8) | ((r >> 2) << 10))
                      : ((lane & 15u) | ((r & 3u) << 4) | ((lane >> 4) << 6) | ((wave & 3u) << 8) |
@@ -121,11 +130,11 @@ __host__ __device__ constexpr uint32_t regbit(int q)
 }
 
 // Tile bits rotated while the tile is in arrangement ARR (each tile bit once):
-// the register bits, plus in B the lane-held bit 12 of 13-bit tiles.
+// the register bits, plus in B the lane-held bits 12 and 13 of larger tiles.
 template <int ARR, int WB>
 __host__ __device__ constexpr uint32_t owned()
 {
-    return ARR == 0 ? (15u << 6) : ARR == 1 ? (15u | (WB == 3 ? 1u << 12 : 0u)) : ((3u << 4) | (3u << 10));
+    return ARR == 0 ? (15u << 6) : ARR == 1 ? (15u | (WB >= 3 ? 1u << 12 : 0u) | (WB == 4 ? 1u << 13 : 0u)) : ((3u << 4) | (3u << 10));
 }
 
 // Offset of register r in arrangement ARR (the part of an amplitude's global
@@ -376,25 +385,32 @@ __device__ __forceinline__ void bfly(V &a, V &b, R m)
     }
 }
 
-// Wave bits of a tile of amplitudes of type V (2 for complex128, 3 for complex64).
+// Wave bits of a tile of amplitudes of type V.
 template <typename V>
-constexpr int kWaveBits = 2;
-template <>
-constexpr int kWaveBits<float2> = 3;
+constexpr int kWaveBits = Tr<std::conditional_t<std::is_same<V, float2>::value, float, double>>::WB;
 
-// Amplitude held by lane l ^ 2 (the partner across tile bit 12 in arrangement
-// B of a 13-bit tile): a DPP quad permutation [2, 3, 0, 1].
-__device__ __forceinline__ float lane_xor2(float v)
+// Amplitude held by the lane that differs in tile bit BIT (12 or 13) in
+// arrangement B: lane l ^ 2 or l ^ 1, a DPP quad permutation.
+template <int BIT>
+__device__ __forceinline__ int lane_dword(int v)
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
+    return __builtin_amdgcn_update_dpp(0, v, BIT == 12 ? 0x4E : 0xB1, 0xF, 0xF, true);
 }
-template <typename V>
-__device__ __forceinline__ V lane_partner(V v)
+template <int BIT>
+__device__ __forceinline__ float2 lane_partner(float2 v)
 {
-    V o;
-    o.x = lane_xor2(v.x);
-    o.y = lane_xor2(v.y);
-    return o;
+    return make_float2(__builtin_bit_cast(float, lane_dword<BIT>(__builtin_bit_cast(int, v.x))),
+                       __builtin_bit_cast(float, lane_dword<BIT>(__builtin_bit_cast(int, v.y))));
+}
+template <int BIT>
+__device__ __forceinline__ double lane_double(double v)
+{
+    return __hiloint2double(lane_dword<BIT>(__double2hiint(v)), lane_dword<BIT>(__double2loint(v)));
+}
+template <int BIT>
+__device__ __forceinline__ double2 lane_partner(double2 v)
+{
+    return make_double2(lane_double<BIT>(v.x), lane_double<BIT>(v.y));
 }
 
 // The factored rotation of bfly() across lanes: both members of a pair get the
@@ -427,7 +443,7 @@ struct Targets {
 };
 
 // Rotations of the target bits among the register bits of arrangement ARR
-// (and, for 13-bit tiles in B, the lane-held bit 12).  Each register bit's
+// (and, in B, the lane-held bits).  Each register bit's
 // stage runs under a wave-uniform branch.  The butterflies leave their
 // results in new registers, and the values must sit in the same registers
 // wherever the taken and the skipped path meet; with SKIP_COPY an empty asm
@@ -438,6 +454,14 @@ struct Targets {
 // applied to complex128 tiles only (complex64 forward passes measured 11 %
 // slower with it) and not in kernels that hold a second vector beside v,
 // where it raises the register count past the kernel's budget.
+template <int BIT, bool TM, int SP, typename V, typename R>
+__device__ __forceinline__ void mix_lanes(V (&v)[16], R m, Targets<SP> tg)
+{
+    if (tg.has(BIT)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bfly_lane<TM>(v[r], lane_partner<BIT>(v[r]), m);
+    }
+}
 template <int ARR, bool TM, bool SKIP_COPY = false, int SP, typename V, typename R>
 __device__ __forceinline__ void mix_stage(V (&v)[16], R m, Targets<SP> tg)
 {
@@ -453,19 +477,33 @@ __device__ __forceinline__ void mix_stage(V (&v)[16], R m, Targets<SP> tg)
             for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(v[r].x), "+v"(v[r].y));
         }
     }
-    if constexpr (ARR == 1 && WB == 3) {
-        if (tg.has(12)) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) bfly_lane<TM>(v[r], lane_partner(v[r]), m);
-        }
-    }
+    if constexpr (ARR == 1 && WB >= 3) mix_lanes<12, TM>(v, m, tg);
+    if constexpr (ARR == 1 && WB == 4) mix_lanes<13, TM>(v, m, tg);
 }
 
 // Adjoint stage: for each target bit, add Im<lam|X_j|phi> over the register
 // pairs (weighted by sig2, the squared factor both vectors still miss), then
-// apply the factored inverse rotation to both.  Across lanes (tile bit 12 of
-// 13-bit tiles, arrangement B) each lane adds Im(conj(lam) phi_partner); the
-// two lanes of a pair together give the pair's term.
+// apply the factored inverse rotation to both.  Across lanes (tile bits 12 and
+// 13, arrangement B) each lane adds Im(conj(lam) phi_partner); the two lanes of
+// a pair together give the pair's term.
+template <int BIT, bool TM, int SP, typename V, typename R>
+__device__ __forceinline__ void adj_lanes(V (&f)[16], V (&l)[16], R m, Targets<SP> tg, double &sig2, double f2,
+                                          double &accB)
+{
+    if (tg.has(BIT)) {
+        typename PairSum<V>::T ps = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const V fp = lane_partner<BIT>(f[r]), lp = lane_partner<BIT>(l[r]);
+            ps = imcx_acc(l[r], fp, ps);
+            bfly_lane<TM>(l[r], lp, m);
+            bfly_lane<TM>(f[r], fp, m);
+        }
+        accB = fma(sig2, (double)ps, accB);
+        asm volatile("" : "+v"(accB));
+        sig2 *= f2;
+    }
+}
 template <int ARR, bool TM, int SP, typename V, typename R>
 __device__ __forceinline__ void adj_stage(V (&f)[16], V (&l)[16], R m, Targets<SP> tg,
                                           double &sig2, double f2, double &accB)
@@ -495,25 +533,22 @@ __device__ __forceinline__ void adj_stage(V (&f)[16], V (&l)[16], R m, Targets<S
                 }
         }
     }
-    if constexpr (ARR == 1 && WB == 3) {
-        if (tg.has(12)) {
-            typename PairSum<V>::T ps = 0;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const V fp = lane_partner(f[r]), lp = lane_partner(l[r]);
-                ps = imcx_acc(l[r], fp, ps);
-                bfly_lane<TM>(l[r], lp, m);
-                bfly_lane<TM>(f[r], fp, m);
-            }
-            accB = fma(sig2, (double)ps, accB);
-            asm volatile("" : "+v"(accB));
-            sig2 *= f2;
-        }
-    }
+    if constexpr (ARR == 1 && WB >= 3) adj_lanes<12, TM>(f, l, m, tg, sig2, f2, accB);
+    if constexpr (ARR == 1 && WB == 4) adj_lanes<13, TM>(f, l, m, tg, sig2, f2, accB);
 }
 
 // Sum over the target bits owned by arrangement ARR of Im<lam|X_j|phi> on the
 // register (and lane) pairs, times w (the product of the factors both vectors miss).
+template <int BIT, int SP, typename V>
+__device__ __forceinline__ void beta_lanes(const V (&f)[16], const V (&l)[16], Targets<SP> tg, double &ps)
+{
+    if (tg.has(BIT)) {
+        typename PairSum<V>::T pq = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pq = imcx_acc(l[r], lane_partner<BIT>(f[r]), pq);
+        ps += (double)pq;
+    }
+}
 template <int ARR, int SP, typename V>
 __device__ __forceinline__ void beta_terms(const V (&f)[16], const V (&l)[16], Targets<SP> tg,
                                            double w, double &accB)
@@ -537,14 +572,8 @@ __device__ __forceinline__ void beta_terms(const V (&f)[16], const V (&l)[16], T
             else ps += (double)pq;
         }
     }
-    if constexpr (ARR == 1 && WB == 3) {
-        if (tg.has(12)) {
-            PS pq = 0;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) pq = imcx_acc(l[r], lane_partner(f[r]), pq);
-            ps += (double)pq;
-        }
-    }
+    if constexpr (ARR == 1 && WB >= 3) beta_lanes<12>(f, l, tg, ps);
+    if constexpr (ARR == 1 && WB == 4) beta_lanes<13>(f, l, tg, ps);
     accB = fma(w, ps, accB);
     asm volatile("" : "+v"(accB));
 }
@@ -739,7 +768,7 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
     // Two-vector passes of complex64 tiles (16 waves per CU, 128 registers)
     // load the cost entries where they are used, which keeps them out of the
     // register budget of the rotations; the other waves cover the latency.
-    constexpr bool kLateCost = Tr<R>::NW == 8 && (MODE == kBwd || MODE == kBwdFuse);
+    constexpr bool kLateCost = sizeof(R) == 4 && (MODE == kBwd || MODE == kBwdFuse);
     CT cin[NR], cv[NR];
     if (phaseIn) {
 #pragma unroll
@@ -773,7 +802,7 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
         }
         // complex128 turn: the loaded tile (the state before the group, in
         // arrangement A) stays in registers for the terms of A's bits at the end
-        constexpr bool kKeep0 = MODE == kTurn && WB == 2;
+        constexpr bool kKeep0 = MODE == kTurn && sizeof(R) == 8;
         V v0[kKeep0 ? NR : 1];
         if constexpr (kKeep0) {
 #pragma unroll

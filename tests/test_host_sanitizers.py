@@ -62,6 +62,15 @@ def test_small_tiles_under_sanitizers(tmp_path):
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM_INCLUDE),
                     reason="needs g++ and the HIP headers")
+def test_large_tiles_under_sanitizers(tmp_path):
+    out = _build_and_run(tmp_path, "large_check",
+                         [os.path.join(HOST, "large_check.cpp"), os.path.join(CSRC, "plan.cpp")],
+                         ["-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE])
+    assert "large tiles ok (4)" in out
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM_INCLUDE),
+                    reason="needs g++ and the HIP headers")
 def test_cost_pieces_under_sanitizers(tmp_path):
     out = _build_and_run(tmp_path, "cost_pieces_check",
                          [os.path.join(HOST, "cost_pieces_check.cpp"), os.path.join(CSRC, "cost_terms.cpp")],
