@@ -293,7 +293,8 @@ qaoa_status qaoa_profile_read(qaoa_handle h, int32_t kind, int64_t *launches, do
  * rotates the qubits in target_bits[i]; the remaining tile bits are low
  * spectator bits kept for contiguous memory access (runs of >= 64 bytes).
  * (MaxCut handles run half of the tiles, see qaoa_create_maxcut; states of up
- * to 16 MiB take smaller tiles, in two sweeps per layer.)
+ * to 16 MiB take smaller tiles, and n = 23, 24 (QAOA_C64: 24, 25) larger ones,
+ * in two sweeps per layer.)
  *   cap       capacity of the two output arrays
  *   npasses   receives the number of sweeps per layer
  * Errors: INVALID_ARGUMENT for n outside [1, QAOA_MAX_QUBITS], an unknown
