@@ -359,8 +359,10 @@ double pass_bytes(qaoa_handle h, int mode, const qk::PassArgs &a)
                     ((a.flags & (qk::kPhaseIn | qk::kEOut)) ? c : 0));
     if (mode == qk::kTurn || mode == qk::kTurnPhase) return N * ((initd ? 0 : s) + c + (store ? s : 0));
     if (mode == qk::kFwdFuse) return N * (2 * s + c);
-    if (mode == qk::kBwdFuse) return N * (4 * s + c);
-    return N * (2 * s + (store ? 2 * s : 0) + ((a.flags & qk::kPhaseOut) ? c : 0));
+    if (mode == qk::kBwdFirst) return N * (s + c);
+    const double phi = (a.flags & qk::kNoPhi) ? 0 : s;
+    if (mode == qk::kBwdFuse) return N * (3 * s + phi + c);
+    return N * (2 * s + (store ? s + phi : 0) + ((a.flags & qk::kPhaseOut) ? c : 0));
 }
 
 qaoa_status take_event(qaoa_handle h, hipEvent_t *ev)
@@ -402,7 +404,7 @@ qaoa_status run_pass(qaoa_handle h, int mode, const qk::PassArgs &args)
         a.flags |= qk::kFarPhase;
     // reported kinds: 0 forward, 1 turn, 2 backward, 3 / 4 layer-boundary forward / backward
     const int kind = mode == qk::kFwd ? 0 : (mode == qk::kTurn || mode == qk::kTurnPhase) ? 1
-                     : mode == qk::kBwd ? 2 : mode == qk::kFwdFuse ? 3 : 4;
+                     : (mode == qk::kBwd || mode == qk::kBwdFirst) ? 2 : mode == qk::kFwdFuse ? 3 : 4;
     return timed_launch(h, kind, pass_bytes(h, mode, a),
                         [&] {
                             if (!h->on_near) return qk::launch_pass(mode, c64(h), a, nblocks(h), h->stream);
@@ -481,6 +483,13 @@ struct Slots {
     double *G(int l) const { return parts + (uint64_t)(1 + p + l) * T; }
 };
 
+// Whether the last backward sweep makes phi from the cost entries (kBwdFirst): its
+// kernels are those of the memory-bound tiles.
+bool makes_first(qaoa_handle h)
+{
+    return plan_of(h).size() > 1 && !(h->on_near && h->near <= qk::tile_bits(c64(h)));
+}
+
 // Backward sweep after the last group of layer p-1 has been undone (by the
 // turn pass or by the first pass of a reverse sweep from a stored state): each
 // layer undoes its groups in the reverse of the forward order; a layer's first
@@ -496,6 +505,7 @@ qaoa_status enqueue_backward(qaoa_handle h, int p, const double *gamma, const do
 {
     const std::vector<qk::Geometry> &G = plan_of(h);
     const int P = (int)G.size();
+    const bool first = makes_first(h);
     for (int l = p - 1; l >= 0; --l) {
         for (int j = 0; j < P; ++j) {
             const int idx = P - 1 - j;
@@ -516,8 +526,10 @@ qaoa_status enqueue_backward(qaoa_handle h, int p, const double *gamma, const do
                 } else {
                     a.flags |= qk::kPhaseOut;
                     if (l == 0) a.flags |= qk::kNoStore;
+                    if (first && l == 0) mode = qk::kBwdFirst;
                 }
             }
+            if (first && (P > 2 ? l == 0 && idx == 1 : l == 1 && idx == 0)) a.flags |= qk::kNoPhi;
             qaoa_status st = run_pass(h, mode, a);
             if (st != QAOA_OK) return st;
         }
@@ -595,6 +607,7 @@ qaoa_status enqueue_reverse(qaoa_handle h, int p, const double *gamma, const dou
         a.part_g = sl.G(l);
         if (l == 0) a.flags |= qk::kNoStore;
     }
+    if (P == 2 && p == 1 && makes_first(h)) a.flags |= qk::kNoPhi;
     qaoa_status st = run_pass(h, qk::kBwd, a);
     if (st != QAOA_OK) return st;
     return enqueue_backward(h, p, gamma, beta, lam, sl);

@@ -230,9 +230,10 @@ struct Chunk {
             for (int idx = P - 1; idx >= 0; --idx) {
                 if (idx == P - 1) continue;  // undone by the turn or by layer l + 1's first group
                 const int gi = group(l, idx);
-                if (idx > 0) e = pass(kBwd, gi, kBetaAcc, l, l, l, nullptr, slotB(l));
-                else if (l > 0) e = pass(kBwdFuse, gi, kBetaAcc, l, l - 1, l, nullptr, slotB(l), slotG(l), slotB(l - 1));
-                else e = pass(kBwd, gi, kBetaAcc | kPhaseOut | kNoStore, 0, 0, 0, nullptr, slotB(0), slotG(0));
+                const int noPhi = !c.quad && (P > 2 ? l == 0 && idx == 1 : l == 1 && idx == 0) ? kNoPhi : 0;
+                if (idx > 0) e = pass(kBwd, gi, kBetaAcc | noPhi, l, l, l, nullptr, slotB(l));
+                else if (l > 0) e = pass(kBwdFuse, gi, kBetaAcc | noPhi, l, l - 1, l, nullptr, slotB(l), slotG(l), slotB(l - 1));
+                else e = pass(c.quad ? kBwd : kBwdFirst, gi, kBetaAcc | kPhaseOut | kNoStore, 0, 0, 0, nullptr, slotB(0), slotG(0));
                 if (e != hipSuccess) return e;
             }
         hipLaunchKernelGGL(k_many_adam, dim3(count), dim3(kAdamThreads), 0, s, B, begin, c.cap,

@@ -52,7 +52,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, typename Tr<R>::V *
     if (threadIdx.x == 0) {
         if (MODE == kTurn || MODE == kTurnPhase || (MODE == kFwd && (a.flags & kEOut))) a.part_e[b] = sums[0];
         if (MODE != kFwd) a.part_b[b] = (a.flags & kBetaAcc) ? a.part_b[b] + sums[1] : sums[1];
-        if (MODE == kTurnPhase || (MODE == kBwd && (a.flags & kPhaseOut))) a.part_g[b] = sums[2];
+        if (MODE == kTurnPhase || MODE == kBwdFirst || (MODE == kBwd && (a.flags & kPhaseOut))) a.part_g[b] = sums[2];
     }
 }
 template <typename R, int MODE, bool TM, int SP>
@@ -406,6 +406,12 @@ void launch_single(int mode, const PassArgs &a, dim3 grid, hipStream_t s)
             return;
         }
     }
+    if constexpr (SP <= 0) {
+        if (mode == kBwdFirst) {
+            hipLaunchKernelGGL((k_pass<R, kBwdFirst, TM, SP>), grid, block, 0, s, a);
+            return;
+        }
+    }
     if (mode == kFwd) hipLaunchKernelGGL((k_pass<R, kFwd, TM, SP>), grid, block, 0, s, a);
     else if (mode == kTurn) hipLaunchKernelGGL((k_pass<R, kTurn, TM, SP>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_pass<R, kBwd, TM, SP>), grid, block, 0, s, a);
@@ -440,6 +446,7 @@ template <typename R, int SP>
 hipError_t QK_LAUNCH_PASS(int mode, const PassArgs &a, uint64_t nblocks, hipStream_t s)
 {
     const dim3 grid((unsigned)nblocks);
+    if (SP > 0 && mode == kBwdFirst) return hipErrorInvalidValue;  // a pass without spectators
     if (mode == kFwdFuse) {
         launch_fuse<R, kFwdFuse, SP>(a, grid, s);
     } else if (mode == kBwdFuse) {
@@ -486,6 +493,12 @@ hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64
                 hipLaunchKernelGGL((k_many_pair<2, SP>), half, block, 0, s, b, m);
                 return hipGetLastError();
             }
+        }
+    }
+    if constexpr (SP <= 0) {
+        if (mode == kBwdFirst) {
+            hipLaunchKernelGGL((k_many_pass<kBwdFirst, SP>), grid, block, 0, s, a, m);
+            return hipGetLastError();
         }
     }
     if (mode == kFwd) hipLaunchKernelGGL((k_many_pass<kFwd, SP>), grid, block, 0, s, a, m);

@@ -30,7 +30,9 @@ enum PassMode : int {
     // opposite orders, so the last group of layer l and the first group of
     // layer l+1 share a geometry and one sweep serves both:
     kFwdFuse = 4,   // group of layer l, phase of layer l+1, same group of layer l+1
-    kBwdFuse = 5    // their inverses with the <lam|X|phi> terms of both layers and <lam|C|phi>
+    kBwdFuse = 5,   // their inverses with the <lam|X|phi> terms of both layers and <lam|C|phi>
+    kBwdFirst = 6   // the last backward sweep (layer 1's first group): phi there is the uniform state
+                    // times layer 1's phase, so it is made from the cost entries, not loaded
 };
 
 // Pass flags.
@@ -44,7 +46,8 @@ enum PassFlags : int {
     kStream = 64,    // nontemporal loads/stores (tiles with long contiguous runs)
     kBetaAcc2 = 128, // kBetaAcc for the second rotation's partials (kBwdFuse)
     kLamFromC = 256, // (kBwd) lam = C phi formed from the loaded phi instead of loaded
-    kFarPhase = 512  // |gamma| max|C| may leave the fast phase reduction's range
+    kFarPhase = 512, // |gamma| max|C| may leave the fast phase reduction's range
+    kNoPhi = 1024    // (kBwd, kBwdFuse) phi is not stored: kBwdFirst follows
 };
 
 // Below this bound on |gamma| max|C| every phase takes the fast reduction

@@ -759,7 +759,7 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
     constexpr bool kSkipB = SP >= 4 && WB == 2 && !TURN;
     // which optional steps this launch performs (compile-time where the mode decides)
     const bool phaseIn = MODE == kTurnPhase || (MODE == kFwd && (a.flags & kPhaseIn));
-    const bool phaseOut = MODE == kTurnPhase || MODE == kBwdFuse || (MODE == kBwd && (a.flags & kPhaseOut));
+    const bool phaseOut = MODE == kTurnPhase || MODE == kBwdFuse || MODE == kBwdFirst || (MODE == kBwd && (a.flags & kPhaseOut));
     const bool wantE = TURN || (MODE == kFwd && (a.flags & kEOut));
     const bool wantB = MODE != kFwd;
     const bool wantG = phaseOut;
@@ -918,6 +918,49 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
                 }
             }
         }
+    } else if constexpr (MODE == kBwdFirst) {
+        // Undo the group on lam alone; phi before it is the uniform state times the
+        // phase.  Both then sit at the same point, so each arrangement's
+        // <lam|X|phi> terms are taken there, on the way back from C to A.  The sweep
+        // is bound by its six transposes (n = 26 folded, complex128: 276 us for
+        // 0.8 GB, where loading phi too took 247); what it gains is that the sweep
+        // before it need not store phi (421 -> 300 us).  E + G: n = 25 QUBO, p = 1
+        // 1211 -> 1124 us, n = 26 MaxCut, p = 6 7.92 -> 7.81 ms, a batch of 1024
+        // small graphs 25.8 -> 25.0 ms.
+        V l[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) l[r] = VA(r) ? ld(&lam[ZA(r)], strm) : zero;
+        if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
+        const R mb = (R)a.mul_b;
+        mix_stage<0, TM>(l, mb, tg);
+        xpose<0, 1>(l, lds, lane, wave);
+        mix_stage<1, TM>(l, mb, tg);
+        xpose<1, 2>(l, lds, lane, wave);
+        mix_stage<2, TM>(l, mb, tg);
+        const R sb = (R)a.scl_b;
+        const V a0 = {(R)a.amp0, (R)0};
+        V f[NR];
+        const auto PK = phase_consts<R>(-a.gamma_out);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            l[r] = vscale(l[r], sb);
+            f[r] = zero;
+            if (VC(r)) {
+                R c, s;
+                phase_cs<(SP >= 0)>(-a.gamma_out, cv[r], c, s, PK);
+                f[r] = cmul(a0, c, s);
+                accG += (double)cv[r] * imcx(l[r], f[r]);
+            }
+        }
+        asm volatile("" : "+v"(accG));
+        beta_terms<2>(f, l, tg, 1.0, accB);
+        xpose<2, 1>(f, lds, lane, wave);
+        xpose<2, 1>(l, lds, lane, wave);
+        beta_terms<1>(f, l, tg, 1.0, accB);
+        xpose<1, 0>(f, lds, lane, wave);
+        xpose<1, 0>(l, lds, lane, wave);
+        beta_terms<0>(f, l, tg, 1.0, accB);
+        REDUCE();
     } else {
         V f[NR], l[NR];
         if (MODE == kBwd && (a.flags & kLamFromC)) {
@@ -940,6 +983,7 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
         if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
         if constexpr (RES) __syncthreads();
         const R mb = (R)a.mul_b;
+        const bool storePhi = !(a.flags & kNoPhi);
         const double f2 = a.fac_b * a.fac_b;
         double sig2 = 1.0;
         adj_stage<0, TM>(f, l, mb, tg, sig2, f2, accB);
@@ -1019,7 +1063,7 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
 #pragma unroll
             for (int r = 0; r < NR; ++r)
                 if (VA(r)) {
-                    st(vscale(f[r], sb2), &psi[thrA3 ^ offA(r)], strm);
+                    if (storePhi) st(vscale(f[r], sb2), &psi[thrA3 ^ offA(r)], strm);
                     st(vscale(l[r], sb2), &lam[thrA3 ^ offA(r)], strm);
                 }
         } else {
@@ -1028,7 +1072,7 @@ __device__ __forceinline__ void tile_pass(const PassArgs &a, uint64_t t, typenam
 #pragma unroll
                 for (int r = 0; r < NR; ++r)
                     if (VC(r)) {
-                        st(f[r], &psi[ZC(r)], strm);
+                        if (storePhi) st(f[r], &psi[ZC(r)], strm);
                         st(l[r], &lam[ZC(r)], strm);
                     }
             }
