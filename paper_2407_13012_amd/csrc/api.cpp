@@ -1199,14 +1199,20 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     const int sbits = qk::sample_subblock_bits(h->n);
     const uint64_t nsub = h->N >> sbits;
     const uint64_t nscr = qk::scan_scratch_doubles(nsub);
-    // layout: sub[nsub] | pre[nsub + 1] | scratch[nscr] | (host output staging)
-    const size_t base = 2 * nsub + 1 + nscr;
+    // layout: sub[nsub] | pre[nsub + 1] | scratch[nscr] | fine[nfine] | (host output staging)
     const size_t stage = out_is_device ? 0 : (size_t)shots * 2;
-    if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, base + stage)) != QAOA_OK) return st;
+    uint64_t nfine = qk::sample_fine_doubles(h->n, h->fold, shots);
+    st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nsub + 1 + nscr + nfine + stage);
+    if (st == QAOA_ERR_OUT_OF_MEMORY && nfine) {  // the shots do without
+        nfine = 0;
+        st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nsub + 1 + nscr + stage);
+    }
+    if (st != QAOA_OK) return st;
+    const size_t base = 2 * nsub + 1 + nscr + nfine;
     if ((st = ensure_results(h, 1)) != QAOA_OK) return st;
     if (h->pin && !h->scanned) HIPCHECK(h, hipEventCreateWithFlags(&h->scanned, hipEventDisableTiming));
-    double *sub = h->parts, *pre = sub + nsub, *scr = pre + nsub + 1;
-    HIPCHECK(h, qk::launch_submass(c64(h), h->psi, h->n, h->fold, sbits, sub, h->stream));
+    double *sub = h->parts, *pre = sub + nsub, *scr = pre + nsub + 1, *fine = nfine ? scr + nscr : nullptr;
+    HIPCHECK(h, qk::launch_submass(c64(h), h->psi, h->n, h->fold, sbits, sub, fine, h->stream));
     HIPCHECK(h, qk::launch_exclusive_scan(sub, nsub, pre, scr, results(h), h->stream));
     if (h->pin) HIPCHECK(h, hipEventRecord(h->scanned, h->stream));
     uint64_t *dz = z;
@@ -1215,7 +1221,7 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
         dz = (uint64_t *)(h->parts + base);
         dc = cost ? h->parts + base + shots : nullptr;
     }
-    HIPCHECK(h, qk::launch_shots(c64(h), h->psi, h->cost, h->n, h->fold, sbits, pre, nsub, shots, seed, dz,
+    HIPCHECK(h, qk::launch_shots(c64(h), h->psi, h->cost, h->n, h->fold, sbits, pre, nsub, fine, shots, seed, dz,
                                  dc, h->stream));
     // the shots run while the total is waited for; without norm they write nothing
     double T = 0;

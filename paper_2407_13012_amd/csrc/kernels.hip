@@ -340,37 +340,16 @@ __device__ __forceinline__ double philox_uniform53(uint64_t seed, uint64_t s)
     return (double)(w >> 11) * 0x1.0p-53;
 }
 
-// Mass of each sub-block of 2^sbits amplitudes: one wave per sub-block, each
-// lane sums a fixed set of elements in order, then a shuffle tree.  The mirror
-// image of a folded state's sub-block holds the same elements, lanes and order
-// reversed: its wave takes both sums from one read (sub-blocks of 256, n <= 32;
-// the tree over reversed lanes pairs the same sums).
+// Mass of each sub-block of 2^sbits amplitudes (sbits != 8): one wave per
+// sub-block, each lane sums a fixed set of elements in order, then a shuffle tree.
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_submass(const typename Tr<R>::V *psi, uint64_t N,
                                                       bool folded, int sbits, uint64_t nsub, double *sub)
 {
     const uint64_t j = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
-    const bool both = folded && sbits == 8;
-    if (j >= (both ? nsub / 2 : nsub)) return;  // whole wave exits together
+    if (j >= nsub) return;  // whole wave exits together
     const uint64_t sb = 1ull << sbits, z0 = j << sbits;
-    if (both) {
-        double q[4], a = 0.0, b = 0.0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) q[r] = norm2(psi[z0 + lane + 64 * r]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            a += q[r];
-            b += q[3 - r];
-        }
-        a = wave_sum(a);
-        b = wave_sum(b);
-        if (lane == 0) {
-            sub[j] = a;
-            sub[nsub - 1 - j] = b;
-        }
-        return;
-    }
     double acc = 0.0;
     for (uint64_t i = lane; i < sb; i += 64) {
         const uint64_t z = z0 + i;
@@ -378,6 +357,76 @@ __global__ __launch_bounds__(kThreads) void k_submass(const typename Tr<R>::V *p
     }
     acc = wave_sum(acc);
     if (lane == 0) sub[j] = acc;
+}
+
+// x of another lane of the row of 16 (DPP control CTRL).
+template <int CTRL>
+__device__ __forceinline__ double row_lane(double x)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, true));
+}
+// wave_sum (the same pairs in the same order) without LDS: halves and rows by lane
+// swaps; after the pairs 8 apart agree, a rotation by 4 reaches the pairs 4 apart.
+__device__ __forceinline__ double wave_sum_lanes(double x)
+{
+    {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+        x = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+    {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+        x = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+    x += row_lane<0x128>(x);
+    x += row_lane<0x124>(x);
+    x += row_lane<0x4E>(x);
+    return x + row_lane<0xB1>(x);
+}
+
+// The same for sub-blocks of 256 amplitudes (n in 8..32), of which `count` are
+// stored.  The mirror image of a folded state's sub-block holds the same elements,
+// lanes and order reversed: its sum is taken from the same read (the tree over
+// reversed lanes pairs the same sums).  With `fine`, also the masses of the
+// sub-block's 16 runs of 16 amplitudes, in any order of summing (k_shots).
+// Bound by memory: the 1 GiB of n = 26 take 165 us, 190 with `fine`, whose 32 MiB
+// are kept for the shots (two and four sub-blocks per wave: 201 and 207).
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_submass256(const typename Tr<R>::V *psi, uint64_t count, bool folded,
+                                                         uint64_t nsub, double *sub, double *fine)
+{
+    const uint64_t j = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63u;
+    if (j >= count) return;  // whole wave exits together
+    double q[4], a = 0.0, b = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) q[r] = norm2(psi[(j << 8) + lane + 64 * r]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        a += q[r];
+        b += q[3 - r];
+    }
+    a = wave_sum_lanes(a);
+    if (folded) b = wave_sum_lanes(b);
+    if (lane == 0) {
+        sub[j] = a;
+        if (folded) sub[nsub - 1 - j] = b;
+    }
+    if (fine) {
+        double f = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double x = q[r];
+            x += row_lane<0xB1>(x);
+            x += row_lane<0x4E>(x);
+            x += row_lane<0x141>(x);
+            x += row_lane<0x140>(x);
+            f = (lane & 15u) == (uint32_t)r ? x : f;
+        }
+        if ((lane & 15u) < 4) fine[j * 16 + (lane & 15u) * 4 + (lane >> 4)] = f;
+    }
 }
 
 constexpr int kScanChunk = kThreads * 16;  // entries per workgroup in the scan
@@ -485,11 +534,18 @@ __global__ __launch_bounds__(kThreads) void k_scan_final(const double *in, uint6
 // with 16 loads ahead of the chain of sums).  Here eight lanes read eight consecutive
 // amplitudes of one shot, and the masses go to the shot's lane through LDS: 0.43 ms,
 // of which 0.18 are the chains (n = 14) and the rest 2.1 GB of reads.
+//
+// With `fine`, the masses of the runs of 16 amplitudes, a shot needs 128 bytes of
+// those and the 16 amplitudes of one run: 0.12 ms instead of 0.45 (1024 shots at n =
+// 22: 11.5 instead of 28 us).  The sums then round
+// otherwise, by less than 2^-44 T in all (256 additions against 32, each off by at
+// most 2^-53 of a sum of at most T): the z found is that of the scan unless one of
+// the two sums around t is within 2^-43 T of it, in which case the shot is scanned.
 template <typename R, int W>
 __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi,
                                                     const typename Tr<R>::CT *C, uint64_t N,
                                                     bool folded, int sbits, const double *pre, uint64_t nsub,
-                                                    int64_t shots, uint64_t seed, uint64_t *zout,
+                                                    const double *fine, int64_t shots, uint64_t seed, uint64_t *zout,
                                                     double *cout)
 {
     constexpr int kLoads = 8, kRows = W / 8, kStep = 8 * kLoads / kRows;  // loads in flight; amplitudes per turn
@@ -520,6 +576,48 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
         double acc = pre[lo];
         uint32_t before = 0;
         bool found = !mine;
+        if (fine) {
+#pragma unroll
+            for (int k = 0; k < kRows; ++k)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    m[k * 8 + row][8 * i + sub] = fine[stored((zr[k] >> 4) + 8 * i + sub, N >> 4, folded)];
+            __builtin_amdgcn_wave_barrier();
+            double under = acc;  // the sum before the run, then before the amplitude
+            uint32_t run = 0;
+            if (!found) {
+                double sum = acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    sum += m[lane][r];
+                    if (sum <= t) under = sum;
+                    run += sum <= t ? 1u : 0u;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const uint64_t zb = zr[k] + 16 * min((uint32_t)__shfl((int)run, k * 8 + row), 15u);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) m[k * 8 + row][8 * i + sub] = norm2(psi[stored(zb + 8 * i + sub, N, folded)]);
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (!found) {
+                double sum = under, over = t;
+                uint32_t in = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    sum += m[lane][r];
+                    if (sum <= t) under = sum;
+                    else if (in == (uint32_t)r) over = sum;
+                    in += sum <= t ? 1u : 0u;
+                }
+                const double eps = T * 0x1p-43;
+                found = run < 16 && in < 16 && over > t + eps && under < t - eps;
+                before = found ? 16 * run + in : 0u;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
         for (uint64_t d = 0; d < sb; d += kStep) {
             const uint64_t open = __ballot(!found);
             if (!open) break;
@@ -784,11 +882,35 @@ uint64_t scan_scratch_doubles(uint64_t count)
     return (count + kScanChunk - 1) / kScanChunk + 1;
 }
 
-hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub,
+// The runs' masses save the shots' reads and a chain of up to 256 sums, and cost
+// the writing of 8 bytes for 16 amplitudes: up to 2^25 stored amplitudes they pay for
+// any number of shots (whole call, us, without and with: n = 14 36 and 30, 22 57 and
+// 44, 24 84 and 72), at 2^26 from 2^16 shots on (1024 shots 221 and 228, 64 000 254
+// and 232), beyond from as many more.  Up to 128 MiB of them are kept.
+uint64_t sample_fine_doubles(int n, bool folded, int64_t shots)
+{
+    const uint64_t held = 1ull << (folded ? n - 1 : n);
+    return sample_subblock_bits(n) == 8 && n <= 28 && (held <= 1ull << 25 || (uint64_t)shots >= held >> 10)
+               ? held >> 4
+               : 0;
+}
+
+hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub, double *fine,
                           hipStream_t s)
 {
     const uint64_t N = 1ull << n, nsub = 1ull << (n - sbits);
-    const unsigned nb = (unsigned)(((folded && sbits == 8 ? nsub / 2 : nsub) + 3) / 4);
+    if (sbits == 8) {
+        const uint64_t count = folded ? nsub / 2 : nsub;
+        const dim3 grid((unsigned)((count + 3) / 4));
+        if (c64)
+            hipLaunchKernelGGL(k_submass256<float>, grid, dim3(kThreads), 0, s, (const Tr<float>::V *)psi, count,
+                               folded, nsub, sub, fine);
+        else
+            hipLaunchKernelGGL(k_submass256<double>, grid, dim3(kThreads), 0, s, (const Tr<double>::V *)psi, count,
+                               folded, nsub, sub, fine);
+        return hipGetLastError();
+    }
+    const unsigned nb = (unsigned)((nsub + 3) / 4);
     if (c64)
         hipLaunchKernelGGL(k_submass<float>, dim3(nb), dim3(kThreads), 0, s, (const Tr<float>::V *)psi,
                            N, folded, sbits, nsub, sub);
@@ -812,18 +934,20 @@ hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, 
 }
 
 hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool folded, int sbits,
-                        const double *pre, uint64_t nsub, int64_t shots, uint64_t seed,
+                        const double *pre, uint64_t nsub, const double *fine, int64_t shots, uint64_t seed,
                         uint64_t *z, double *cost, hipStream_t s)
 {
     const uint64_t N = 1ull << n;
     // 8 shots a wave, whose sub-blocks are read 64 amplitudes at a time, while that
     // gives every SIMD a wave or few; 32 a wave, whose chains of sums fill four times
     // the lanes, beyond (n = 20, both in us: 16 000 shots 64 and 87, 64 000 89 and 93,
-    // 250 000 164 and 142, 10^6 473 and 327)
+    // 250 000 164 and 142, 10^6 473 and 327).  With the runs' masses a shot has little
+    // to read, and the lanes count from 2^14 shots on (n = 22, us per call: 1024 shots
+    // 42 and 45, 16 000 44 and 44, 64 000 53 and 45).
 #define QK_SHOTS(R, W)                                                                                         \
     hipLaunchKernelGGL((k_shots<R, W>), dim3(grid_for((uint64_t)shots * (64 / W))), dim3(kThreads), 0, s,          \
-                       (const Tr<R>::V *)psi, (const Tr<R>::CT *)C, N, folded, sbits, pre, nsub, shots, seed, z, cost)
-    if (shots <= (1 << 16)) {
+                       (const Tr<R>::V *)psi, (const Tr<R>::CT *)C, N, folded, sbits, pre, nsub, fine, shots, seed, z, cost)
+    if (shots <= (fine ? 1 << 14 : 1 << 16)) {
         if (c64) QK_SHOTS(float, 8);
         else QK_SHOTS(double, 8);
     } else {

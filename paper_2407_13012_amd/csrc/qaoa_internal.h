@@ -263,18 +263,20 @@ hipError_t launch_minmax_final(const double *pmin, const double *pmax, uint64_t 
                                double *out, hipStream_t s);
 hipError_t launch_widen_cost(const float *C32, double *out, uint64_t N, hipStream_t s);
 
-// Sampling: sub-block masses, their exclusive scan, then one thread per shot.
+// Sampling: sub-block masses, their exclusive scan, then one lane per shot.
 // `folded`: psi (and C) hold the half of a folded state; masses and shots are
 // those of the whole one, summed in its order.
 int sample_subblock_bits(int n);
+// Masses of the runs of 16 amplitudes that a call keeps beside them (`fine`; 0: none).
+uint64_t sample_fine_doubles(int n, bool folded, int64_t shots);
 uint64_t scan_scratch_doubles(uint64_t count);
-hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub,
+hipError_t launch_submass(bool c64, const void *psi, int n, bool folded, int sbits, double *sub, double *fine,
                           hipStream_t s);
 // *total (may be host memory) also receives the sum.
 hipError_t launch_exclusive_scan(const double *in, uint64_t count, double *out, double *scratch,
                                  double *total, hipStream_t s);
 hipError_t launch_shots(bool c64, const void *psi, const void *C, int n, bool folded, int sbits,
-                        const double *pre, uint64_t nsub, int64_t shots, uint64_t seed,
+                        const double *pre, uint64_t nsub, const double *fine, int64_t shots, uint64_t seed,
                         uint64_t *z, double *cost, hipStream_t s);
 
 // Gradient of a small state in one launch (small.hip): at most 2^kSmallBits
