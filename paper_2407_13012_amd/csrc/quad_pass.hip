@@ -6,7 +6,7 @@
 // amplitudes in 256 threads an n = 17 MaxCut state was 16 workgroups of 14-19 us
 // on 256 CUs.  Tiles of 1024 amplitudes make 64 of them with a quarter of the
 // work each; the tile grows with n as far as two sweeps per layer need it.
-// E + G at p = 6, complex128 MaxCut: n = 17 230 -> 122 us (a sweep 14-19 -> 7 us).
+// E + G at p = 6, complex128 MaxCut: n = 17 230 -> 102 us (a sweep 14-19 -> 5-8 us).
 //
 // Compiled once per QK_QUAD_REAL (double or float).
 #include "many_device.h"
