@@ -1205,6 +1205,7 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nsub + 1 + nscr + nfine + stage);
     if (st == QAOA_ERR_OUT_OF_MEMORY && nfine) {  // the shots do without
         nfine = 0;
+        (void)hipGetLastError();  // the failed allocation is not the next launch's error
         st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nsub + 1 + nscr + stage);
     }
     if (st != QAOA_OK) return st;

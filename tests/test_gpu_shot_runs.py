@@ -64,3 +64,37 @@ def test_shots_at_the_rounding_of_a_boundary():
         z, c = q.sample(shots, 11)
     z_ref, c_ref = oracle.sample(n, psi, C, shots, seed=11)
     assert np.array_equal(z, z_ref) and np.array_equal(c, c_ref)
+
+
+def test_shots_without_room_for_the_run_masses():
+    import torch
+    from paper_2407_13012_amd import QaoaHandle, _binding
+    n, limit, refused = 20, [None], []
+
+    def alloc(nbytes, stream, _user):
+        if limit[0] is not None and nbytes > limit[0]:
+            refused.append(int(nbytes))
+            return None
+        return torch.cuda.caching_allocator_alloc(int(nbytes), torch.cuda.current_device(), int(stream or 0))
+
+    def free(ptr, _nbytes, _stream, _user):
+        torch.cuda.caching_allocator_delete(int(ptr))
+
+    own = _binding.Allocator(_binding.ALLOC_FN(alloc), _binding.FREE_FN(free), None)
+    gamma, beta = qi.uniform_angles(2, seed=[20, n, 1])
+    inst = _instance(n, "qubo")
+    with QaoaHandle.from_instance(inst) as q:
+        q.statevector(gamma, beta, copy=False)
+        z_ref, c_ref = q.sample(100, 5)
+    _binding.qaoa_set_allocator(own)
+    try:
+        q = QaoaHandle.from_instance(inst)
+    finally:
+        _binding.qaoa_set_allocator(None)
+    with q:
+        q.statevector(gamma, beta, copy=False)
+        limit[0] = 400 << 10  # the run masses take 512 KiB, everything else 70
+        z, c = q.sample(100, 5)
+        E = q.evaluate(gamma, beta)
+    assert len(refused) == 1 and np.isfinite(E)
+    assert np.array_equal(z, z_ref) and np.array_equal(c, c_ref)
