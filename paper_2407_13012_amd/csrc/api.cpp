@@ -65,7 +65,8 @@ struct qaoa_handle_s {
     // device memory and a copy.
     double *pin = nullptr;
     size_t pin_cap = 0;    // doubles
-    int copied = 0;        // results copied so far
+    int copied = 0;        // results copied so far (collect)
+    bool no_pin = false;   // pinning failed: not tried again
     double *res = nullptr;
     size_t res_cap = 0;    // doubles
     hipEvent_t scanned = nullptr;  // sampling: the total mass has been written
@@ -244,14 +245,12 @@ qaoa_status ensure_doubles(qaoa_handle h, double **buf, size_t *cap, size_t coun
     return QAOA_OK;
 }
 
-// Ensure that kernels have `count` doubles to write their results to.
+// Ensure that kernels have `count` doubles to write their results to.  A call does
+// this once, before its first launch: pinning would wait for what is queued.
 qaoa_status ensure_results(qaoa_handle h, size_t count)
 {
     if (h->pin_cap >= count) return QAOA_OK;
-    if (!h->pin && h->copied < 3) {
-        ++h->copied;
-        return ensure_doubles(h, &h->res, &h->res_cap, count);
-    }
+    if (!h->pin && (h->copied < 3 || h->no_pin)) return ensure_doubles(h, &h->res, &h->res_cap, count);
     if (h->pin) {
         HIPCHECK(h, hipStreamSynchronize(h->stream));
         (void)hipHostFree(h->pin);
@@ -262,6 +261,7 @@ qaoa_status ensure_results(qaoa_handle h, size_t count)
     if (hipHostMalloc((void **)&h->pin, cap * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         h->pin = nullptr;
+        h->no_pin = true;
         return ensure_doubles(h, &h->res, &h->res_cap, count);
     }
     h->pin_cap = cap;
@@ -272,7 +272,10 @@ double *results(qaoa_handle h) { return h->pin ? h->pin : h->res; }
 // Waits for the stream and copies the first `count` results.
 qaoa_status collect(qaoa_handle h, size_t count, double *host)
 {
-    if (!h->pin) HIPCHECK(h, hipMemcpyAsync(host, h->res, count * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    if (!h->pin) {
+        ++h->copied;
+        HIPCHECK(h, hipMemcpyAsync(host, h->res, count * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    }
     HIPCHECK(h, hipStreamSynchronize(h->stream));
     if (h->pin) std::memcpy(host, h->pin, count * sizeof(double));
     return QAOA_OK;
@@ -639,10 +642,10 @@ qaoa_status ensure_lam(qaoa_handle h)
     return QAOA_OK;
 }
 
+// Sums `nslots` slots of `count` partials into the results (ensure_results) and
+// waits for them.
 qaoa_status fetch_results(qaoa_handle h, int nslots, uint64_t count, double *host)
 {
-    const qaoa_status st = ensure_results(h, (size_t)nslots);
-    if (st != QAOA_OK) return st;
     HIPCHECK(h, qk::launch_sum_slots(h->parts, count, count, nslots, sum_scale(h), results(h), h->stream));
     return collect(h, (size_t)nslots, host);
 }
@@ -1086,6 +1089,7 @@ qaoa_status qaoa_expectation(qaoa_handle h, double *E)
     DeviceGuard dg(h->device);
     const uint64_t T = (h->M + qk::kTile - 1) / qk::kTile;
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, T)) != QAOA_OK) return st;
+    if ((st = ensure_results(h, 1)) != QAOA_OK) return st;
     HIPCHECK(h, qk::launch_expect(c64(h), h->psi, h->cost, stored_bits(h), h->parts, h->stream));
     return fetch_results(h, 1, T, E);
 }
@@ -1102,10 +1106,11 @@ qaoa_status qaoa_evaluate(qaoa_handle h, int32_t p, const double *gamma, const d
         return qaoa_expectation(h, E);
     }
     DeviceGuard dg(h->device);
-    h->state_valid = false;
     choose_tiles(h, p, gamma);
     const uint64_t T = nblocks(h);
     if ((st = ensure_doubles(h, &h->parts, &h->parts_cap, T)) != QAOA_OK) return st;
+    if ((st = ensure_results(h, 1)) != QAOA_OK) return st;
+    h->state_valid = false;
     if ((st = run_forward(h, p, gamma, beta, false, true)) != QAOA_OK) return st;
     if ((st = keep_angles(h, p, gamma, beta)) != QAOA_OK) return st;
     h->state_valid = true;

@@ -1,0 +1,84 @@
+// What the library's calls do on the host: which memory they take, which kernels
+// they launch and in what order (fake_hip.h).  argv[1] names the check.
+#include "fake_hip.h"
+#include "qaoa.h"
+
+namespace {
+
+const double kGamma[3] = {0.2, 0.3, 0.4}, kBeta[3] = {0.6, 0.5, 0.4};
+
+qaoa_handle ring(int n, int precision = QAOA_C128)
+{
+    std::vector<int32_t> e;
+    for (int i = 0; i < n; ++i) {
+        e.push_back(i);
+        e.push_back((i + 1) % n);
+    }
+    qaoa_handle h = nullptr;
+    EXPECT(qaoa_create_maxcut(n, n, e.data(), nullptr, precision, nullptr, &h) == QAOA_OK);
+    return h;
+}
+
+void gradient(qaoa_handle h)
+{
+    double E, dg[3], db[3];
+    EXPECT(qaoa_gradient(h, 3, kGamma, kBeta, &E, dg, db) == QAOA_OK);
+}
+
+// A handle's first three results are copied from device memory; its fourth call
+// pins memory, once, and before it launches anything.
+void pinned_results()
+{
+    for (int n : {10, 14, 22}) {  // one launch, small tiles, large sweeps
+        qaoa_handle h = ring(n);
+        const int before = fake().pins;
+        for (int k = 0; k < 3; ++k) gradient(h);
+        EXPECT(fake().pins == before);
+        fake().log.clear();
+        gradient(h);
+        EXPECT(fake().pins == before + 1 && fake().log.front() == "pin");
+        double E;
+        gradient(h);
+        EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK && qaoa_expectation(h, &E) == QAOA_OK);
+        EXPECT(fake().pins == before + 1);
+        qaoa_destroy(h);
+    }
+    // each call takes one result, whatever it computes
+    qaoa_handle h = ring(14);
+    const int before = fake().pins;
+    double E;
+    EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK && qaoa_expectation(h, &E) == QAOA_OK);
+    gradient(h);
+    EXPECT(fake().pins == before);
+    fake().log.clear();
+    EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK);
+    EXPECT(fake().pins == before + 1 && fake().log.front() == "pin");
+    qaoa_destroy(h);
+}
+
+// Memory that cannot be pinned is not asked for again.
+void pinning_refused()
+{
+    fake().pin_fails = true;
+    qaoa_handle h = ring(14);
+    const int before = fake().pins;
+    for (int k = 0; k < 8; ++k) gradient(h);
+    EXPECT(fake().pins == before + 1);
+    qaoa_destroy(h);
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::map<std::string, void (*)()> checks = {
+        {"pinned_results", pinned_results},
+        {"pinning_refused", pinning_refused},
+    };
+    const auto it = checks.find(argc > 1 ? argv[1] : "");
+    EXPECT(it != checks.end());
+    it->second();
+    EXPECT(fake().live.empty());
+    std::printf("%s ok\n", argv[1]);
+    return 0;
+}
