@@ -291,13 +291,6 @@ __global__ __launch_bounds__(kThreads) void k_unfold_words(const W *in, uint64_t
         out[(2 * half - 1 - i / words) * words + i % words] = v;
     }
 }
-// out[i] = in[count - 1 - i]
-template <typename W>
-__global__ __launch_bounds__(kThreads) void k_reverse(const W *in, uint64_t count, W *out)
-{
-    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < count; i += stride) out[i] = in[count - 1 - i];
-}
 // The same for cost entries, fp32 widened to fp64.
 __global__ __launch_bounds__(kThreads) void k_unfold_widen(const float *in, uint64_t half, double *out)
 {
@@ -813,15 +806,6 @@ hipError_t launch_unfold(const void *in, uint64_t half, int entry_bytes, void *o
     if (entry_bytes == 16 && a % 16 == 0) return go(uint4{});
     if (entry_bytes >= 8 && a % 8 == 0) return go(uint64_t{});
     return a % 4 == 0 ? go(uint32_t{}) : go(uint8_t{});
-}
-
-hipError_t launch_reverse(const void *in, uint64_t count, int entry_bytes, void *out, hipStream_t s)
-{
-    const dim3 grid(grid_for(count)), block(kThreads);
-    if (entry_bytes == 16) hipLaunchKernelGGL(k_reverse<uint4>, grid, block, 0, s, (const uint4 *)in, count, (uint4 *)out);
-    else if (entry_bytes == 8) hipLaunchKernelGGL(k_reverse<uint64_t>, grid, block, 0, s, (const uint64_t *)in, count, (uint64_t *)out);
-    else hipLaunchKernelGGL(k_reverse<uint32_t>, grid, block, 0, s, (const uint32_t *)in, count, (uint32_t *)out);
-    return hipGetLastError();
 }
 
 hipError_t launch_unfold_widen(const float *in, uint64_t half, double *out, hipStream_t s)

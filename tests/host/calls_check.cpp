@@ -67,6 +67,48 @@ void pinning_refused()
     qaoa_destroy(h);
 }
 
+// The allocation of `bytes` bytes, the first a handle made of that size.
+const uint8_t *buffer(size_t bytes)
+{
+    for (const auto &kv : fake().live)
+        if (kv.second == bytes) return (const uint8_t *)kv.first;
+    EXPECT(!"no such allocation");
+    return nullptr;
+}
+
+// Whole host arrays of a folded handle: the stored half and its mirror image, in
+// pageable and pinned memory at any address, with no device memory to be had.
+void host_exports()
+{
+    for (int n : {14, 18}) {
+        for (int prec : {QAOA_C128, QAOA_C64}) {
+            const size_t N = (size_t)1 << n, amp = prec == QAOA_C64 ? 8 : 16;
+            qaoa_handle h = ring(n, prec);
+            std::vector<uint8_t> out(N * 16 + 64);
+            const uint8_t *psi = buffer(N / 2 * amp);
+            for (int pin = 0; pin < 2; ++pin)
+                for (size_t at : {0, 8, 4}) {
+                    fake().pinned = pin ? (char *)out.data() : nullptr;
+                    fake().pinned_bytes = pin ? out.size() : 0;
+                    fake().largest = fake().free_bytes = 0;
+                    uint8_t *o = out.data() + at;
+                    EXPECT(qaoa_statevector(h, 3, kGamma, kBeta, o, 0) == QAOA_OK);
+                    for (size_t z = 0; z < N; ++z)
+                        EXPECT(!std::memcmp(o + z * amp, psi + (z < N / 2 ? z : N - 1 - z) * amp, amp));
+                    if (prec == QAOA_C128) {
+                        const uint8_t *cost = buffer(N / 2 * 8);
+                        EXPECT(qaoa_cost_diagonal(h, (double *)o, 0) == QAOA_OK);
+                        for (size_t z = 0; z < N; ++z)
+                            EXPECT(!std::memcmp(o + z * 8, cost + (z < N / 2 ? z : N - 1 - z) * 8, 8));
+                    }
+                    fake().largest = ~(size_t)0;
+                    fake().free_bytes = 1ull << 40;
+                }
+            qaoa_destroy(h);
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -74,6 +116,7 @@ int main(int argc, char **argv)
     const std::map<std::string, void (*)()> checks = {
         {"pinned_results", pinned_results},
         {"pinning_refused", pinning_refused},
+        {"host_exports", host_exports},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());

@@ -22,9 +22,8 @@ struct Fake {
     size_t largest = ~(size_t)0;                  // allocations above this fail
     bool pin_fails = false;
     int pins = 0, mallocs = 0, copies = 0;
-    int foreign_device = -1;                      // device of `foreign` memory
-    char *foreign = nullptr;
-    size_t foreign_bytes = 0;
+    char *pinned = nullptr;                       // memory that a caller has pinned
+    size_t pinned_bytes = 0;
     dim3 grid, block;                             // of the launch being pushed
     size_t shared = 0;
     hipStream_t stream = nullptr;
@@ -52,14 +51,6 @@ inline int launches(const char *part)
     } while (0)
 
 // The effect of the kernels that move entries (arguments as the kernels take them).
-template <typename W>
-inline void host_reverse(void **a)
-{
-    const W *in = *(const W **)a[0];
-    const uint64_t count = *(uint64_t *)a[1];
-    W *out = *(W **)a[2];
-    for (uint64_t i = 0; i < count; ++i) out[i] = in[count - 1 - i];
-}
 struct Entry16 {
     uint64_t a, b;
 };
@@ -78,7 +69,6 @@ inline void host_unfold(void **a)
 inline void run_kernel(const std::string &name, void **args)
 {
     const bool w16 = name.find("HIP_vector_type") != std::string::npos, w8 = name.find("Im") != std::string::npos;
-    if (name.find("k_reverse") != std::string::npos) w16 ? host_reverse<Entry16>(args) : w8 ? host_reverse<uint64_t>(args) : host_reverse<uint32_t>(args);
     if (name.find("k_unfold_words") != std::string::npos) w16 ? host_unfold<Entry16>(args) : w8 ? host_unfold<uint64_t>(args) : host_unfold<uint32_t>(args);
     if (name.find("k_unfold_widen") != std::string::npos) {
         const float *in = *(const float **)args[0];
@@ -174,12 +164,13 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
 {
     std::memset(a, 0, sizeof *a);
     const char *c = (const char *)p;
-    if (fake().foreign && c >= fake().foreign && c < fake().foreign + fake().foreign_bytes) {
-        if (fake().foreign_device < 0) return hipErrorInvalidValue;  // unknown to the runtime
-        a->type = hipMemoryTypeDevice;
-        a->device = fake().foreign_device;
+    if (c >= fake().pinned && c < fake().pinned + fake().pinned_bytes) {
+        a->type = hipMemoryTypeHost;
+        a->hostPointer = a->devicePointer = (void *)p;
         return hipSuccess;
     }
+    const auto it = fake().live.upper_bound((void *)p);
+    if (it == fake().live.begin() || c >= (const char *)std::prev(it)->first + std::prev(it)->second) return hipErrorInvalidValue;
     a->type = hipMemoryTypeDevice;
     a->device = 0;
     a->devicePointer = (void *)p;
