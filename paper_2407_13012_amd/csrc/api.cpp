@@ -663,16 +663,19 @@ std::vector<qk::Geometry> geometries(qaoa_handle h, const std::vector<qk::PassPl
     return out;
 }
 
-// The address at which kernels of the handle's device may write pinned host memory
-// `out` (NULL: it is not, or not that device's).
-void *pinned_address(qaoa_handle h, const void *out)
+// The address at which kernels of the handle's device may write `out`: its own
+// memory, or host memory pinned for it.  NULL for any other (of another device,
+// managed, unknown to the runtime), which only copies reach safely.
+void *kernel_address(qaoa_handle h, void *out)
 {
     hipPointerAttribute_t a;
     if (hipPointerGetAttributes(&a, out) != hipSuccess) {
         (void)hipGetLastError();  // memory the runtime does not know is no error
         return nullptr;
     }
-    return a.type == hipMemoryTypeHost && a.device == h->device && a.hostPointer == out ? a.devicePointer : nullptr;
+    if (a.device != h->device) return nullptr;
+    if (a.type == hipMemoryTypeDevice) return out;
+    return a.type == hipMemoryTypeHost && a.hostPointer == out ? a.devicePointer : nullptr;
 }
 
 // The mirrored half of a folded array in host memory: out[2 M - 1 - z] = out[z]
@@ -691,7 +694,7 @@ void mirror(char *out, uint64_t M)
 // Neither takes device memory.
 qaoa_status unfold_to_host(qaoa_handle h, const void *half, size_t entry, void *out)
 {
-    if (void *dst = pinned_address(h, out)) {
+    if (void *dst = kernel_address(h, out)) {
         HIPCHECK(h, qk::launch_unfold(half, h->M, (int)entry, dst, h->stream));
         HIPCHECK(h, hipStreamSynchronize(h->stream));
         return QAOA_OK;
@@ -700,6 +703,22 @@ qaoa_status unfold_to_host(qaoa_handle h, const void *half, size_t entry, void *
     HIPCHECK(h, hipStreamSynchronize(h->stream));
     if (entry == 16) mirror<16>((char *)out, h->M);
     else mirror<8>((char *)out, h->M);
+    return QAOA_OK;
+}
+
+// Whole array of a folded one in device memory, in stream order.  Where kernels may
+// not write it, the half is copied, turned round in place for its mirror image, and
+// turned back.
+qaoa_status unfold_to_device(qaoa_handle h, void *half, size_t entry, void *out)
+{
+    if (void *dst = kernel_address(h, out)) {
+        HIPCHECK(h, qk::launch_unfold(half, h->M, (int)entry, dst, h->stream));
+        return QAOA_OK;
+    }
+    for (size_t at : {(size_t)0, h->M * entry}) {
+        HIPCHECK(h, hipMemcpyAsync((char *)out + at, half, h->M * entry, hipMemcpyDeviceToDevice, h->stream));
+        HIPCHECK(h, qk::launch_reverse(half, h->M, (int)entry, h->stream));
+    }
     return QAOA_OK;
 }
 
@@ -1018,12 +1037,11 @@ qaoa_status qaoa_cost_diagonal(qaoa_handle h, double *out, int32_t out_is_device
     if (!out) return fail(QAOA_ERR_INVALID_ARGUMENT, "out is NULL");
     DeviceGuard dg(h->device);
     if (h->fold) {
+        if (!c64(h)) return out_is_device ? unfold_to_device(h, h->cost, 8, out) : unfold_to_host(h, h->cost, 8, out);
         if (out_is_device) {
-            HIPCHECK(h, c64(h) ? qk::launch_unfold_widen((const float *)h->cost, h->M, out, h->stream)
-                               : qk::launch_unfold(h->cost, h->M, 8, out, h->stream));
+            HIPCHECK(h, qk::launch_unfold_widen((const float *)h->cost, h->M, out, h->stream));
             return QAOA_OK;
         }
-        if (!c64(h)) return unfold_to_host(h, h->cost, 8, out);
     }
     if (!c64(h)) {
         HIPCHECK(h, hipMemcpyAsync(out, h->cost, h->N * 8,
@@ -1089,10 +1107,7 @@ qaoa_status qaoa_statevector(qaoa_handle h, int32_t p, const double *gamma, cons
     if ((st = keep_angles(h, p, gamma, beta)) != QAOA_OK) return st;
     h->state_valid = true;
     if (out) {
-        if (h->fold && out_is_device) {
-            HIPCHECK(h, qk::launch_unfold(h->psi, h->M, (int)amp_bytes(h->prec), out, h->stream));
-            return QAOA_OK;
-        }
+        if (h->fold && out_is_device) return unfold_to_device(h, h->psi, amp_bytes(h->prec), out);
         if (h->fold) return unfold_to_host(h, h->psi, amp_bytes(h->prec), out);
         HIPCHECK(h, hipMemcpyAsync(out, h->psi, h->N * amp_bytes(h->prec),
                                    out_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,

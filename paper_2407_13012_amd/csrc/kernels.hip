@@ -291,7 +291,18 @@ __global__ __launch_bounds__(kThreads) void k_unfold_words(const W *in, uint64_t
         out[(2 * half - 1 - i / words) * words + i % words] = v;
     }
 }
-// The same for cost entries, fp32 widened to fp64.
+// x[i] <-> x[count - 1 - i]
+template <typename W>
+__global__ __launch_bounds__(kThreads) void k_reverse(W *x, uint64_t count)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
+    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < count / 2; i += stride) {
+        const W a = x[i], b = x[count - 1 - i];
+        x[i] = b;
+        x[count - 1 - i] = a;
+    }
+}
+// The same as k_unfold_words for cost entries, fp32 widened to fp64.
 __global__ __launch_bounds__(kThreads) void k_unfold_widen(const float *in, uint64_t half, double *out)
 {
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
@@ -806,6 +817,15 @@ hipError_t launch_unfold(const void *in, uint64_t half, int entry_bytes, void *o
     if (entry_bytes == 16 && a % 16 == 0) return go(uint4{});
     if (entry_bytes >= 8 && a % 8 == 0) return go(uint64_t{});
     return a % 4 == 0 ? go(uint32_t{}) : go(uint8_t{});
+}
+
+hipError_t launch_reverse(void *x, uint64_t count, int entry_bytes, hipStream_t s)
+{
+    const dim3 grid(grid_for(count / 2)), block(kThreads);
+    if (entry_bytes == 16) hipLaunchKernelGGL(k_reverse<uint4>, grid, block, 0, s, (uint4 *)x, count);
+    else if (entry_bytes == 8) hipLaunchKernelGGL(k_reverse<uint64_t>, grid, block, 0, s, (uint64_t *)x, count);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 hipError_t launch_unfold_widen(const float *in, uint64_t half, double *out, hipStream_t s)

@@ -253,6 +253,8 @@ hipError_t launch_fill_plus(bool c64, void *psi, int n, uint64_t count, hipStrea
 // entries of 8 or 16 bytes at any address, or fp32 entries widened to fp64.
 hipError_t launch_unfold(const void *in, uint64_t half, int entry_bytes, void *out, hipStream_t s);
 hipError_t launch_unfold_widen(const float *in, uint64_t half, double *out, hipStream_t s);
+// Turns an array of entries of 8 or 16 bytes round in place.
+hipError_t launch_reverse(void *x, uint64_t count, int entry_bytes, hipStream_t s);
 hipError_t launch_expect(bool c64, const void *psi, const void *C, int n, double *parts,
                          hipStream_t s);
 hipError_t launch_minmax(bool c64, const void *C, int n, double *pmin, double *pmax,

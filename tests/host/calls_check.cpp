@@ -109,6 +109,40 @@ void host_exports()
     }
 }
 
+// Whole device arrays of a folded handle: its own device's memory is written by a
+// kernel, memory of another device or unknown to the runtime only by copies.
+void device_exports()
+{
+    for (int prec : {QAOA_C128, QAOA_C64}) {
+        const int n = 14;
+        const size_t N = (size_t)1 << n, amp = prec == QAOA_C64 ? 8 : 16;
+        qaoa_handle h = ring(n, prec);
+        const uint8_t *psi = buffer(N / 2 * amp), *cost = prec == QAOA_C128 ? buffer(N / 2 * 8) : nullptr;
+        const std::vector<uint8_t> was(psi, psi + N / 2 * amp);
+        for (int kind = 0; kind < 3; ++kind) {
+            void *out = nullptr;
+            if (kind < 2) EXPECT(hipMalloc(&out, N * 16 + 16) == hipSuccess);
+            else out = std::malloc(N * 16 + 16);
+            if (kind == 1) fake().owner[out] = 1;
+            uint8_t *o = (uint8_t *)out + 16;
+            fake().log.clear();
+            EXPECT(qaoa_statevector(h, 3, kGamma, kBeta, o, 1) == QAOA_OK);
+            for (size_t z = 0; z < N; ++z)
+                EXPECT(!std::memcmp(o + z * amp, &was[(z < N / 2 ? z : N - 1 - z) * amp], amp));
+            EXPECT(!std::memcmp(psi, was.data(), was.size()));
+            if (cost) {
+                EXPECT(qaoa_cost_diagonal(h, (double *)o, 1) == QAOA_OK);
+                for (size_t z = 0; z < N; ++z) EXPECT(!std::memcmp(o + z * 8, cost + (z < N / 2 ? z : N - 1 - z) * 8, 8));
+            }
+            EXPECT(launches("k_unfold_words") == (kind == 0 ? (cost ? 2 : 1) : 0));
+            fake().owner.erase(out);
+            if (kind < 2) EXPECT(hipFree(out) == hipSuccess);
+            else std::free(out);
+        }
+        qaoa_destroy(h);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -117,6 +151,7 @@ int main(int argc, char **argv)
         {"pinned_results", pinned_results},
         {"pinning_refused", pinning_refused},
         {"host_exports", host_exports},
+        {"device_exports", device_exports},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());

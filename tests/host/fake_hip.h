@@ -6,6 +6,7 @@
 #pragma once
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -24,6 +25,7 @@ struct Fake {
     int pins = 0, mallocs = 0, copies = 0;
     char *pinned = nullptr;                       // memory that a caller has pinned
     size_t pinned_bytes = 0;
+    std::map<void *, int> owner;                  // allocations of other devices than 0
     dim3 grid, block;                             // of the launch being pushed
     size_t shared = 0;
     hipStream_t stream = nullptr;
@@ -66,9 +68,16 @@ inline void host_unfold(void **a)
         out[(2 * half - 1 - i / words) * words + i % words] = in[i];
     }
 }
+template <typename W>
+inline void host_reverse(void **a)
+{
+    W *x = *(W **)a[0];
+    std::reverse(x, x + *(uint64_t *)a[1]);
+}
 inline void run_kernel(const std::string &name, void **args)
 {
     const bool w16 = name.find("HIP_vector_type") != std::string::npos, w8 = name.find("Im") != std::string::npos;
+    if (name.find("k_reverse") != std::string::npos) w16 ? host_reverse<Entry16>(args) : host_reverse<uint64_t>(args);
     if (name.find("k_unfold_words") != std::string::npos) w16 ? host_unfold<Entry16>(args) : w8 ? host_unfold<uint64_t>(args) : host_unfold<uint32_t>(args);
     if (name.find("k_unfold_widen") != std::string::npos) {
         const float *in = *(const float **)args[0];
@@ -172,7 +181,8 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
     const auto it = fake().live.upper_bound((void *)p);
     if (it == fake().live.begin() || c >= (const char *)std::prev(it)->first + std::prev(it)->second) return hipErrorInvalidValue;
     a->type = hipMemoryTypeDevice;
-    a->device = 0;
+    const auto of = fake().owner.find(std::prev(it)->first);
+    a->device = of == fake().owner.end() ? 0 : of->second;
     a->devicePointer = (void *)p;
     return hipSuccess;
 }
