@@ -71,7 +71,8 @@ typedef enum {
  * The handle allocates the state and cost diagonal on the current HIP device
  * (Sec. IV-B: state and cost arrays at initialisation, other buffers lazily when
  * first needed).  The cost diagonal is built here.
- * Errors: INVALID_ARGUMENT, OUT_OF_MEMORY (2^n buffers exceed free memory), DEVICE.
+ * Errors: INVALID_ARGUMENT, OUT_OF_MEMORY (the state and the cost diagonal, or
+ * that half of them, exceed free memory), DEVICE.
  */
 qaoa_status qaoa_create_maxcut(int32_t n, int64_t m, const int32_t *edges, const double *w,
                                int32_t precision, void *stream, qaoa_handle *out);

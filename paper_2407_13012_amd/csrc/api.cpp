@@ -635,7 +635,7 @@ qaoa_status ensure_lam(qaoa_handle h)
     if (h->lam) return QAOA_OK;
     size_t fr = 0, tot = 0;
     HIPCHECK(h, hipMemGetInfo(&fr, &tot));
-    if (!fits(h, (double)h->N * amp_bytes(h->prec), fr))
+    if (!fits(h, (double)h->A * amp_bytes(h->prec), fr))
         return fail(QAOA_ERR_OUT_OF_MEMORY, "adjoint vector does not fit in free device memory");
     if (dev_alloc(h, &h->lam, h->A * amp_bytes(h->prec)) != hipSuccess)
         return fail(QAOA_ERR_OUT_OF_MEMORY, "adjoint vector allocation failed");
@@ -759,7 +759,7 @@ qaoa_status create_common(int32_t n, int32_t precision, bool maxcut, void *strea
         delete h;
         return device_fail(nullptr, "hipMemGetInfo", e);
     }
-    const double need = (double)h->N * (double)(amp_bytes(precision) + cost_bytes(precision)) +
+    const double need = (double)h->A * (double)(amp_bytes(precision) + cost_bytes(precision)) +
                         (double)nblocks(n, precision == QAOA_C64) * 8.0 * 2 + (1 << 20);
     if (!fits(h, need, fr)) {
         delete h;

@@ -143,6 +143,30 @@ void device_exports()
     }
 }
 
+// Free memory is compared with what a handle allocates: half of the state for a
+// folded one (16 + 8 bytes per amplitude, the adjoint vector 16 more), all of it
+// for a polynomial.
+void memory_checks()
+{
+    const int n = 20;
+    const size_t half = (size_t)1 << (n - 1), room = 2 << 20;
+    fake().free_bytes = half * 24 + room;
+    qaoa_handle h = ring(n);
+    const uint64_t mask = 3;
+    const double w = 1.0;
+    qaoa_handle whole = nullptr;
+    EXPECT(qaoa_create_poly(n, 1, &mask, &w, 0.0, QAOA_C128, nullptr, &whole) == QAOA_ERR_OUT_OF_MEMORY && !whole);
+    double E, dg[3], db[3];
+    fake().free_bytes = half * 16 - 1;
+    EXPECT(qaoa_gradient(h, 3, kGamma, kBeta, &E, dg, db) == QAOA_ERR_OUT_OF_MEMORY);
+    fake().free_bytes = half * 16;
+    gradient(h);
+    qaoa_destroy(h);
+    fake().free_bytes = half * 24;
+    std::vector<int32_t> e = {0, 1};
+    EXPECT(qaoa_create_maxcut(n, 1, e.data(), nullptr, QAOA_C128, nullptr, &h) == QAOA_ERR_OUT_OF_MEMORY);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -152,6 +176,7 @@ int main(int argc, char **argv)
         {"pinning_refused", pinning_refused},
         {"host_exports", host_exports},
         {"device_exports", device_exports},
+        {"memory_checks", memory_checks},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());
