@@ -701,7 +701,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     double2 *d_psi, *d_lam;
     uint32_t *d_cnt;
     uint64_t *d_ticks;
-    char *d_scratch;
+    char *d_scratch = nullptr;
     if ((st = upload(b, &d_order, order.data(), count)) != QAOA_OK ||
         (st = upload(b, &d_n, n, count)) != QAOA_OK ||
         (st = upload(b, &d_eoff, edge_offsets, (size_t)count + 1)) != QAOA_OK ||
@@ -718,9 +718,17 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
         (st = upload<double2>(b, &d_lam, nullptr, (size_t)b->workgroups * slot)) != QAOA_OK ||
         (st = upload<double>(b, &d_cost, nullptr, (size_t)b->workgroups * slot)) != QAOA_OK ||
         (st = upload<uint32_t>(b, &d_cnt, nullptr, 2)) != QAOA_OK ||
-        (st = upload<uint64_t>(b, &d_ticks, nullptr, (size_t)count * 2)) != QAOA_OK ||
-        (st = upload<char>(b, &d_scratch, nullptr, scratch)) != QAOA_OK)
+        (st = upload<uint64_t>(b, &d_ticks, nullptr, (size_t)count * 2)) != QAOA_OK)
         return cleanup(st);
+    // The classes' sums and angles come on top of what the batch has always taken:
+    // without room for them every instance goes to the persistent launch.
+    if (b->nbig && hipMalloc((void **)&d_scratch, scratch) != hipSuccess) {
+        (void)hipGetLastError();
+        d_scratch = nullptr;
+        b->classes.clear();
+        b->nbig = 0;
+    }
+    if (d_scratch) b->allocs.push_back(d_scratch);
     qk::place_classes(b->classes, p, d_psi + small, d_lam + small, d_cost + small, d_scratch);
     A.count = count;
     A.begin = 0;

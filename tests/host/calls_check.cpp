@@ -167,6 +167,69 @@ void memory_checks()
     EXPECT(qaoa_create_maxcut(n, 1, e.data(), nullptr, QAOA_C128, nullptr, &h) == QAOA_ERR_OUT_OF_MEMORY);
 }
 
+// A batch of rings of the given sizes and one weight for all edges of each.
+struct Batch {
+    std::vector<int32_t> n, edges;
+    std::vector<int64_t> off{0};
+    std::vector<double> w;
+    qaoa_batch_options o{100, 0.05, 0.9, 0.999, 1e-8, 0, 10, 1, 0, {}, 0};
+    qaoa_batch b = nullptr;
+    Batch(const std::vector<int> &sizes, const std::vector<double> &weights)
+    {
+        for (size_t k = 0; k < sizes.size(); ++k) {
+            n.push_back(sizes[k]);
+            for (int i = 0; i < sizes[k]; ++i) {
+                edges.push_back(i);
+                edges.push_back((i + 1) % sizes[k]);
+                w.push_back(weights[k]);
+            }
+            off.push_back((int64_t)w.size());
+        }
+    }
+    qaoa_status create()
+    {
+        return qaoa_batch_create((int32_t)n.size(), n.data(), off.data(), edges.data(), w.data(), 2, &o, &b);
+    }
+    // the launches of one run from gamma = 0.3 everywhere
+    void run()
+    {
+        const std::vector<double> g(2 * n.size(), 0.3);
+        std::vector<double> og(g), ob(g);
+        fake().log.clear();
+        EXPECT(qaoa_batch_run(b, g.data(), g.data(), og.data(), ob.data(), nullptr, nullptr) == QAOA_OK);
+    }
+    ~Batch() { qaoa_batch_destroy(b); }
+};
+
+// A batch whose slots fit, but not what the size classes keep beside them, runs as
+// one persistent launch.
+void batch_without_class_scratch()
+{
+    const std::vector<int> sizes = {14, 13, 9};
+    const std::vector<double> w = {1.0, 1.0, 1.0};
+    size_t all = 0;
+    {
+        Batch b(sizes, w);
+        b.o.use_graph = 0;
+        b.o.steps = 1;
+        EXPECT(b.create() == QAOA_OK);
+        all = fake().taken;
+        b.run();
+        EXPECT(launches("k_many_adam") == 2 && launches("k_batch") == 1);
+    }
+    for (int graph : {0, 1}) {
+        Batch b(sizes, w);
+        b.o.use_graph = graph;
+        fake().budget = all - 1;
+        fake().log.clear();
+        EXPECT(b.create() == QAOA_OK);
+        EXPECT(graph == 0 || launches("k_batch") == 1);  // captured
+        b.run();
+        EXPECT(launches("k_many") == 0 && launches("k_batch") == (graph ? 0 : 1));
+    }
+    fake().budget = ~(size_t)0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -177,6 +240,7 @@ int main(int argc, char **argv)
         {"host_exports", host_exports},
         {"device_exports", device_exports},
         {"memory_checks", memory_checks},
+        {"batch_without_class_scratch", batch_without_class_scratch},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());

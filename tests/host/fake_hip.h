@@ -21,6 +21,7 @@ struct Fake {
     std::map<void *, size_t> live;                // device allocations
     size_t free_bytes = 1ull << 40;               // reported as free
     size_t largest = ~(size_t)0;                  // allocations above this fail
+    size_t budget = ~(size_t)0, taken = 0;        // bytes to be had and live
     bool pin_fails = false;
     int pins = 0, mallocs = 0, copies = 0;
     char *pinned = nullptr;                       // memory that a caller has pinned
@@ -127,16 +128,21 @@ hipError_t hipMalloc(void **p, size_t bytes)
 {
     ++fake().mallocs;
     *p = nullptr;
-    if (bytes > fake().largest) return hipErrorOutOfMemory;
+    if (bytes > fake().largest || bytes > fake().budget - fake().taken) return hipErrorOutOfMemory;
     uint8_t *q = (uint8_t *)std::malloc(bytes);
     for (size_t i = 0; i < bytes; ++i) q[i] = (uint8_t)(i * 37 + (i >> 8) * 11 + (i >> 16) * 5 + 1) & 0x3f;
     fake().live[q] = bytes;
+    fake().taken += bytes;
     *p = q;
     return hipSuccess;
 }
 hipError_t hipFree(void *p)
 {
-    EXPECT(!p || fake().live.erase(p) == 1);
+    if (!p) return hipSuccess;
+    const auto it = fake().live.find(p);
+    EXPECT(it != fake().live.end());
+    fake().taken -= it->second;
+    fake().live.erase(it);
     std::free(p);
     return hipSuccess;
 }
