@@ -453,6 +453,7 @@ struct qaoa_batch_s {
     hipStream_t streams[qk::kManyStreams] = {};
     hipEvent_t fork = nullptr, join[qk::kManyStreams] = {};
     double weight_bound = 0;  // largest sum of |weights| of an instance of the classes
+    double reach = 0;         // farthest an angle moves during a run (adam_reach)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool use_graph = true;
@@ -514,20 +515,36 @@ qaoa_status launch_resident(qaoa_batch b)
     return QAOA_OK;
 }
 
+// The farthest an angle can move in the batch's steps of Adam.  With r = b1^2 / b2,
+// Cauchy-Schwarz on the moment sums of step t bounds |m_t| / sqrt(v_t) by
+// (1 - b1) sqrt((1 - r^t) / ((1 - b2)(1 - r))), and the bias corrections multiply it
+// by sqrt(1 - b2^t) / (1 - b1^t).  (Defaults: 1 for t = 1, 7.3 for large t.)  Steps
+// beyond kSummed take the bound that falls with t.
+double adam_reach(const qk::BatchArgs &A)
+{
+    constexpr int kSummed = 4096;
+    if (A.steps == 0) return 0.0;
+    const double r = A.b2 > 0.0 ? A.b1 * A.b1 / A.b2 : 1.0, q = (1.0 - A.b2) * (1.0 - r);
+    if (!(q > 0.0)) return INFINITY;
+    double sum = 0.0, p1 = 1.0, p2 = 1.0, pr = 1.0;
+    for (int t = 1; t <= std::min(A.steps, kSummed); ++t) {
+        p1 *= A.b1;
+        p2 *= A.b2;
+        pr *= r;
+        sum += (1.0 - A.b1) / (1.0 - p1) * std::sqrt((1.0 - p2) * (1.0 - pr) / q);
+    }
+    if (A.steps > kSummed) sum += (A.steps - kSummed) * (1.0 - A.b1) / (1.0 - p1) / std::sqrt(q);
+    return A.lr * sum;
+}
+
 // Whether a phase |gamma C| of the size classes could leave the fast
-// reduction's range during a run from gamma0.  A step of Adam moves an angle
-// by at most lr / sqrt((1 - b2)(1 - b1^2 / b2)): Cauchy-Schwarz on the moment
-// sums, and the bias corrections only make it smaller.
+// reduction's range during a run from gamma0.
 bool far_phases(qaoa_batch b, const double *gamma0)
 {
-    const qk::BatchArgs &A = b->args;
-    const double q = A.b2 > 0.0 ? (1.0 - A.b2) * (1.0 - A.b1 * A.b1 / A.b2) : 0.0;
-    if (!(q > 0.0) && A.steps > 0) return true;
     double g = 0.0;
     for (int k = 0; k < b->nbig; ++k)
         for (int l = 0; l < b->p; ++l) g = std::max(g, std::fabs(gamma0[(size_t)b->order[k] * b->p + l]));
-    if (A.steps > 0) g += A.steps * A.lr / std::sqrt(q);
-    return !(g * b->weight_bound < qk::near_phase_limit(false));
+    return !((g + b->reach) * b->weight_bound < qk::near_phase_limit(false));
 }
 
 // The streamed instances of a run: the size classes on their streams beside the
@@ -757,6 +774,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     A.cost = d_cost;
     A.slot = slot;
     A.counter = d_cnt;
+    b->reach = adam_reach(A);
     b->args_res = A;
     b->args_res.begin = b->split;
     b->args_res.end = count;

@@ -3,6 +3,9 @@
 #include "fake_hip.h"
 #include "qaoa.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace {
 
 const double kGamma[3] = {0.2, 0.3, 0.4}, kBeta[3] = {0.6, 0.5, 0.4};
@@ -230,6 +233,37 @@ void batch_without_class_scratch()
     fake().budget = ~(size_t)0;
 }
 
+// What `steps` steps of Adam can move an angle by at most.
+double reach(const qaoa_batch_options &o)
+{
+    double s = 0.0;
+    const double r = o.beta1 * o.beta1 / o.beta2;
+    for (int t = 1; t <= o.steps; ++t)
+        s += o.lr * (1 - o.beta1) / (1 - std::pow(o.beta1, t)) *
+             std::sqrt((1 - std::pow(o.beta2, t)) * (1 - std::pow(r, t)) / ((1 - o.beta2) * (1 - r)));
+    return s;
+}
+
+// Instances run in their size class while |gamma| sum|w| stays below 5e5 over the
+// start angle 0.3 and all that Adam can add.
+void batch_phase_bound()
+{
+    for (int steps : {0, 1, 100, 4096, 6000}) {
+        for (double side : {0.99, 1.001}) {
+            Batch b({14}, {0.0});
+            b.o.steps = steps;
+            b.o.lr = 1e-3;
+            const double weight = side * 5e5 / (0.3 + reach(b.o)) / 14;
+            std::fill(b.w.begin(), b.w.end(), weight);
+            EXPECT(b.create() == QAOA_OK);
+            b.run();
+            EXPECT(launches("k_many_adam") == (side < 1.0 ? steps : 0));
+            EXPECT(launches("k_many_final") == (side < 1.0 ? 1 : 0));
+            EXPECT((launches("k_batch") > 0) == (side > 1.0));
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -241,6 +275,7 @@ int main(int argc, char **argv)
         {"device_exports", device_exports},
         {"memory_checks", memory_checks},
         {"batch_without_class_scratch", batch_without_class_scratch},
+        {"batch_phase_bound", batch_phase_bound},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());
