@@ -314,8 +314,9 @@ qaoa_status qaoa_pass_plan(int32_t n, int32_t precision, int32_t cap, int32_t *n
  * every pass of a step is one launch over the tiles of all of them, and the
  * sizes run side by side on streams of the batch.  For the others a fixed grid
  * of workgroups takes instances from an on-device queue, largest n first, and a
- * workgroup runs one instance start to end.  (Larger ones join that queue in a
- * run whose phases |gamma C| could leave the fast reduction's range, 5e5.)
+ * workgroup runs one instance start to end.  (Sizes of which an instance's phases
+ * |gamma C| could leave the fast reduction's range, 5e5, during a run take such a
+ * queue after the other sizes.)
  * The vectors live in `workgroups` scratch slots of 2^nmax amplitudes (state,
  * adjoint vector and cost diagonal, complex128).  An instance's run is its
  * cost diagonal (as qaoa_create_maxcut), then `steps` Adam ascent steps on

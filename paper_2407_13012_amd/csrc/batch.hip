@@ -3,8 +3,8 @@
 //
 // Instances of more than one tile (n > 12) run in lockstep, all of one size
 // together (batch_many.hip).  The others, one tile each, run in the persistent
-// launch below, which also takes every instance of a run whose phases could
-// leave the fast reduction's range (far_phases).  A fixed grid of workgroups pops instances from a work queue (largest n
+// launch below, which also takes the sizes of which a run's phases could leave the
+// fast reduction's range (mark_far).  A fixed grid of workgroups pops instances from a work queue (largest n
 // first).  A workgroup owns one instance at a time and runs everything for it
 // in its own scratch slot: the cost diagonal (Sec. IV-A, cut indicator per
 // edge), then for every Adam step one expectation + adjoint gradient (the
@@ -452,7 +452,7 @@ struct qaoa_batch_s {
     std::vector<qk::SizeClass> classes;
     hipStream_t streams[qk::kManyStreams] = {};
     hipEvent_t fork = nullptr, join[qk::kManyStreams] = {};
-    double weight_bound = 0;  // largest sum of |weights| of an instance of the classes
+    std::vector<double> weight_sum;  // of |weights|, of the classes' instances (in processing order)
     double reach = 0;         // farthest an angle moves during a run (adam_reach)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -487,16 +487,17 @@ qaoa_status upload(qaoa_batch b, T **dst, const T *src, size_t count)
     return QAOA_OK;
 }
 
-// The persistent launch over order[begin, split).
-qaoa_status launch_streamed(qaoa_batch b, int begin)
+// The persistent launch over order[begin, end), in slots of `slot` amplitudes.
+qaoa_status launch_streamed(qaoa_batch b, int begin, int end, uint64_t slot)
 {
     hipLaunchKernelGGL(qk::k_reset, dim3(1), dim3(1), 0, b->stream, b->args.counter);
     BCHECK(b, hipGetLastError());
-    if (b->split > begin) {
-        const dim3 grid(std::min(b->workgroups, b->split - begin));
+    if (end > begin) {
+        const dim3 grid(std::min(b->workgroups, end - begin));
         qk::BatchArgs A = b->args;
         A.begin = begin;
-        if (begin > 0) A.slot = 1ull << qk::kTileBits;  // one-tile instances, beside the size classes
+        A.end = end;
+        A.slot = slot;
         if (b->wpe == 2) hipLaunchKernelGGL(qk::k_batch<2>, grid, dim3(qk::kThreads), 0, b->stream, A);
         else hipLaunchKernelGGL(qk::k_batch<1>, grid, dim3(qk::kThreads), 0, b->stream, A);
         BCHECK(b, hipGetLastError());
@@ -537,30 +538,44 @@ double adam_reach(const qk::BatchArgs &A)
     return A.lr * sum;
 }
 
-// Whether a phase |gamma C| of the size classes could leave the fast
-// reduction's range during a run from gamma0.
-bool far_phases(qaoa_batch b, const double *gamma0)
+// Marks the size classes of which an instance's phases |gamma C| could leave the
+// fast reduction's range during a run from gamma0; whether there are others.
+bool mark_far(qaoa_batch b, const double *gamma0)
 {
-    double g = 0.0;
-    for (int k = 0; k < b->nbig; ++k)
-        for (int l = 0; l < b->p; ++l) g = std::max(g, std::fabs(gamma0[(size_t)b->order[k] * b->p + l]));
-    return !((g + b->reach) * b->weight_bound < qk::near_phase_limit(false));
+    bool near = false;
+    for (qk::SizeClass &c : b->classes) {
+        c.far = false;
+        for (int k = c.begin; k < c.begin + c.count; ++k) {
+            double g = 0.0;
+            for (int l = 0; l < b->p; ++l) g = std::max(g, std::fabs(gamma0[(size_t)b->order[k] * b->p + l]));
+            if (!((g + b->reach) * b->weight_sum[k] < qk::near_phase_limit(false))) c.far = true;
+        }
+        near = near || !c.far;
+    }
+    return near;
 }
 
-// The streamed instances of a run: the size classes on their streams beside the
-// small instances on the batch's own.
-qaoa_status launch_classes(qaoa_batch b)
+// The streamed instances of a run.  The size classes run on their streams beside
+// the one-tile instances on the batch's own; classes marked far take the persistent
+// launch after them, in whole slots, which overlap the other classes' vectors.
+qaoa_status launch_all(qaoa_batch b, const double *gamma0)
 {
+    const uint64_t slot = b->args.slot;
+    if (!mark_far(b, gamma0)) return launch_streamed(b, 0, b->split, slot);
     BCHECK(b, hipEventRecord(b->fork, b->stream));
     for (hipStream_t s : b->streams) BCHECK(b, hipStreamWaitEvent(s, b->fork, 0));
     BCHECK(b, qk::run_classes(b->classes, b->args, b->streams));
-    return QAOA_OK;
-}
-qaoa_status join_classes(qaoa_batch b)
-{
+    qaoa_status st = launch_streamed(b, b->nbig, b->split, 1ull << qk::kTileBits);
+    if (st != QAOA_OK) return st;
     for (int k = 0; k < qk::kManyStreams; ++k) {
         BCHECK(b, hipEventRecord(b->join[k], b->streams[k]));
         BCHECK(b, hipStreamWaitEvent(b->stream, b->join[k], 0));
+    }
+    for (size_t k = 0; k < b->classes.size(); ++k) {
+        if (!b->classes[k].far) continue;
+        const int begin = b->classes[k].begin;
+        while (k + 1 < b->classes.size() && b->classes[k + 1].far) ++k;
+        if ((st = launch_streamed(b, begin, b->classes[k].begin + b->classes[k].count, slot)) != QAOA_OK) return st;
     }
     return QAOA_OK;
 }
@@ -604,7 +619,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     const int64_t E = edge_offsets[count];
     if (E > 0 && !edges) return bfail(QAOA_ERR_INVALID_ARGUMENT, "edges is NULL");
     std::vector<double> scale(count, 1.0);
-    double weight_bound = 0.0;
+    std::vector<double> sums(count, 0.0);
     for (int i = 0; i < count; ++i) {
         double s = 0.0;
         for (int64_t k = edge_offsets[i]; k < edge_offsets[i + 1]; ++k) {
@@ -616,7 +631,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
             s += std::fabs(wk);
         }
         if (s > 0.0) scale[i] = 1.0 / s;
-        if (n[i] > qk::kTileBits) weight_bound = std::max(weight_bound, s);
+        sums[i] = s;
     }
 
     qaoa_batch b = new (std::nothrow) qaoa_batch_s();
@@ -628,7 +643,6 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     b->use_graph = o.use_graph != 0;
     b->wpe = o.waves_per_simd == 2 ? 2 : 1;
     b->resident_max_n = o.resident_max_n;
-    b->weight_bound = weight_bound;
     auto cleanup = [&](qaoa_status st) {
         std::string keep = qk::error_message();
         qaoa_batch_destroy(b);
@@ -698,7 +712,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     // The slots hold `workgroups` whole states of the largest size.  The small
     // instances use the start of theirs, packed at one tile each, the size
     // classes what lies behind.
-    while (b->nbig < count && n[order[b->nbig]] > qk::kTileBits) ++b->nbig;
+    while (b->nbig < count && n[order[b->nbig]] > qk::kTileBits) b->weight_sum.push_back(sums[order[b->nbig++]]);
     const uint64_t small = (uint64_t)b->workgroups << qk::kTileBits;
     size_t scratch = 0;
     try {
@@ -785,7 +799,7 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
     if (b->use_graph && !b->nbig) {
         if (hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return cleanup(bfail(QAOA_ERR_DEVICE, "graph capture failed"));
-        st = launch_streamed(b, 0);
+        st = launch_streamed(b, 0, b->split, slot);
         if (st == QAOA_OK) st = launch_resident(b);
         hipGraph_t gr = nullptr;
         const hipError_t e = hipStreamEndCapture(b->stream, &gr);
@@ -829,10 +843,7 @@ qaoa_status qaoa_batch_run(qaoa_batch b, const double *gamma0, const double *bet
     if (b->exec) {
         BCHECK(b, hipGraphLaunch(b->exec, b->stream));
     } else {
-        const bool classes = b->nbig && !far_phases(b, gamma0);
-        if (classes) st = launch_classes(b);
-        if (st == QAOA_OK) st = launch_streamed(b, classes ? b->nbig : 0);
-        if (st == QAOA_OK && classes) st = join_classes(b);
+        st = launch_all(b, gamma0);
         if (st == QAOA_OK) st = launch_resident(b);
         if (st != QAOA_OK) return st;
     }

@@ -43,6 +43,7 @@ struct SizeClass {
     int begin = 0, count = 0;  // range of the processing order
     int cap = 0;               // instances at a time
     int stream = 0;
+    bool far = false;          // this run's phases may leave the fast range: not run here
     uint64_t M = 0, T = 0;     // stored amplitudes and tiles per instance
     int quad = 0;              // tile bits of the small-tile sweeps (0: the large tiles)
     std::vector<Geometry> geo; // folded passes of one layer
@@ -61,7 +62,7 @@ std::vector<SizeClass> make_classes(const std::vector<int32_t> &order, const int
                                     uint64_t amps, const std::vector<std::vector<PassPlan>> &plans, const int *depth, size_t *scratch);
 // Carves the classes' vectors (from psi, lam, cost) and small buffers (from scratch).
 void place_classes(std::vector<SizeClass> &cls, int p, double2 *psi, double2 *lam, double *cost, void *scratch);
-// Enqueues the whole optimisation of the classes on the kManyStreams streams.
+// Enqueues the whole optimisation of the classes not marked far on the kManyStreams streams.
 hipError_t run_classes(const std::vector<SizeClass> &cls, const BatchArgs &B, hipStream_t *streams);
 
 }  // namespace qk

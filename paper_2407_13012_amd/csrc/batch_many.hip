@@ -363,7 +363,7 @@ hipError_t run_classes(const std::vector<SizeClass> &cls, const BatchArgs &B, hi
         any = false;
         for (int s = 0; s < kManyStreams; ++s) {
             At &a = at[s];
-            while (a.k < cls.size() && cls[a.k].stream != s) ++a.k;
+            while (a.k < cls.size() && (cls[a.k].stream != s || cls[a.k].far)) ++a.k;
             if (a.k == cls.size()) continue;
             any = true;
             const SizeClass &c = cls[a.k];

@@ -193,10 +193,11 @@ struct Batch {
     {
         return qaoa_batch_create((int32_t)n.size(), n.data(), off.data(), edges.data(), w.data(), 2, &o, &b);
     }
-    // the launches of one run from gamma = 0.3 everywhere
-    void run()
+    // the launches of one run from these gammas (both layers), 0.3 where none is given
+    void run(std::vector<double> gamma = {})
     {
-        const std::vector<double> g(2 * n.size(), 0.3);
+        std::vector<double> g;
+        for (size_t k = 0; k < n.size(); ++k) g.insert(g.end(), 2, k < gamma.size() ? gamma[k] : 0.3);
         std::vector<double> og(g), ob(g);
         fake().log.clear();
         EXPECT(qaoa_batch_run(b, g.data(), g.data(), og.data(), ob.data(), nullptr, nullptr) == QAOA_OK);
@@ -264,6 +265,37 @@ void batch_phase_bound()
     }
 }
 
+// Only the sizes of which an instance's own phases may leave the range go to the
+// persistent launch, neighbours in size together, after the other sizes.
+void batch_far_sizes()
+{
+    const double heavy = 1e6;
+    const struct {
+        std::vector<int> n;
+        std::vector<double> w, gamma;
+        int classes, queues;  // size classes run, persistent launches
+    } cases[] = {
+        {{16, 15, 14, 9}, {1, heavy, 1, 1}, {}, 2, 2},       // one-tile, then n = 15
+        {{16, 15, 14, 9}, {heavy, heavy, 1, 1}, {}, 1, 2},   // 16 and 15 in one launch
+        {{16, 15, 14, 9}, {heavy, 1, heavy, 1}, {}, 1, 3},
+        {{16, 15, 14, 9}, {heavy, heavy, heavy, 1}, {}, 0, 1},  // all in one launch
+        {{15, 14, 15}, {1, 1, heavy}, {}, 1, 1},             // a size with one such instance
+        {{15, 14}, {heavy, 1}, {1e-9, 1e3}, 2, 0},           // its own angles count
+    };
+    for (const auto &c : cases) {
+        Batch b(c.n, c.w);
+        b.o.steps = c.gamma.empty() ? 2 : 0;
+        b.o.use_graph = 0;
+        EXPECT(b.create() == QAOA_OK);
+        for (int rep = 0; rep < 2; ++rep) {
+            b.run(c.gamma);
+            EXPECT(launches("k_many_final") == c.classes && launches("k_batch") == c.queues);
+            b.run({1e12, 1e12, 1e12, 1e12});  // every size
+            EXPECT(launches("k_many") == 0 && launches("k_batch") == 1);
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -276,6 +308,7 @@ int main(int argc, char **argv)
         {"memory_checks", memory_checks},
         {"batch_without_class_scratch", batch_without_class_scratch},
         {"batch_phase_bound", batch_phase_bound},
+        {"batch_far_sizes", batch_far_sizes},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());

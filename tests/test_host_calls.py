@@ -29,7 +29,8 @@ def checks(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name", ["pinned_results", "pinning_refused", "host_exports", "device_exports", "memory_checks",
-                                  "batch_without_class_scratch", "batch_phase_bound"])
+                                  "batch_without_class_scratch", "batch_phase_bound",
+                                  "batch_far_sizes"])
 def test_host_calls(checks, name):
     out = subprocess.run([checks, name], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and f"{name} ok" in out.stdout, out.stdout + out.stderr
