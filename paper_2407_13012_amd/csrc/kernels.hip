@@ -528,6 +528,15 @@ __global__ __launch_bounds__(kThreads) void k_scan_final(const double *in, uint6
     }
 }
 
+// What lanes of a wave wrote to LDS before it, the others read after it, and the
+// other way round.
+__device__ __forceinline__ void wave_exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // W shots per wave (grid-stride), a lane each: u -> target t = u * total, binary search
 // over the sub-block prefix, then a sequential scan inside the sub-block for the first
 // z whose cumulative mass exceeds t.  A zero-probability z never satisfies the
@@ -586,7 +595,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
                     m[k * 8 + row][8 * i + sub] = fine[stored((zr[k] >> 4) + 8 * i + sub, N >> 4, folded)];
-            __builtin_amdgcn_wave_barrier();
+            wave_exchange();
             double under = acc;  // the sum before the run, then before the amplitude
             uint32_t run = 0;
             if (!found) {
@@ -598,14 +607,14 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
                     run += sum <= t ? 1u : 0u;
                 }
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_exchange();
 #pragma unroll
             for (int k = 0; k < kRows; ++k) {
                 const uint64_t zb = zr[k] + 16 * min((uint32_t)__shfl((int)run, k * 8 + row), 15u);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) m[k * 8 + row][8 * i + sub] = norm2(psi[stored(zb + 8 * i + sub, N, folded)]);
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_exchange();
             if (!found) {
                 double sum = under, over = t;
                 uint32_t in = 0;
@@ -620,7 +629,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
                 found = run < 16 && in < 16 && over > t + eps && under < t - eps;
                 before = found ? 16 * run + in : 0u;
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_exchange();
         }
         for (uint64_t d = 0; d < sb; d += kStep) {
             const uint64_t open = __ballot(!found);
@@ -636,7 +645,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
                 if ((open >> ((k % kRows) * 8 + row)) & 1ull)
                     m[(k % kRows) * 8 + row][e] = d + e < sb ? norm2(v[k]) : 0.0;
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_exchange();
             if (!found) {
 #pragma unroll
                 for (int r = 0; r < kStep; ++r) {
@@ -645,7 +654,7 @@ __global__ __launch_bounds__(kThreads) void k_shots(const typename Tr<R>::V *psi
                 }
                 found = acc > t;
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_exchange();
         }
         uint64_t zsel = z0 + before;
         if (!found) {
