@@ -306,9 +306,8 @@ qaoa_status qaoa_pass_plan(int32_t n, int32_t precision, int32_t cap, int32_t *n
 
 /*
  * Batched engine: many small weighted MaxCut instances, each optimised with
- * Adam on its 2p angles, in one persistent launch (Sec. V-B: parameter
- * optimisation driven by the simulator's gradients; here every instance's loop
- * runs on the device).
+ * Adam on its 2p angles (Sec. V-B: parameter optimisation driven by the
+ * simulator's gradients; here every instance's loop runs on the device).
  *
  * Instances of more than 12 qubits run by size, all of one size in lockstep:
  * every pass of a step is one launch over the tiles of all of them, and the

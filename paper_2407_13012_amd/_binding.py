@@ -696,7 +696,9 @@ class QaoaHandle:
 
 class QaoaBatch:
     """Owning wrapper of a batched-engine object (qaoa_batch_*): many MaxCut
-    instances optimised with on-device Adam in one persistent launch."""
+    instances optimised with on-device Adam, those of more than 12 qubits by size in
+    lockstep, the others in a persistent launch (a captured graph when there are only
+    those)."""
 
     def __init__(self, graphs, p: int, **options):
         self.count = len(graphs)

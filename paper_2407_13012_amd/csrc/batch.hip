@@ -12,7 +12,8 @@
 // tiles of a pass processed in order by the workgroup) and the Adam update of
 // the 2p angles, and finally E at the optimised angles.  Every wave reaches
 // the end of the queue, so the launch always drains.  The queue counter is
-// reset by a kernel, and the pair (reset, engine) is captured in a hipGraph.
+// reset by a kernel, and for a batch without size classes the pair (reset, engine) is
+// captured in a hipGraph.
 #include "qaoa.h"
 #include "batch_internal.h"
 #include "tile_device.h"
