@@ -12,7 +12,7 @@ roofline of the dominant kernel (HIP events bracketing every pass launch on the
 library's stream, divided into the pass's algorithmic bytes) and the CPU
 oracle's throughput on a bounded sample of the same workload.  Under "extra":
 the complex64 variant, 10^6-shot sampling, the batched engine on 4096 graphs of
-n ~ U{10..20} (p = 4, 100 Adam steps each, one persistent launch), and the
+n ~ U{10..20} (p = 4, 100 Adam steps each), and the
 time-to-ratio of learned versus linear-ramp starts on held-out ER(24, 0.5)
 graphs (p = 8, a sample of the evaluation set).
 """
@@ -123,7 +123,7 @@ def copy_ceiling(gib: float) -> float:
 def small_workloads() -> dict:
     """The two smaller configurations: E+G latency of the n=12, p=2 MaxCut and
     E+G time of the n=26 3-regular weighted MaxCut (p=6) in both precisions,
-    the latter against its byte model (P_min = 2)."""
+    the latter against its byte model (P_min = 2) over the amplitudes it keeps."""
     import torch
 
     import qaoa_inputs as qi
@@ -147,9 +147,15 @@ def small_workloads() -> dict:
                 q.gradient(w["gamma"], w["beta"])
             dt = (time.perf_counter() - t0) / 10
         out[f"regular26_p6_{prec}_grad_ms"] = dt * 1e3
-        out[f"regular26_p6_{prec}_model_roofline_frac"] = (model_bytes_per_amp(26, 6, s, c) * 2.0 ** 26 / dt
-                                                           / (HBM_PEAK_GBS * 1e9))
+        out[f"regular26_p6_{prec}_model_roofline_frac"] = (model_bytes_per_amp(26, 6, s, c) * stored_amplitudes(26, s)
+                                                           / dt / (HBM_PEAK_GBS * 1e9))
     return out
+
+
+def stored_amplitudes(n: int, s: int = 16) -> float:
+    """Amplitudes (of s bytes) that a MaxCut state keeps and sweeps: half of them when it
+    is more than one tile, as C(z) = C(~z)."""
+    return 2.0 ** (n - 1 if n > (12 if s == 16 else 13) else n)
 
 
 def batch_bytes_per_amp(n: int, p: int, kmax: int = 10) -> float:
@@ -173,9 +179,46 @@ def batch_bytes_per_amp(n: int, p: int, kmax: int = 10) -> float:
     return fwd + (2 * s + c) + bwd
 
 
+def batch_step_bytes(n: int, p: int, kmax: int = 10, resident_max_n: int = 0) -> float:
+    """Algorithmic bytes of one instance's E+G in the batched engine.  An LDS-resident
+    instance moves only its cost entries.  Above one tile the state is folded, the last
+    backward sweep makes phi from the cost entries and, unless the turn is the sweep
+    before it, that one does not store phi (16 bytes each)."""
+    if n <= resident_max_n:
+        return 8.0 * (2 * p - 1) * 2.0 ** n
+    per_amp = batch_bytes_per_amp(n, p, kmax)
+    if n > 12:
+        P = 1 + -(-(n - 12) // kmax)
+        per_amp -= 16 * (2 if p > 1 or P > 2 else 1)
+    return per_amp * stored_amplitudes(n)
+
+
+def launch_loads(ns, which, t_start, t_end, workgroups: int, cus: int) -> dict:
+    """How evenly the workgroups of the persistent launches are loaded, from the
+    timeline: each of their instances has one workgroup to itself.  Instances of more
+    than 12 qubits run side by side by size, so only their span is given."""
+    import numpy as np
+    out = {}
+    for name, sel, grid in (("size_classes", (which == 0) & (ns > 12), None),
+                            ("streamed", (which == 0) & (ns <= 12), workgroups),
+                            ("resident", which == 1, min(cus, workgroups))):
+        if not np.any(sel):
+            continue
+        span = float(t_end[sel].max() - t_start[sel].min())
+        out[name] = {"instances": int(sel.sum()), "span_s": span, "first_start_s": float(t_start[sel].min())}
+        if grid is not None:
+            grid = min(grid, int(sel.sum()))
+            busy = float(np.sum(t_end[sel] - t_start[sel]))
+            out[name].update(workgroups=grid, busy_fraction=busy / (grid * span) if span > 0 else None)
+    big = ns == ns.max()
+    out["largest_n"] = {"n": int(ns.max()), "mean_s": float(np.mean(t_end[big] - t_start[big])),
+                        "last_end_s": float(t_end[big].max())}
+    return out
+
+
 def batch_leg(count: int, p: int, steps: int, log) -> dict:
     """The batched engine on the n ~ U{10..20} MaxCut family: `count` graphs,
-    depth p, `steps` Adam steps each, all in one persistent launch."""
+    depth p, `steps` Adam steps each."""
     import numpy as np
     import torch
 
@@ -199,27 +242,11 @@ def batch_leg(count: int, p: int, steps: int, log) -> dict:
     ns = np.array([g.n for g in graphs])
     kmax = {int(k): int(v) for k, v in choice["group_by_n"].items()}
     amps = float(np.sum(2.0 ** ns))
-    res_n = opts["resident_max_n"]
-    # LDS-resident instances move only their cost entries through memory
-    algo = sum((8.0 * (2 * p - 1) if n <= res_n else batch_bytes_per_amp(int(n), p, kmax.get(int(n), 10)))
-               * 2.0 ** n for n in ns) * steps
+    algo = sum(batch_step_bytes(int(n), p, kmax.get(int(n), 10), opts["resident_max_n"]) for n in ns) * steps
     evals = count * steps
     log(f"[bench] batch {count} graphs x {steps} steps: {dt:.2f} s ({evals / dt:.0f} E+G/s)")
     cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
-    launches = {}
-    for k, name in ((0, "streamed"), (1, "resident")):
-        sel = which == k
-        if not np.any(sel):
-            continue
-        grid = min(opts["workgroups"], int(sel.sum())) if k == 0 else min(cus, opts["workgroups"], int(sel.sum()))
-        span = float(t_end[sel].max() - t_start[sel].min())
-        busy = float(np.sum(t_end[sel] - t_start[sel]))
-        launches[name] = {"instances": int(sel.sum()), "workgroups": grid, "span_s": span,
-                          "busy_fraction": busy / (grid * span) if span > 0 else None,
-                          "first_start_s": float(t_start[sel].min())}
-    big = ns == ns.max()
-    launches["largest_n"] = {"n": int(ns.max()), "mean_s": float(np.mean(t_end[big] - t_start[big])),
-                             "last_end_s": float(t_end[big].max())}
+    launches = launch_loads(ns, which, t_start, t_end, opts["workgroups"], cus)
     return {
         "graphs": count, "p": p, "adam_steps": steps, "seconds": dt,
         "grad_evals_per_s": evals / dt,
