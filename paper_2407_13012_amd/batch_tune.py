@@ -1,22 +1,27 @@
 """Autotuner and dataset driver for the batched engine (qaoa_batch_*).
 
-The engine's launch is shaped by a few knobs that only measurement can settle
-on a given device:
+The engine's launches are shaped by a few knobs that only measurement can settle
+on a given device.  Instances of more than 12 qubits run by size, all of one size
+in lockstep; those of one tile, and sizes whose phases could leave the fast range
+(with any number of tiles), in persistent launches of one workgroup per instance:
 
 * the fusion depth of the mixer passes per qubit count n (``group_by_n``):
   a layer of an n-qubit instance, n > 12, is applied as one low pass of 12
   qubits plus ceil((n - 12) / k) high passes of at most k qubits each, so
-  smaller k means more, narrower passes over the slot;
-* the register budget of the engine kernel (``waves_per_simd``, 1 or 2);
-* the number of persistent workgroups (``workgroups``);
+  smaller k means more, narrower passes; a depth that allows the two passes of
+  the small tiles lets a size of few amplitudes run on those;
+* the number of scratch slots (``workgroups``), which is the persistent launch's
+  grid and, as the sizes share the slots' memory, how many instances of a size
+  run at a time;
+* the register budget of the persistent launch's kernel (``waves_per_simd``, 1 or 2);
 * the largest n run LDS-resident (``resident_max_n``, 0 or 12): instances of
   at most 12 qubits are one tile, and may either stream through their slot
-  between passes within the main launch or keep both vectors in LDS in a
+  between passes within the persistent launch or keep both vectors in LDS in a
   second launch of one workgroup per compute unit.
 
 ``tune`` times short runs of the actual batch (a couple of Adam steps per
 instance) over these candidates, keeps the fastest, and caches the choice in a
-JSON file keyed by the device and the batch's size histogram and depth.
+JSON file keyed by the device, the engine and the batch's size histogram and depth.
 All arithmetic runs in the HIP library; this module only picks options, times
 calls and moves results.
 """
@@ -35,6 +40,9 @@ from ._binding import QaoaBatch, QaoaHandle
 HERE = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_CACHE = os.path.join(HERE, "tuning", "batch_mi355x.json")
 DEPTHS = (4, 6, 8, 10)
+# Part of the cache key: choices measured on an engine that launched otherwise do
+# not hold.  Raised with every change of how instances are launched.
+ENGINE = 2
 
 
 def device_key() -> str:
@@ -74,7 +82,7 @@ def tune(graphs: Sequence, p: int, cache: Optional[str] = DEFAULT_CACHE, probe_s
     timings that chose it under "measured"."""
     import torch
     log = log or (lambda *a: None)
-    dkey, bkey = device_key(), batch_key(graphs, p)
+    dkey, bkey = f"{device_key()}|engine{ENGINE}", batch_key(graphs, p)
     table = {}
     if cache and os.path.exists(cache):
         with open(cache) as fh:
