@@ -1253,11 +1253,12 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     if (st != QAOA_OK) return st;
     const size_t base = 2 * nsub + 1 + nscr + nfine;
     if ((st = ensure_results(h, 1)) != QAOA_OK) return st;
-    if (h->pin && !h->scanned) HIPCHECK(h, hipEventCreateWithFlags(&h->scanned, hipEventDisableTiming));
+    const bool wait_total = h->pin && out_is_device;
+    if (wait_total && !h->scanned) HIPCHECK(h, hipEventCreateWithFlags(&h->scanned, hipEventDisableTiming));
     double *sub = h->parts, *pre = sub + nsub, *scr = pre + nsub + 1, *fine = nfine ? scr + nscr : nullptr;
     HIPCHECK(h, qk::launch_submass(c64(h), h->psi, h->n, h->fold, sbits, sub, fine, h->stream));
     HIPCHECK(h, qk::launch_exclusive_scan(sub, nsub, pre, scr, results(h), h->stream));
-    if (h->pin) HIPCHECK(h, hipEventRecord(h->scanned, h->stream));
+    if (wait_total) HIPCHECK(h, hipEventRecord(h->scanned, h->stream));
     uint64_t *dz = z;
     double *dc = cost;
     if (!out_is_device) {
@@ -1266,9 +1267,10 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     }
     HIPCHECK(h, qk::launch_shots(c64(h), h->psi, h->cost, h->n, h->fold, sbits, pre, nsub, fine, shots, seed, dz,
                                  dc, h->stream));
-    // the shots run while the total is waited for; without norm they write nothing
+    // The shots run while the total is waited for; without norm they write nothing.
+    // Host outputs wait for the shots anyway: then the stream is waited for.
     double T = 0;
-    if (h->pin) {
+    if (wait_total) {
         HIPCHECK(h, hipEventSynchronize(h->scanned));
         T = h->pin[0];
     } else if ((st = collect(h, 1, &T)) != QAOA_OK) {

@@ -170,6 +170,24 @@ void memory_checks()
     EXPECT(qaoa_create_maxcut(n, 1, e.data(), nullptr, QAOA_C128, nullptr, &h) == QAOA_ERR_OUT_OF_MEMORY);
 }
 
+// Shots to device memory return once the total is known, while they run: an event
+// behind the scan.  Shots to host memory wait for the stream, with no event.
+void sample_waits()
+{
+    qaoa_handle h = ring(14);
+    for (int k = 0; k < 4; ++k) gradient(h);
+    double E, cost[8];
+    uint64_t z[8];
+    EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK);
+    for (int device = 0; device < 2; ++device) {
+        fake().log.clear();
+        EXPECT(qaoa_sample(h, 8, 1, z, cost, device) == QAOA_OK);
+        EXPECT(launches("event") == device && launches("k_shots") == 1);
+        if (device) EXPECT(fake().log[fake().log.size() - 2] == "event");
+    }
+    qaoa_destroy(h);
+}
+
 // A batch of rings of the given sizes and one weight for all edges of each.
 struct Batch {
     std::vector<int32_t> n, edges;
@@ -306,6 +324,7 @@ int main(int argc, char **argv)
         {"host_exports", host_exports},
         {"device_exports", device_exports},
         {"memory_checks", memory_checks},
+        {"sample_waits", sample_waits},
         {"batch_without_class_scratch", batch_without_class_scratch},
         {"batch_phase_bound", batch_phase_bound},
         {"batch_far_sizes", batch_far_sizes},

@@ -80,6 +80,7 @@ inline void run_kernel(const std::string &name, void **args)
     const bool w16 = name.find("HIP_vector_type") != std::string::npos, w8 = name.find("Im") != std::string::npos;
     if (name.find("k_reverse") != std::string::npos) w16 ? host_reverse<Entry16>(args) : host_reverse<uint64_t>(args);
     if (name.find("k_unfold_words") != std::string::npos) w16 ? host_unfold<Entry16>(args) : w8 ? host_unfold<uint64_t>(args) : host_unfold<uint32_t>(args);
+    if (name.find("k_scan_final") != std::string::npos) **(double **)args[5] = 1.0;  // the total
     if (name.find("k_unfold_widen") != std::string::npos) {
         const float *in = *(const float **)args[0];
         const uint64_t half = *(uint64_t *)args[1];
@@ -258,7 +259,11 @@ hipError_t hipEventDestroy(hipEvent_t e)
     std::free((void *)e);
     return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t)
+{
+    fake().log.push_back("event");
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t)
 {
