@@ -451,6 +451,7 @@ struct qaoa_batch_s {
     // order[0, nbig): more than one tile each, run by size class on their own streams
     int nbig = 0;
     std::vector<qk::SizeClass> classes;
+    int nstreams = 0;
     hipStream_t streams[qk::kManyStreams] = {};
     hipEvent_t fork = nullptr, join[qk::kManyStreams] = {};
     std::vector<double> weight_sum;  // of |weights|, of the classes' instances (in processing order)
@@ -564,11 +565,11 @@ qaoa_status launch_all(qaoa_batch b, const double *gamma0)
     const uint64_t slot = b->args.slot;
     if (!mark_far(b, gamma0)) return launch_streamed(b, 0, b->split, slot);
     BCHECK(b, hipEventRecord(b->fork, b->stream));
-    for (hipStream_t s : b->streams) BCHECK(b, hipStreamWaitEvent(s, b->fork, 0));
+    for (int k = 0; k < b->nstreams; ++k) BCHECK(b, hipStreamWaitEvent(b->streams[k], b->fork, 0));
     BCHECK(b, qk::run_classes(b->classes, b->args, b->streams));
     qaoa_status st = launch_streamed(b, b->nbig, b->split, 1ull << qk::kTileBits);
     if (st != QAOA_OK) return st;
-    for (int k = 0; k < qk::kManyStreams; ++k) {
+    for (int k = 0; k < b->nstreams; ++k) {
         BCHECK(b, hipEventRecord(b->join[k], b->streams[k]));
         BCHECK(b, hipStreamWaitEvent(b->stream, b->join[k], 0));
     }
@@ -670,14 +671,6 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
         per_cu_res = 1;
     if (hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess)
         return cleanup(bfail(QAOA_ERR_DEVICE, "stream creation failed"));
-    if (nmax > qk::kTileBits) {
-        bool ok = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
-        for (int k = 0; k < qk::kManyStreams; ++k)
-            ok = ok && hipStreamCreateWithFlags(&b->streams[k], hipStreamNonBlocking) == hipSuccess &&
-                 hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming) == hipSuccess;
-        if (!ok) return cleanup(bfail(QAOA_ERR_DEVICE, "stream creation failed"));
-    }
-
     const uint64_t slot = 1ull << nmax;
     size_t fr = 0, tot = 0;
     if (hipMemGetInfo(&fr, &tot) != hipSuccess) return cleanup(bfail(QAOA_ERR_DEVICE, "hipMemGetInfo failed"));
@@ -722,6 +715,16 @@ qaoa_status qaoa_batch_create(int32_t count, const int32_t *n, const int64_t *ed
                                             &scratch);
     } catch (...) {
         return cleanup(bfail(QAOA_ERR_OUT_OF_MEMORY, "host allocation"));
+    }
+
+    // a stream with its join event for each that has classes (about 40 us apiece)
+    if (b->nbig) {
+        for (const qk::SizeClass &c : b->classes) b->nstreams = std::max(b->nstreams, c.stream + 1);
+        bool ok = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
+        for (int k = 0; k < b->nstreams; ++k)
+            ok = ok && hipStreamCreateWithFlags(&b->streams[k], hipStreamNonBlocking) == hipSuccess &&
+                 hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming) == hipSuccess;
+        if (!ok) return cleanup(bfail(QAOA_ERR_DEVICE, "stream creation failed"));
     }
 
     qk::BatchArgs &A = b->args;

@@ -314,6 +314,21 @@ void batch_far_sizes()
     }
 }
 
+// A batch has its own stream and one for each size class, up to three.
+void batch_streams()
+{
+    const std::vector<std::vector<int>> batches = {{12, 9}, {13, 13, 9}, {14, 13}, {16, 15, 14, 13, 13, 4}};
+    const int more[] = {0, 1, 2, 3};
+    for (size_t k = 0; k < batches.size(); ++k) {
+        const int before = fake().streams;
+        Batch b(batches[k], std::vector<double>(batches[k].size(), 1.0));
+        b.o.steps = 1;
+        EXPECT(b.create() == QAOA_OK && fake().streams == before + 1 + more[k]);
+        b.run();
+        EXPECT(fake().streams == before + 1 + more[k]);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -328,6 +343,7 @@ int main(int argc, char **argv)
         {"batch_without_class_scratch", batch_without_class_scratch},
         {"batch_phase_bound", batch_phase_bound},
         {"batch_far_sizes", batch_far_sizes},
+        {"batch_streams", batch_streams},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     EXPECT(it != checks.end());

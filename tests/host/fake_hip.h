@@ -23,7 +23,7 @@ struct Fake {
     size_t largest = ~(size_t)0;                  // allocations above this fail
     size_t budget = ~(size_t)0, taken = 0;        // bytes to be had and live
     bool pin_fails = false;
-    int pins = 0, mallocs = 0, copies = 0;
+    int pins = 0, mallocs = 0, copies = 0, streams = 0;
     char *pinned = nullptr;                       // memory that a caller has pinned
     size_t pinned_bytes = 0;
     std::map<void *, int> owner;                  // allocations of other devices than 0
@@ -220,6 +220,7 @@ const char *hipGetErrorString(hipError_t) { return "fake"; }
 hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorInvalidValue; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
 {
+    ++fake().streams;
     *s = (hipStream_t)std::malloc(1);
     return hipSuccess;
 }

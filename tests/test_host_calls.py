@@ -31,7 +31,7 @@ def checks(tmp_path_factory):
 @pytest.mark.parametrize("name", ["pinned_results", "pinning_refused", "host_exports", "device_exports", "memory_checks",
                                   "sample_waits",
                                   "batch_without_class_scratch", "batch_phase_bound",
-                                  "batch_far_sizes"])
+                                  "batch_far_sizes", "batch_streams"])
 def test_host_calls(checks, name):
     out = subprocess.run([checks, name], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and f"{name} ok" in out.stdout, out.stdout + out.stderr
