@@ -98,10 +98,15 @@ namespace {
 
 thread_local qaoa_allocator g_alloc{};  // allocator for handles created on this thread
 
-// Device allocation through the handle's allocator.
+// Device allocation through the handle's allocator.  The runtime keeps a failed one
+// as its last error, which the next launch check would take for its own.
 hipError_t dev_alloc(qaoa_handle h, void **p, size_t bytes)
 {
-    if (!h->alloc.alloc) return hipMalloc(p, bytes);
+    if (!h->alloc.alloc) {
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
+    }
     *p = h->alloc.alloc(bytes, (void *)h->stream, h->alloc.user);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
@@ -1247,7 +1252,6 @@ qaoa_status qaoa_sample(qaoa_handle h, int64_t shots, uint64_t seed, uint64_t *z
     st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nsub + 1 + nscr + nfine + stage);
     if (st == QAOA_ERR_OUT_OF_MEMORY && nfine) {  // the shots do without
         nfine = 0;
-        (void)hipGetLastError();  // the failed allocation is not the next launch's error
         st = ensure_doubles(h, &h->parts, &h->parts_cap, 2 * nsub + 1 + nscr + stage);
     }
     if (st != QAOA_OK) return st;

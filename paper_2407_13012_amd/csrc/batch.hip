@@ -475,6 +475,7 @@ qaoa_status bfail(qaoa_status st, const char *msg)
         hipError_t e_ = (call);                                                \
         if (e_ != hipSuccess) {                                                \
             if (b) (b)->poisoned = true;                                       \
+            (void)hipGetLastError(); /* reported here, not by the next launch check */ \
             qk::set_error_message(std::string(#call " failed: ") + hipGetErrorString(e_)); \
             return QAOA_ERR_DEVICE;                                            \
         }                                                                      \

@@ -606,6 +606,7 @@ namespace {
         hipError_t e_ = (call);                                                        \
         if (e_ != hipSuccess) {                                                        \
             (m)->poisoned = true;                                                      \
+            (void)hipGetLastError(); /* reported here, not by the next launch check */ \
             return mfail(QAOA_ERR_DEVICE, std::string(#call " failed: ") + hipGetErrorString(e_)); \
         }                                                                              \
     } while (0)
@@ -939,6 +940,7 @@ qaoa_status qaoa_mpnn_create(int32_t p, qaoa_mpnn *out)
     m->p = p;
     m->lay = Layout(p);
     auto bad = [&](const char *msg) {
+        (void)hipGetLastError();
         qaoa_mpnn_destroy(m);
         return mfail(QAOA_ERR_DEVICE, msg);
     };

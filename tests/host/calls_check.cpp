@@ -170,6 +170,28 @@ void memory_checks()
     EXPECT(qaoa_create_maxcut(n, 1, e.data(), nullptr, QAOA_C128, nullptr, &h) == QAOA_ERR_OUT_OF_MEMORY);
 }
 
+// A handle is usable after an allocation that failed, its own or another object's.
+void failed_allocations()
+{
+    qaoa_handle h = ring(20);
+    double E, dg[3], db[3];
+    fake().largest = (size_t)1 << 20;
+    EXPECT(qaoa_gradient(h, 3, kGamma, kBeta, &E, dg, db) == QAOA_ERR_OUT_OF_MEMORY);
+    EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK);
+    qaoa_mpnn m = nullptr;
+    fake().largest = 0;
+    EXPECT(qaoa_mpnn_create(4, &m) == QAOA_ERR_DEVICE);
+    EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK);
+    const int32_t n = 9, edge[2] = {0, 1};
+    const int64_t off[2] = {0, 1};
+    qaoa_batch b = nullptr;
+    EXPECT(qaoa_batch_create(1, &n, off, edge, nullptr, 1, nullptr, &b) == QAOA_ERR_DEVICE);
+    EXPECT(qaoa_evaluate(h, 3, kGamma, kBeta, &E) == QAOA_OK);
+    fake().largest = ~(size_t)0;
+    gradient(h);
+    qaoa_destroy(h);
+}
+
 // Shots to device memory return once the total is known, while they run: an event
 // behind the scan.  Shots to host memory wait for the stream, with no event.
 void sample_waits()
@@ -339,6 +361,7 @@ int main(int argc, char **argv)
         {"host_exports", host_exports},
         {"device_exports", device_exports},
         {"memory_checks", memory_checks},
+        {"failed_allocations", failed_allocations},
         {"sample_waits", sample_waits},
         {"batch_without_class_scratch", batch_without_class_scratch},
         {"batch_phase_bound", batch_phase_bound},

@@ -22,6 +22,7 @@ struct Fake {
     size_t free_bytes = 1ull << 40;               // reported as free
     size_t largest = ~(size_t)0;                  // allocations above this fail
     size_t budget = ~(size_t)0, taken = 0;        // bytes to be had and live
+    hipError_t last_error = hipSuccess;           // of a failed call, until it is read
     bool pin_fails = false;
     int pins = 0, mallocs = 0, copies = 0, streams = 0;
     char *pinned = nullptr;                       // memory that a caller has pinned
@@ -129,7 +130,7 @@ hipError_t hipMalloc(void **p, size_t bytes)
 {
     ++fake().mallocs;
     *p = nullptr;
-    if (bytes > fake().largest || bytes > fake().budget - fake().taken) return hipErrorOutOfMemory;
+    if (bytes > fake().largest || bytes > fake().budget - fake().taken) return fake().last_error = hipErrorOutOfMemory;
     uint8_t *q = (uint8_t *)std::malloc(bytes);
     for (size_t i = 0; i < bytes; ++i) q[i] = (uint8_t)(i * 37 + (i >> 8) * 11 + (i >> 16) * 5 + 1) & 0x3f;
     fake().live[q] = bytes;
@@ -152,7 +153,7 @@ hipError_t hipHostMalloc(void **p, size_t bytes, unsigned)
     ++fake().pins;
     fake().log.push_back("pin");
     *p = fake().pin_fails ? nullptr : std::calloc(bytes, 1);
-    return *p ? hipSuccess : hipErrorOutOfMemory;
+    return *p ? hipSuccess : fake().last_error = hipErrorOutOfMemory;
 }
 hipError_t hipHostFree(void *p)
 {
@@ -215,7 +216,12 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, in
     *n = 2;
     return hipSuccess;
 }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void)
+{
+    const hipError_t e = fake().last_error;
+    fake().last_error = hipSuccess;
+    return e;
+}
 const char *hipGetErrorString(hipError_t) { return "fake"; }
 hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorInvalidValue; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)

@@ -29,7 +29,7 @@ def checks(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name", ["pinned_results", "pinning_refused", "host_exports", "device_exports", "memory_checks",
-                                  "sample_waits",
+                                  "failed_allocations", "sample_waits",
                                   "batch_without_class_scratch", "batch_phase_bound",
                                   "batch_far_sizes", "batch_streams"])
 def test_host_calls(checks, name):
