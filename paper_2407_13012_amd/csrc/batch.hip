@@ -4,8 +4,9 @@
 // Instances of more than one tile (n > 12) run in lockstep, all of one size
 // together (batch_many.hip).  The others, one tile each, run in the persistent
 // launch below, which also takes the sizes of which a run's phases could leave the
-// fast reduction's range (mark_far).  A fixed grid of workgroups pops instances from a work queue (largest n
-// first).  A workgroup owns one instance at a time and runs everything for it
+// fast reduction's range (mark_far).  A fixed grid of workgroups pops instances from
+// a work queue (largest n first).  A workgroup owns one instance at a time and runs
+// everything for it
 // in its own scratch slot: the cost diagonal (Sec. IV-A, cut indicator per
 // edge), then for every Adam step one expectation + adjoint gradient (the
 // same tiled passes as the single-instance path, Sec. II-B / IV-C, with the

@@ -10,7 +10,7 @@
 // partials of a step, updates the angles and leaves the rotations' coefficients
 // for the next step's passes.  Sizes are independent of each other and run on
 // three streams.  Measured (p = 4, n ~ U{10..20}): 48 graphs x 8 steps
-// 325 -> 5.0 ms, 1024 graphs x 3 steps 206 -> 26.5 ms (there at 5.5 TB/s;
+// 325 -> 4.7-5.6 ms, 1024 graphs x 3 steps 206 -> 25-27 ms (there at 5.5 TB/s;
 // fewer instances at a time, so that their vectors stay in the last-level cache,
 // are slower: 28.0 ms with 192 MB per size, 33.8 with 64 MB).
 //

@@ -16,8 +16,9 @@
 //     A: lane = bits 0-5,        reg = bits 6-9,         wave = bits 10-11
 //     B: reg = bits 0-3,         lane = bits 4-9,        wave = bits 10-11
 //     C: lane = bits 0-3,6,7,    reg = bits 4,5,10,11,   wave = bits 8-9
-//   For TB = 13 bit 12 is a third wave bit in B and C and lane bit 5 in A,
-//   where its rotation pairs each lane with the lane 32 away.
+//   For TB = 13 bit 12 is a third wave bit in A and C and lane bit 1 in B, where
+//   its rotation pairs each lane with the one 2 away (tile_device.h, which also has
+//   the larger tiles).
 //   Global loads happen in A and stores in C; with k = 10 every access is a
 //   64 B run of consecutive amplitudes, with S >= 6 a run of >= 512 B.
 //

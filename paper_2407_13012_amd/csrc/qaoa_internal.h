@@ -211,11 +211,11 @@ hipError_t launch_many_sp(int mode, const PassArgs &a, const ManyArgs &m, uint64
                           hipStream_t s);
 // Spectator class of a pass on tiles of TB bits with kernels of its own (0 or 2..7), else -1.
 int static_spectators(const Geometry &g, int TB, int mode);
-// out[k] = scale * (sum of slot k); scale 2 for the half sums of a folded state.
 // The passes of a plan_quad plan (phases within the fast reduction's range).
 hipError_t launch_quad(int mode, bool c64, int tbits, const PassArgs &a, uint64_t nblocks, hipStream_t s);
 template <typename R>
 hipError_t launch_quad_real(int mode, int tbits, const PassArgs &a, uint64_t nblocks, hipStream_t s);
+// out[k] = scale * (sum of slot k); scale 2 for the half sums of a folded state.
 hipError_t launch_sum_slots(const double *parts, uint64_t count, uint64_t stride, int nslots, double scale,
                             double *out, hipStream_t s);
 
